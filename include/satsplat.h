@@ -433,7 +433,7 @@ ss_status ss_mlp_backward(ss_mlp *mlp, const float *w, const float *pts, const f
  * memory (code under HIP graph capture, tight training or serving loops, harnesses that
  * forbid hipMalloc).  Same arguments, outputs and rounding as ss_mlp_backward (the same
  * kernels run), but the MLP needs no bound workspace: the buffers live in a fixed device
- * array inside the library of 15.1 MiB per device (held from library load until the
+ * array inside the library of 8.2 MiB per device (held from library load until the
  * process ends), laid out for M <= SS_NOALLOC_MAX_POINTS points; a larger M returns
  * SS_ERR_CAPACITY and launches nothing.  The call allocates nothing, device or host
  * memory.  All calls on one device share that array: calls that overlap on one device

@@ -415,12 +415,10 @@ static ss_status upload_views(ss_plan *p)
 
 // ------------------------------------------------------------------ surrogate MLP
 // Byte offsets of the MLP's buffers for batches of up to `maxp` points: BF16 / FP32 weight
-// copies, saved features and activations, logits, activation gradients, per-block partial
-// weight gradients and output-layer partials.  constexpr so that the allocation-free
-// training entry point can size its static scratch array at compile time.
+// copies (inference) and the training blocks' partial gradients.  constexpr so that the
+// allocation-free training entry point can size its static scratch array at compile time.
 struct MlpLayout {
-    size_t o_wb = 0, o_wf = 0, o_F = 0, o_H = 0, o_logit = 0, o_dA = 0, o_pdw = 0, o_pdb = 0,
-           o_pout = 0, total = 0;
+    size_t o_wb = 0, o_wf = 0, o_part = 0, total = 0;
 };
 
 static constexpr MlpLayout mlp_layout_for(int64_t maxp)
@@ -428,24 +426,15 @@ static constexpr MlpLayout mlp_layout_for(int64_t maxp)
     MlpLayout L{};
     size_t o = 0;
     auto take = [&o](size_t b) { size_t r = o; o += (b + 255) & ~size_t(255); return r; };
-    const size_t M = (size_t)(maxp > 0 ? maxp : 0);
-    const size_t nblk = (M + kDwChunk - 1) / kDwChunk;   // mlp_dw_blocks(M)
-    const size_t nout = (M + 255) / 256;
     L.o_wb = take(kMlpBf16 * 2);
     L.o_wf = take(kMlpF32 * 4);
-    L.o_F = take(M * kMlpIn * 2);
-    L.o_H = take(3 * M * kMlpWidth * 2);
-    L.o_logit = take(M * 4);
-    L.o_dA = take(2 * M * kMlpWidth * 2);
-    L.o_pdw = take(nblk * kMlpWidth * kMlpIn * 4);
-    L.o_pdb = take(nblk * kMlpWidth * 4);
-    L.o_pout = take(nout * 66 * 4);
+    L.o_part = take((size_t)mlp_train_blocks(maxp > 0 ? maxp : 0) * kTrStride * 4);
     L.total = o;
     return L;
 }
 
 // Allocation-free MLP backward (ss_mlp_backward_noalloc): its buffers live in this fixed
-// device array, laid out for batches of up to kNoAllocMaxPoints points (15.1 MiB), not in
+// device array, laid out for batches of up to kNoAllocMaxPoints points (8.2 MiB), not in
 // a bound workspace.  Every device holds its own copy.  Host code never passes the
 // array's name to a kernel (on the host it is only a stand-in symbol): the device
 // address comes from hipGetSymbolAddress, once per device, when a context is created on
@@ -1207,56 +1196,9 @@ ss_status ss_mlp_forward(ss_mlp *m, const float *w, const float *pts, int64_t n_
     SS_HIP(launch_mlp_prep(w, m->at<uint16_t>(m->L.o_wb), m->at<float>(m->L.o_wf), st));
     const int64_t M = all_pairs ? n_pts * n_sun : n_pts;
     SS_HIP(launch_mlp_forward(m->at<uint16_t>(m->L.o_wb), m->at<float>(m->L.o_wf), pts, sun, M,
-                              all_pairs ? n_pts : 0, mlp_norm(m), prob != 0, out, nullptr, nullptr,
-                              st));
+                              all_pairs ? n_pts : 0, mlp_norm(m), prob != 0, out, st));
     return SS_OK;
 }
-
-}  // extern "C"
-
-// MLP backward (recomputing forward + BCE / given-logit-gradient adjoint + weight
-// gradients) with its buffers at `base` laid out by L (L sized for >= M points).
-static ss_status mlp_backward_at(const ss_mlp *m, char *base, const MlpLayout &L, const float *w,
-                                 const float *pts, const float *sun, int64_t M,
-                                 const float *labels, const float *d_logits, float scale,
-                                 float *d_w, float *loss, hipStream_t st)
-{
-    auto at16 = [base](size_t off) { return reinterpret_cast<uint16_t *>(base + off); };
-    auto at32 = [base](size_t off) { return reinterpret_cast<float *>(base + off); };
-    uint16_t *wb = at16(L.o_wb);
-    float *wf = at32(L.o_wf);
-    uint16_t *F = at16(L.o_F);
-    uint16_t *H = at16(L.o_H);
-    uint16_t *H1 = H, *H2 = H + M * kMlpWidth, *H3 = H + 2 * M * kMlpWidth;
-    uint16_t *dA0 = at16(L.o_dA), *dA1 = dA0 + M * kMlpWidth;
-    float *logit = at32(L.o_logit);
-    float *pdw = at32(L.o_pdw), *pdb = at32(L.o_pdb), *pout = at32(L.o_pout);
-    const int nblk = mlp_dw_blocks(M);
-    const int nout = (int)((M + 255) / 256);
-    SS_HIP(launch_mlp_prep(w, wb, wf, st));
-    // saved activations: saveH holds h1, h2, h3 contiguous ([3][M][64])
-    SS_HIP(launch_mlp_forward(wb, wf, pts, sun, M, 0, mlp_norm(m), false, logit, F, H, st));
-    SS_HIP(launch_mlp_out_bwd(logit, labels, d_logits, scale, wb, H3, M, dA0, pout, st));
-    SS_HIP(launch_mlp_reduce(pout, nout, kMlpWidth + 1, 66, d_w + kOffW4, st));
-    if (loss) SS_HIP(launch_mlp_reduce(pout + 65, nout, 1, 66, loss, st));
-    // layer 3
-    SS_HIP(launch_mlp_dw(dA0, H2, kMlpWidth, M, pdw, pdb, st));
-    SS_HIP(launch_mlp_reduce(pdw, nblk, kMlpW3, kMlpW3, d_w + kOffW3, st));
-    SS_HIP(launch_mlp_reduce(pdb, nblk, kMlpWidth, kMlpWidth, d_w + kOffB3, st));
-    SS_HIP(launch_mlp_dh(dA0, wb + kMlpW1 + kMlpW2, H2, M, dA1, st));
-    // layer 2
-    SS_HIP(launch_mlp_dw(dA1, H1, kMlpWidth, M, pdw, pdb, st));
-    SS_HIP(launch_mlp_reduce(pdw, nblk, kMlpW2, kMlpW2, d_w + kOffW2, st));
-    SS_HIP(launch_mlp_reduce(pdb, nblk, kMlpWidth, kMlpWidth, d_w + kOffB2, st));
-    SS_HIP(launch_mlp_dh(dA1, wb + kMlpW1, H1, M, dA0, st));
-    // layer 1
-    SS_HIP(launch_mlp_dw(dA0, F, kMlpIn, M, pdw, pdb, st));
-    SS_HIP(launch_mlp_reduce(pdw, nblk, kMlpW1, kMlpW1, d_w + kOffW1, st));
-    SS_HIP(launch_mlp_reduce(pdb, nblk, kMlpWidth, kMlpWidth, d_w + kOffB1, st));
-    return SS_OK;
-}
-
-extern "C" {
 
 ss_status ss_mlp_backward(ss_mlp *m, const float *w, const float *pts, const float *sun, int64_t M,
                           const float *labels, const float *d_logits, float scale, float *d_w,
@@ -1267,8 +1209,9 @@ ss_status ss_mlp_backward(ss_mlp *m, const float *w, const float *pts, const flo
         return fail(SS_ERR_INVALID_ARG, "NULL pointer");
     if (M < 1 || M > m->maxp) return fail(SS_ERR_CAPACITY, "M must be in [1, max_points]");
     SS_HIP(hipSetDevice(m->ctx->device));
-    return mlp_backward_at(m, m->ws, m->L, w, pts, sun, M, labels, d_logits, scale, d_w, loss,
-                           reinterpret_cast<hipStream_t>(stream));
+    SS_HIP(launch_mlp_train(w, pts, sun, M, labels, d_logits, scale, mlp_norm(m),
+                            m->at<float>(m->L.o_part), d_w, loss, reinterpret_cast<hipStream_t>(stream)));
+    return SS_OK;
 }
 
 ss_status ss_mlp_backward_noalloc(ss_mlp *m, const float *w, const float *pts, const float *sun,
@@ -1283,8 +1226,10 @@ ss_status ss_mlp_backward_noalloc(ss_mlp *m, const float *w, const float *pts, c
                                          std::to_string(kNoAllocMaxPoints) + "]");
     if (!m->ctx->scratch) return fail(SS_ERR_STATE, "no scratch array on this device");
     SS_HIP(hipSetDevice(m->ctx->device));
-    return mlp_backward_at(m, m->ctx->scratch, kNoAllocLayout, w, pts, sun, M, labels, d_logits,
-                           scale, d_w, loss, reinterpret_cast<hipStream_t>(stream));
+    SS_HIP(launch_mlp_train(w, pts, sun, M, labels, d_logits, scale, mlp_norm(m),
+                            reinterpret_cast<float *>(m->ctx->scratch + kNoAllocLayout.o_part), d_w,
+                            loss, reinterpret_cast<hipStream_t>(stream)));
+    return SS_OK;
 }
 
 ss_status ss_mlp_adam(float *w, float *m, float *v, const float *g, int64_t n, float lr, float beta1,
@@ -1317,8 +1262,7 @@ ss_status ss_shadow_surrogate(ss_plan *p, ss_mlp *mlp, const float *w, const ss_
         StageScope scope(p, SS_STAGE_MLP, st);
         SS_HIP(launch_mlp_prep(w, mlp->at<uint16_t>(mlp->L.o_wb), mlp->at<float>(mlp->L.o_wf), st));
         SS_HIP(launch_mlp_forward(mlp->at<uint16_t>(mlp->L.o_wb), mlp->at<float>(mlp->L.o_wf), s->mean,
-                                  v->sun, p->n * (int64_t)p->nv, p->n, mlp_norm(mlp), true, vis,
-                                  nullptr, nullptr, st));
+                                  v->sun, p->n * (int64_t)p->nv, p->n, mlp_norm(mlp), true, vis, st));
     }
     // band 0: no point can fall back, the network's output is the whole pass
     if (band == 0.f) return SS_OK;

@@ -13,7 +13,8 @@
 // so the 96 sin/cos values of a point are spread over 4 lanes with no duplication and no
 // LDS staging; the layers are computed transposed so that hidden activations stay in
 // registers (see k_mlp_forward).  Weights live in LDS, row-major [out][in], so a weight
-// operand is 16 contiguous bytes.  The backward kernels work on 32-point tiles.
+// operand is 16 contiguous bytes.  Training is one kernel that runs forward and backward
+// of 128 points per block step (see k_mlp_train) and one that sums its partial gradients.
 #include "ss_internal.h"
 #include "ss_mlp.h"
 
@@ -23,7 +24,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16;
 
-constexpr int kPtsPerWave = 32;
 // the forward takes kFwdPT tiles of 16 points per wave step: each weight fragment read
 // from LDS feeds kFwdPT independent MFMA chains
 constexpr int kFwdPT = 4;
@@ -49,12 +49,6 @@ union Frag {
 __device__ __forceinline__ f32x4 mfma(const Frag &a, const Frag &b, f32x4 c)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
-}
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v)
-{
-    return __builtin_amdgcn_update_dpp(0.f, v, CTRL, 0xF, 0xF, true);
 }
 
 // --------------------------------------------------------------- weight prep
@@ -146,6 +140,12 @@ __device__ __forceinline__ int hidden_input(int k)
     return 16 * (2 * ks + (e >> 2)) + 4 * q + (e & 3);
 }
 
+// ... and back: neuron -> the input index that names it (two bit fields swapped)
+__device__ __forceinline__ int hidden_slot(int j)
+{
+    return (j & 0x23) | ((j & 0x0C) << 1) | ((j & 0x10) >> 2);
+}
+
 __device__ __forceinline__ void load_weights(MlpLds &L, const u16 *wb, const float *wf)
 {
     const uint4 *src = reinterpret_cast<const uint4 *>(wb);
@@ -161,34 +161,19 @@ __device__ __forceinline__ void load_weights(MlpLds &L, const u16 *wb, const flo
     for (int i = threadIdx.x; i < 3 * kMlpWidth + 1; i += blockDim.x) L.b[i] = wf[i];
 }
 
-// acc[rt][ct] (16x16 tiles) += A (32 x K, operand frags from `a`) * W^T
-template <int KSTEPS>
-__device__ __forceinline__ void layer_mfma(const Frag (&a)[2][KSTEPS], const u16 *W, int ldw,
-                                           int lane, f32x4 (&acc)[2][4])
-{
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-            Frag b;
-            b.q = *reinterpret_cast<const uint4 *>(W + (ct * 16 + (lane & 15)) * ldw + ks * 32 +
-                                                   8 * (lane >> 4));
-#pragma unroll
-            for (int rt = 0; rt < 2; ++rt) acc[rt][ct] = mfma(a[rt][ks], b, acc[rt][ct]);
-        }
-    }
-}
-
-// One layer, transposed: acc[ot][pt] (neurons 16 ot.., points 16 pt..) = bias +
-// W[ot rows] x[pt] over KSTEPS k-steps; W row-major [out][in] (in LDS).
+// One layer, transposed: acc[ot][pt] (neurons 16 ot.., points 16 pt..) = bias (zero when
+// null) + W[ot rows] x[pt] over KSTEPS k-steps; W row-major [out][in] (in LDS).
 template <int KSTEPS, int PT>
 __device__ __forceinline__ void layer_t(const u16 *W, int ldw, const float *bias,
                                         const Frag (&x)[PT][KSTEPS], int lane, f32x4 (&acc)[4][PT])
 {
 #pragma unroll
     for (int ot = 0; ot < 4; ++ot) {
-        const float *bo = bias + ot * 16 + 4 * (lane >> 4);
-        const f32x4 b0 = f32x4{bo[0], bo[1], bo[2], bo[3]};
+        f32x4 b0 = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (bias) {
+            const float *bo = bias + ot * 16 + 4 * (lane >> 4);
+            b0 = f32x4{bo[0], bo[1], bo[2], bo[3]};
+        }
 #pragma unroll
         for (int pt = 0; pt < PT; ++pt) acc[ot][pt] = b0;
 #pragma unroll
@@ -230,36 +215,12 @@ __device__ __forceinline__ void relu_to_operand(const f32x4 (&acc)[4][PT], Frag 
         }
 }
 
-// the activations of one layer for the backward, [M][64] in neuron order: 4 consecutive
-// neurons (8 bytes) per lane and accumulator tile
-template <int PT>
-__device__ __forceinline__ void save_layer(const Frag (&h)[PT][2], u16 *dst, int64_t base, int64_t M,
-                                           int lane)
-{
-#pragma unroll
-    for (int pt = 0; pt < PT; ++pt) {
-        const int64_t i = base + pt * 16 + (lane & 15);
-        if (i >= M) continue;
-#pragma unroll
-        for (int ot = 0; ot < 4; ++ot) {
-            const Frag &f = h[pt][ot >> 1];
-            const int e0 = 4 * (ot & 1);
-            uint2 v;
-            v.x = (uint32_t)f.h[e0] | ((uint32_t)f.h[e0 + 1] << 16);
-            v.y = (uint32_t)f.h[e0 + 2] | ((uint32_t)f.h[e0 + 3] << 16);
-            *reinterpret_cast<uint2 *>(dst + i * kMlpWidth + ot * 16 + 4 * (lane >> 4)) = v;
-        }
-    }
-}
-
 // Forward over M points.  Point i uses position pts[i % G] and sun[i / G] when G > 0
-// (every surfel under every sun), or pts[i] and sun[i] when G == 0.  When `saveF` /
-// `saveH` are given the bf16 features [M,128] and hidden activations [3][M,64] are
-// written for the backward.
+// (every surfel under every sun), or pts[i] and sun[i] when G == 0.
 __global__ __launch_bounds__(kMlpThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_mlp_forward(
     const u16 *__restrict__ wb, const float *__restrict__ wf, const float *__restrict__ pts,
     const float *__restrict__ sun, int64_t M, int64_t G, MlpNorm nz, int prob,
-    float *__restrict__ out, u16 *__restrict__ saveF, u16 *__restrict__ saveH)
+    float *__restrict__ out)
 {
     __shared__ MlpLds L;
     load_weights(L, wb, wf);
@@ -297,8 +258,7 @@ __global__ __launch_bounds__(kMlpThreads) __attribute__((amdgpu_waves_per_eu(3))
 #pragma unroll
         for (int pt = 0; pt < PT; ++pt) {
             int64_t i = base + pt * 16 + (lane & 15);
-            const bool valid = i < M;
-            if (!valid) i = M - 1;
+            if (i >= M) i = M - 1;
             int64_t ip = i, is = i;
             if (G > 0) {
                 ip = ip0 + (i - base);
@@ -312,24 +272,15 @@ __global__ __launch_bounds__(kMlpThreads) __attribute__((amdgpu_waves_per_eu(3))
             for (int ks = 0; ks < 3; ++ks) feature_chunk(ph[ks], lane >> 4, fa[pt][ks]);
             if (!one_sun) sun_chunk(sun[2 * is], sun[2 * is + 1], lane >> 4, fa[pt][3]);
             else fa[pt][3] = fsun;
-            if (saveF && valid) {
-#pragma unroll
-                for (int ks = 0; ks < 4; ++ks)
-                    *reinterpret_cast<uint4 *>(saveF + i * kMlpIn + ks * 32 + 8 * (lane >> 4)) =
-                        fa[pt][ks].q;
-            }
         }
         f32x4 acc[4][PT];
         Frag h[PT][2];
         layer_t<4>(L.W1, kLdIn, L.b, fa, lane, acc);
         relu_to_operand(acc, h);
-        if (saveH) save_layer(h, saveH, base, M, lane);
         layer_t<2>(L.W2, kLdWidth, L.b + kMlpWidth, h, lane, acc);
         relu_to_operand(acc, h);
-        if (saveH) save_layer(h, saveH + M * kMlpWidth, base, M, lane);
         layer_t<2>(L.W3, kLdWidth, L.b + 2 * kMlpWidth, h, lane, acc);
         relu_to_operand(acc, h);
-        if (saveH) save_layer(h, saveH + 2 * M * kMlpWidth, base, M, lane);
         // ---- output: logit = w4 . h3 + b4, one more transposed MFMA layer whose weight
         // operand holds w4 in row 0: lane n < 16 gets point n's logit in element 0
         float part[PT];
@@ -353,192 +304,297 @@ __global__ __launch_bounds__(kMlpThreads) __attribute__((amdgpu_waves_per_eu(3))
     }
 }
 
-// ------------------------------------------------------------- output backward
-// Per point: dlogit, BCE loss, da3 = bf16(dlogit * w4 * [h3 > 0]); per block the sums
-// of dlogit * h3 (dw4), dlogit (db4) and the loss -> part[blk][66].
-__global__ __launch_bounds__(256) void k_mlp_out_bwd(
-    const float *__restrict__ logits, const float *__restrict__ labels,
-    const float *__restrict__ dlin, float scale, const u16 *__restrict__ wb,
-    const u16 *__restrict__ H3, int64_t M, u16 *__restrict__ dA3, float *__restrict__ part)
+// ------------------------------------------------------------------- training
+// Loss and weight gradients of M paired points.  Per point: dlogit = (sigmoid(logit) - y)
+// scale or d_logits scale, da3 = bf16(dlogit w4 [h3 > 0]), da2 = bf16((W3^T da3) [h2 > 0]),
+// da1 = bf16((W2^T da2) [h1 > 0]); dW_l = sum da_l h_(l-1)^T, db_l = sum da_l, dw4 = sum
+// dlogit h3, db4 = sum dlogit.
+//
+// A wave takes a 16-point tile through forward and backward, the block's eight waves 128
+// points per step.  Activations and their gradients go to LDS twice: transposed [neuron]
+// [point], where 8 consecutive points of a neuron are an operand of the weight-gradient
+// products (the contraction runs over points), and the gradients also as [point][neuron],
+// the operand of the next layer's product.  Each wave owns 16 rows of half of every dW in registers
+// over all of its block's steps, so partial gradients leave the chip once per block, and
+// features and activations never do.  Biases come from a column of ones.
+// The step is bound by latency (3 forward and 2 backward layers, each a chain of LDS
+// writes, a barrier and MFMAs), so the grid is one block per CU with two waves per SIMD
+// (four waves of two tiles each: 36.4 and 19.9 us against 30.2 and 16.6).
+// One forward + backward + Adam: 65,536 points 32.6 us, 6,001 points
+// 21.2 us (as separate forward, output, weight-gradient and activation-gradient kernels per
+// layer with serial reductions: 525 and 260 us).
+constexpr int kTrThreads = 512, kTrWaves = kTrThreads / 64, kTrPT = 1;
+static_assert(kTrBlockPts == 16 * kTrPT * kTrWaves, "points per block step");
+constexpr int kLdPts = kTrBlockPts + 8;      // padded [neuron][point] rows
+
+struct MlpTrainLds {
+    u16 W1[kMlpWidth * kLdIn];
+    u16 W2[kMlpWidth * kLdWidth], W3[kMlpWidth * kLdWidth];     // columns permuted
+    u16 W2t[kMlpWidth * kLdWidth], W3t[kMlpWidth * kLdWidth];   // [in][out]
+    u16 Ft[kMlpIn * kLdPts];                                   // features [feature][point]
+    u16 H1t[kMlpWidth * kLdPts], H2t[kMlpWidth * kLdPts];       // activations [neuron][point]
+    u16 dAt[kMlpWidth * kLdPts];                                // gradients [neuron][point]
+    u16 dA[kTrBlockPts * kLdWidth];                             // gradients [point][neuron]
+    float b[3 * kMlpWidth + 1];
+    float red[kTrWaves][kMlpWidth + 2];
+};
+
+// Operand fragments of 16 points (hidden numbering) -> dst[neuron][point]
+__device__ __forceinline__ void store_transposed(const Frag (&h)[2], u16 *dst, int point, int g)
 {
-    __shared__ float dl[256];
-    __shared__ float red[4][66];
-    __shared__ float w4s[kMlpWidth];
-    if (threadIdx.x < kMlpWidth) w4s[threadIdx.x] = bf2f(wb[kMlpW1 + kMlpW2 + kMlpW3 + threadIdx.x]);
-    const int64_t base = (int64_t)blockIdx.x * 256;
-    const int64_t m = base + threadIdx.x;
-    float d = 0.f, loss = 0.f;
-    if (m < M) {
-        const float lg = logits[m];
-        if (labels) {
-            const float y = labels[m];
-            d = (1.f / (1.f + expf(-lg)) - y) * scale;
-            loss = (fmaxf(lg, 0.f) - lg * y + log1pf(expf(-fabsf(lg)))) * scale;
-        } else {
-            d = dlin[m] * scale;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            dst[(16 * (2 * ks + (e >> 2)) + 4 * g + (e & 3)) * kLdPts + point] = h[ks].h[e];
+}
+
+// ... and -> dst[point][neuron], four consecutive neurons per store
+__device__ __forceinline__ void store_points(const Frag (&h)[2], u16 *dst, int point, int g)
+{
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        uint2 *row = reinterpret_cast<uint2 *>(dst + point * kLdWidth + 32 * ks + 4 * g);
+        row[0] = make_uint2(h[ks].q.x, h[ks].q.y);
+        row[4] = make_uint2(h[ks].q.z, h[ks].q.w);
+    }
+}
+
+// bf16(x [h > 0]) of a layer's accumulators, in the hidden numbering of h's fragments
+template <int PT>
+__device__ __forceinline__ void mask_to_operand(const f32x4 (&acc)[4][PT], const Frag (&h)[PT][2],
+                                                Frag (&d)[PT][2])
+{
+#pragma unroll
+    for (int pt = 0; pt < PT; ++pt)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                d[pt][ks].h[e] = h[pt][ks].h[e] != 0 ? f2bf(acc[2 * ks + (e >> 2)][pt][e & 3]) : (u16)0;
+}
+
+// dw[jt] (16 rows i0 .. of dW, columns j0 + 16 jt ..) += dAt[rows] Ht[columns]^T over the
+// block's points; db += dAt[rows] 1
+template <int NJ>
+__device__ __forceinline__ void weight_grads(const u16 *dAt, const u16 *Ht, int i0, int j0, int lane,
+                                             f32x4 (&dw)[NJ], f32x4 &db)
+{
+    const int r = lane & 15, g = lane >> 4;
+    Frag ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones.h[e] = 0x3F80;
+#pragma unroll
+    for (int kk = 0; kk < kTrBlockPts / 32; ++kk) {
+        Frag a;
+        a.q = *reinterpret_cast<const uint4 *>(dAt + (i0 + r) * kLdPts + 32 * kk + 8 * g);
+        db = mfma(a, ones, db);
+#pragma unroll
+        for (int jt = 0; jt < NJ; ++jt) {
+            Frag b;
+            b.q = *reinterpret_cast<const uint4 *>(Ht + (j0 + 16 * jt + r) * kLdPts + 32 * kk + 8 * g);
+            dw[jt] = mfma(a, b, dw[jt]);
         }
     }
-    dl[threadIdx.x] = d;
-    __syncthreads();
-    if (m < M) {
-        const u16 *h = H3 + m * kMlpWidth;
-        u16 *o = dA3 + m * kMlpWidth;
-        for (int j = 0; j < kMlpWidth; ++j) {
-            const u16 hj = h[j];
-            o[j] = f2bf((hj != 0 && !(hj & 0x8000)) ? d * w4s[j] : 0.f);
-        }
+}
+
+__global__ __launch_bounds__(kTrThreads) void k_mlp_train(
+    const float *__restrict__ w, const float *__restrict__ pts, const float *__restrict__ sun,
+    int64_t M, const float *__restrict__ labels, const float *__restrict__ dlin, float scale,
+    MlpNorm nz, float *__restrict__ part)
+{
+    __shared__ MlpTrainLds L;
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 4, col = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // this wave's share of the weight gradients: rows i0 .. i0 + 15, columns from half the width
+    const int i0 = 16 * (wave & 3), half = wave >> 2;
+    // unrolled, so that a thread's loads are in flight together
+#pragma unroll
+    for (int q = 0; q < kMlpW1 / kTrThreads; ++q) {
+        const int i = q * kTrThreads + tid;
+        L.W1[(i / kMlpIn) * kLdIn + i % kMlpIn] = f2bf(w[kOffW1 + i]);
     }
-    // column sums: thread t -> column j = t & 63 over points q = t >> 6 (+4)
-    const int j = threadIdx.x & 63, q = threadIdx.x >> 6;
-    float s = 0.f;
-    for (int p = q; p < 256; p += 4)
-        if (base + p < M) s += dl[p] * bf2f(H3[(base + p) * kMlpWidth + j]);
-    red[q][j] = s;
-    if (threadIdx.x < 4) {
-        float a = 0.f, b = 0.f;
-        for (int p = threadIdx.x; p < 256; p += 4) a += dl[p];
-        red[threadIdx.x][64] = a;
-        red[threadIdx.x][65] = 0.f;
+#pragma unroll
+    for (int q = 0; q < kMlpW2 / kTrThreads; ++q) {
+        const int i = q * kTrThreads + tid, o = i / kMlpWidth, k = i % kMlpWidth;
+        const u16 w2 = f2bf(w[kOffW2 + i]), w3 = f2bf(w[kOffW3 + i]);
+        const int p = o * kLdWidth + hidden_slot(k);
+        L.W2[p] = w2;
+        L.W3[p] = w3;
+        L.W2t[k * kLdWidth + o] = w2;
+        L.W3t[k * kLdWidth + o] = w3;
     }
+    if (tid < kMlpWidth) {
+        L.b[tid] = w[kOffB1 + tid];
+        L.b[kMlpWidth + tid] = w[kOffB2 + tid];
+        L.b[2 * kMlpWidth + tid] = w[kOffB3 + tid];
+    }
+    if (tid == 0) L.b[3 * kMlpWidth] = w[kOffB4];
+    // rows of Ft past the 100 features stay zero
+    for (int i = tid; i < (kMlpIn - 96) * kLdPts; i += kTrThreads) L.Ft[96 * kLdPts + i] = 0;
+    // output weights (bf16) in the hidden numbering, for every row of a weight operand: each
+    // lane group then finds its own point's logit in element 0
+    Frag a4[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a4[ks].h[e] = f2bf(w[kOffW4 + hidden_input(32 * ks + 8 * g + e)]);
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 dw1[4], dw2[2], dw3[2], db1 = zero, db2 = zero, db3 = zero;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) dw1[j] = zero;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) dw2[j] = dw3[j] = zero;
+    float dw4[2][8], db4 = 0.f, loss = 0.f;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) dw4[k >> 3][k & 7] = 0.f;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        // loss: simple serial sum over the block (training-only path)
-        float l = 0.f;
-        for (int p = 0; p < 256; ++p) {
-            const int64_t mm = base + p;
-            if (mm < M && labels) {
-                const float lg = logits[mm], y = labels[mm];
-                l += (fmaxf(lg, 0.f) - lg * y + log1pf(expf(-fabsf(lg)))) * scale;
+    for (int64_t base = (int64_t)blockIdx.x * kTrBlockPts; base < M;
+         base += (int64_t)gridDim.x * kTrBlockPts) {
+        Frag fa[kTrPT][4], h1[kTrPT][2], h2[kTrPT][2], h[kTrPT][2], d[kTrPT][2];
+        f32x4 acc[4][kTrPT];
+        int slot[kTrPT];
+#pragma unroll
+        for (int pt = 0; pt < kTrPT; ++pt) {
+            slot[pt] = (wave * kTrPT + pt) * 16 + col;
+            const int64_t i = min(base + slot[pt], M - 1);
+            const float ph[3] = {__fmul_rn(__fsub_rn(pts[3 * i], nz.cx), nz.inv_half),
+                                 __fmul_rn(__fsub_rn(pts[3 * i + 1], nz.cy), nz.inv_half),
+                                 __fmul_rn(__fsub_rn(pts[3 * i + 2], nz.cz), nz.inv_half)};
+#pragma unroll
+            for (int ks = 0; ks < 3; ++ks) {
+                feature_chunk(ph[ks], g, fa[pt][ks]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    L.Ft[(32 * ks + 8 * g + e) * kLdPts + slot[pt]] = fa[pt][ks].h[e];
+            }
+            sun_chunk(sun[2 * i], sun[2 * i + 1], g, fa[pt][3]);
+            if (g == 0) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) L.Ft[(96 + e) * kLdPts + slot[pt]] = fa[pt][3].h[e];
             }
         }
-        red[0][65] = l;
-    }
-    (void)loss;
-    __syncthreads();
-    if (threadIdx.x < 66) {
-        float t = red[0][threadIdx.x];
-        if (threadIdx.x < 65) t += red[1][threadIdx.x] + red[2][threadIdx.x] + red[3][threadIdx.x];
-        part[(int64_t)blockIdx.x * 66 + threadIdx.x] = t;
-    }
-}
-
-// ------------------------------------------------------------ weight gradients
-// part_dw[blk][i][j] = sum over the block's kDwChunk points of dA[m][i] H[m][j] (MFMA,
-// the point index is the contraction), part_db[blk][i] = sum of dA[m][i].
-template <int N>
-__global__ __launch_bounds__(256) void k_mlp_dw(const u16 *__restrict__ dA,
-                                                const u16 *__restrict__ H, int64_t M,
-                                                float *__restrict__ part_dw,
-                                                float *__restrict__ part_db)
-{
-    __shared__ u16 sA[32 * kMlpWidth];
-    __shared__ u16 sH[32 * N];
-    const int lane = threadIdx.x & 63, rt = threadIdx.x >> 6;
-    constexpr int NCT = N / 16;
-    f32x4 acc[NCT];
+        layer_t<4>(L.W1, kLdIn, L.b, fa, lane, acc);
+        relu_to_operand(acc, h1);
+        layer_t<2>(L.W2, kLdWidth, L.b + kMlpWidth, h1, lane, acc);
+        relu_to_operand(acc, h2);
+        layer_t<2>(L.W3, kLdWidth, L.b + 2 * kMlpWidth, h2, lane, acc);
+        relu_to_operand(acc, h);
 #pragma unroll
-    for (int ct = 0; ct < NCT; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float db = 0.f;
-    const int64_t m0 = (int64_t)blockIdx.x * kDwChunk;
-    for (int ks = 0; ks < kDwChunk / 32; ++ks) {
-        const int64_t mb = m0 + ks * 32;
-        __syncthreads();
-        {   // 32 x 64 bf16 of dA: one uint4 per thread
-            const int r = threadIdx.x >> 3, c = (threadIdx.x & 7) * 8;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (mb + r < M) v = *reinterpret_cast<const uint4 *>(dA + (mb + r) * kMlpWidth + c);
-            *reinterpret_cast<uint4 *>(sA + r * kMlpWidth + c) = v;
-        }
-        for (int e = threadIdx.x; e < 32 * N / 8; e += 256) {
-            const int r = e / (N / 8), c = (e % (N / 8)) * 8;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (mb + r < M) v = *reinterpret_cast<const uint4 *>(H + (mb + r) * N + c);
-            *reinterpret_cast<uint4 *>(sH + r * N + c) = v;
-        }
-        __syncthreads();
-        if (threadIdx.x < kMlpWidth)
-            for (int r = 0; r < 32; ++r) db += bf2f(sA[r * kMlpWidth + threadIdx.x]);
-        Frag a;
-        const int i = rt * 16 + (lane & 15), g = lane >> 4;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) a.h[q] = sA[(8 * g + q) * kMlpWidth + i];
-#pragma unroll
-        for (int ct = 0; ct < NCT; ++ct) {
-            Frag b;
-            const int j = ct * 16 + (lane & 15);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) b.h[q] = sH[(8 * g + q) * N + j];
-            acc[ct] = mfma(a, b, acc[ct]);
-        }
-    }
-    float *out = part_dw + (int64_t)blockIdx.x * kMlpWidth * N;
-#pragma unroll
-    for (int ct = 0; ct < NCT; ++ct)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = rt * 16 + 4 * (lane >> 4) + r, j = ct * 16 + (lane & 15);
-            out[i * N + j] = acc[ct][r];
-        }
-    if (threadIdx.x < kMlpWidth) part_db[(int64_t)blockIdx.x * kMlpWidth + threadIdx.x] = db;
-}
-
-// ------------------------------------------------------- propagated activations
-// dA_prev[m][j] = bf16( sum_i dA[m][i] W[i][j] * [Hprev[m][j] > 0] ), W = [out i][in j].
-__global__ __launch_bounds__(256) void k_mlp_dh(const u16 *__restrict__ dA,
-                                                const u16 *__restrict__ Wb,
-                                                const u16 *__restrict__ Hprev, int64_t M,
-                                                u16 *__restrict__ dAp)
-{
-    __shared__ u16 Wt[kMlpWidth * kMlpWidth];   // Wt[j][i] = W[i][j]
-    for (int e = threadIdx.x; e < kMlpWidth * kMlpWidth; e += 256) {
-        const int i = e / kMlpWidth, j = e % kMlpWidth;
-        Wt[j * kMlpWidth + i] = Wb[e];
-    }
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
-    const int64_t ntile = (M + kPtsPerWave - 1) / kPtsPerWave;
-    for (int64_t tile = (int64_t)blockIdx.x * kMlpWaves + wave; tile < ntile;
-         tile += (int64_t)gridDim.x * kMlpWaves) {
-        const int64_t base = tile * kPtsPerWave;
-        Frag a[2][2];
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-            const int64_t m = base + rt * 16 + (lane & 15);
+        for (int pt = 0; pt < kTrPT; ++pt) {
+            store_transposed(h1[pt], L.H1t, slot[pt], g);
+            store_transposed(h2[pt], L.H2t, slot[pt], g);
+            f32x4 o = mfma(a4[0], h[pt][0], zero);
+            o = mfma(a4[1], h[pt][1], o);
+            const float lg = o[0] + L.b[3 * kMlpWidth];
+            const int64_t i = base + slot[pt];
+            float dl = 0.f;
+            if (i < M) {
+                if (labels) {
+                    const float y = labels[i];
+                    dl = (1.f / (1.f + expf(-lg)) - y) * scale;
+                    if (g == 0) loss += (fmaxf(lg, 0.f) - lg * y + log1pf(expf(-fabsf(lg)))) * scale;
+                } else {
+                    dl = dlin[i] * scale;
+                }
+                if (g == 0) db4 += dl;
+            }
 #pragma unroll
             for (int ks = 0; ks < 2; ++ks)
-                a[rt][ks].q = m < M ? *reinterpret_cast<const uint4 *>(dA + m * kMlpWidth + ks * 32 + 8 * g)
-                                    : make_uint4(0, 0, 0, 0);
-        }
-        f32x4 acc[2][4];
 #pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct) acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-        layer_mfma<2>(a, Wt, kMlpWidth, lane, acc);
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int64_t m = base + rt * 16 + 4 * g + r;
-                    const int j = ct * 16 + (lane & 15);
-                    if (m < M) {
-                        const u16 hp = Hprev[m * kMlpWidth + j];
-                        dAp[m * kMlpWidth + j] = f2bf((hp != 0 && !(hp & 0x8000)) ? acc[rt][ct][r] : 0.f);
-                    }
+                for (int e = 0; e < 8; ++e) {
+                    const u16 hj = h[pt][ks].h[e];
+                    if (i < M) dw4[ks][e] += dl * bf2f(hj);
+                    d[pt][ks].h[e] = hj != 0 && i < M ? f2bf(dl * bf2f(a4[ks].h[e])) : (u16)0;
                 }
+            store_transposed(d[pt], L.dAt, slot[pt], g);
+            store_points(d[pt], L.dA, slot[pt], g);
+        }
+        __syncthreads();
+        weight_grads(L.dAt, L.H2t, i0, 32 * half, lane, dw3, db3);
+#pragma unroll
+        for (int layer = 2; layer > 0; --layer) {
+            // gradients of the layer below from this wave's own points
+            Frag x[kTrPT][2];
+#pragma unroll
+            for (int pt = 0; pt < kTrPT; ++pt)
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks)
+                    x[pt][ks].q = *reinterpret_cast<const uint4 *>(L.dA + slot[pt] * kLdWidth + 32 * ks + 8 * g);
+            layer_t<2>(layer == 2 ? L.W3t : L.W2t, kLdWidth, nullptr, x, lane, acc);
+            mask_to_operand(acc, layer == 2 ? h2 : h1, d);
+            __syncthreads();   // every wave has read the gradients above
+#pragma unroll
+            for (int pt = 0; pt < kTrPT; ++pt) {
+                store_transposed(d[pt], L.dAt, slot[pt], g);
+                if (layer == 2) store_points(d[pt], L.dA, slot[pt], g);
+            }
+            __syncthreads();
+            if (layer == 2) weight_grads(L.dAt, L.H1t, i0, 32 * half, lane, dw2, db2);
+            else weight_grads(L.dAt, L.Ft, i0, 64 * half, lane, dw1, db1);
+        }
+        __syncthreads();   // features and activations are rewritten by the next step
+    }
+    // the block's partial gradient, in the order of the parameter vector, then its loss
+    float *out = part + (int64_t)blockIdx.x * kTrStride;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = i0 + 4 * g + r;
+#pragma unroll
+        for (int jt = 0; jt < 4; ++jt)
+            out[kOffW1 + i * kMlpIn + 64 * half + 16 * jt + col] = dw1[jt][r];
+#pragma unroll
+        for (int jt = 0; jt < 2; ++jt) {
+            out[kOffW2 + i * kMlpWidth + 32 * half + 16 * jt + col] = dw2[jt][r];
+            out[kOffW3 + i * kMlpWidth + 32 * half + 16 * jt + col] = dw3[jt][r];
+        }
+        if (col == 0 && half == 0) {
+            out[kOffB1 + i] = db1[r];
+            out[kOffB2 + i] = db2[r];
+            out[kOffB3 + i] = db3[r];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        float x = dw4[k >> 3][k & 7];
+        for (int s = 8; s > 0; s >>= 1) x += __shfl_xor(x, s, 64);
+        if (col == 0) L.red[wave][hidden_input(32 * (k >> 3) + 8 * g + (k & 7))] = x;
+    }
+    for (int s = 8; s > 0; s >>= 1) {
+        db4 += __shfl_xor(db4, s, 64);
+        loss += __shfl_xor(loss, s, 64);
+    }
+    if (lane == 0) {
+        L.red[wave][kMlpWidth] = db4;
+        L.red[wave][kMlpWidth + 1] = loss;
+    }
+    __syncthreads();
+    if (tid < kMlpWidth + 2) {
+        float x = 0.f;
+        for (int k = 0; k < kTrWaves; ++k) x += L.red[k][tid];
+        out[kOffW4 + tid] = x;      // dw4, db4, loss
     }
 }
 
-__global__ void k_mlp_reduce(const float *__restrict__ part, int nblocks, int count, int stride,
-                             float *__restrict__ out)
+// grad[c] = sum over blocks of part[block][c]; the column after the parameters is the loss.
+// 64 columns per block, a quarter of the rows per wave.
+__global__ __launch_bounds__(256) void k_mlp_train_reduce(const float *__restrict__ part, int nblocks,
+                                                          float *__restrict__ d_w, float *__restrict__ loss)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= count) return;
+    __shared__ float red[4][64];
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int c = blockIdx.x * 64 + lane;
     float s = 0.f;
-    for (int b = 0; b < nblocks; ++b) s += part[(int64_t)b * stride + c];
-    out[c] = s;
+    if (c <= kMlpParams) {
+#pragma unroll 8
+        for (int b = q; b < nblocks; b += 4) s += part[(int64_t)b * kTrStride + c];
+    }
+    red[q][lane] = s;
+    __syncthreads();
+    if (q != 0 || c > kMlpParams) return;
+    s = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    if (c < kMlpParams) d_w[c] = s;
+    else if (loss) *loss = s;
 }
 
 __global__ void k_mlp_adam(float *__restrict__ w, float *__restrict__ m, float *__restrict__ v,
@@ -556,8 +612,6 @@ __global__ void k_mlp_adam(float *__restrict__ w, float *__restrict__ m, float *
 }
 
 // ------------------------------------------------------------------ launchers
-int mlp_dw_blocks(int64_t M) { return (int)((M + kDwChunk - 1) / kDwChunk); }
-
 hipError_t launch_mlp_prep(const float *w, uint16_t *wb, float *wf, hipStream_t st)
 {
     hipLaunchKernelGGL(k_mlp_prep, dim3((kMlpBf16 + 255) / 256), dim3(256), 0, st, w, wb, wf);
@@ -566,57 +620,27 @@ hipError_t launch_mlp_prep(const float *w, uint16_t *wb, float *wf, hipStream_t 
 
 hipError_t launch_mlp_forward(const uint16_t *wb, const float *wf, const float *pts,
                               const float *sun, int64_t M, int64_t G, MlpNorm nz, bool prob,
-                              float *out, uint16_t *saveF, uint16_t *saveH, hipStream_t st)
+                              float *out, hipStream_t st)
 {
     if (M <= 0) return hipSuccess;
     int64_t tiles = (M + kFwdPts - 1) / kFwdPts;
     int64_t blocks = (tiles + kMlpWaves - 1) / kMlpWaves;
     if (blocks > 4096) blocks = 4096;
     hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned)blocks), dim3(kMlpThreads), 0, st, wb, wf,
-                       pts, sun, M, G, nz, prob ? 1 : 0, out, saveF, saveH);
+                       pts, sun, M, G, nz, prob ? 1 : 0, out);
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_out_bwd(const float *logits, const float *labels, const float *dlogit_in,
-                              float scale, const uint16_t *wb, const uint16_t *H3, int64_t M,
-                              uint16_t *dA3, float *part, hipStream_t st)
+hipError_t launch_mlp_train(const float *w, const float *pts, const float *sun, int64_t M,
+                            const float *labels, const float *d_logits, float scale, MlpNorm nz,
+                            float *part, float *d_w, float *loss, hipStream_t st)
 {
     if (M <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mlp_out_bwd, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, st, logits,
-                       labels, dlogit_in, scale, wb, H3, M, dA3, part);
-    return hipGetLastError();
-}
-
-hipError_t launch_mlp_dw(const uint16_t *dA, const uint16_t *H, int n, int64_t M, float *part_dw,
-                         float *part_db, hipStream_t st)
-{
-    const int nb = mlp_dw_blocks(M);
-    if (nb == 0) return hipSuccess;
-    if (n == 64)
-        hipLaunchKernelGGL(k_mlp_dw<64>, dim3(nb), dim3(256), 0, st, dA, H, M, part_dw, part_db);
-    else if (n == 128)
-        hipLaunchKernelGGL(k_mlp_dw<128>, dim3(nb), dim3(256), 0, st, dA, H, M, part_dw, part_db);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
-}
-
-hipError_t launch_mlp_dh(const uint16_t *dA, const uint16_t *Wb, const uint16_t *Hprev, int64_t M,
-                         uint16_t *dA_prev, hipStream_t st)
-{
-    if (M <= 0) return hipSuccess;
-    int64_t tiles = (M + kPtsPerWave - 1) / kPtsPerWave;
-    int64_t blocks = (tiles + kMlpWaves - 1) / kMlpWaves;
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_mlp_dh, dim3((unsigned)blocks), dim3(256), 0, st, dA, Wb, Hprev, M, dA_prev);
-    return hipGetLastError();
-}
-
-hipError_t launch_mlp_reduce(const float *part, int nblocks, int count, int stride, float *out,
-                             hipStream_t st)
-{
-    hipLaunchKernelGGL(k_mlp_reduce, dim3((count + 255) / 256), dim3(256), 0, st, part, nblocks, count,
-                       stride, out);
+    const int blocks = mlp_train_blocks(M);
+    hipLaunchKernelGGL(k_mlp_train, dim3(blocks), dim3(kTrThreads), 0, st, w, pts, sun, M, labels,
+                       d_logits, scale, nz, part);
+    hipLaunchKernelGGL(k_mlp_train_reduce, dim3((kMlpParams + 1 + 63) / 64), dim3(256), 0, st, part,
+                       blocks, d_w, loss);
     return hipGetLastError();
 }
 

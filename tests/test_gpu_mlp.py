@@ -85,6 +85,32 @@ def test_backward_matches_oracle(mode):
         assert rel <= 1e-2, (k, rel)
 
 
+@pytest.mark.parametrize("M", [17, 128, 129, 32769])
+def test_training_gradient_is_the_sum_over_pieces(M):
+    """One ragged tile, exactly one and just over one block step (128 points), and more
+    steps than blocks (256 x 128 points + 1, so one block takes a second step): the gradient
+    and loss of the batch are the sums over pieces of 48 points, which sit elsewhere in
+    their tiles.  A point's own terms do not depend on where it sits, so only the order of
+    the FP32 sums differs: at most M terms, 6e-8 sqrt(M) < 2e-5 relative."""
+    pts, sun = pts_suns(M, 100 + M)
+    w = cuda(om.init_params(17))
+    labels = (np.random.default_rng(M).uniform(size=M) > 0.4).astype(np.float32)
+    P, S, Y = cuda(pts), cuda(sun), cuda(labels)
+    net = sg.Mlp(context(), CENTRE, INV_HALF, max_points=M)
+    loss = torch.zeros(1, device="cuda")
+    g = to_np(net.backward(w, P, S, labels=Y, scale=1.0 / M, loss=loss)).astype(np.float64)
+    ref, ref_loss, part = np.zeros_like(g), 0.0, torch.zeros(1, device="cuda")
+    for a in range(0, M, 48):
+        ref += to_np(net.backward(w, P[a:a + 48].contiguous(), S[a:a + 48].contiguous(),
+                                  labels=Y[a:a + 48].contiguous(), scale=1.0 / M, loss=part))
+        ref_loss += float(part.item())
+    assert abs(float(loss.item()) - ref_loss) <= 2e-5 * ref_loss
+    G, R = om.unpack(g), om.unpack(ref)
+    for k in om.SIZES:
+        rel = np.linalg.norm(G[k] - R[k]) / max(np.linalg.norm(R[k]), 1e-30)
+        assert rel <= 2e-5, (k, rel)
+
+
 def test_adam_matches_oracle():
     rng = np.random.default_rng(0)
     n = 5000
