@@ -41,6 +41,22 @@ def test_dsm_init_small_city_matches_oracle(n):
     check(s, cells, ref)
 
 
+@pytest.mark.parametrize("nx,ny,n,height", [(2, 2, 300, 1.0),          # one cell
+                                            (34, 66, 5000, 3.0),       # a block of 2048 and a rest
+                                            (3, 1500, 100, 3.0),       # rows shorter than a group, few samples
+                                            (2, 2050, 4000, 3.0),      # one column
+                                            (70, 70, 4000, 5000.0)])   # block weights beyond 32 bits
+def test_dsm_init_search_edges_match_oracle(nx, ny, n, height):
+    z = np.random.default_rng(nx * 7 + ny).uniform(0.0, height, (ny, nx)).astype(np.float32)
+    s, cells = gi.dsm_init(torch.as_tensor(z, device="cuda"), -3.0, 2.0, 0.5, n, seed=77, with_cells=True)
+    ref = odi.dsm_init(z, -3.0, 2.0, 0.5, n, seed=77)
+    np.testing.assert_array_equal(to_np(cells), ref["cell"])
+    # FP64 geometry rounded once to FP32: half an ulp of the heights and coordinates
+    np.testing.assert_allclose(to_np(s.mean), ref["mean"], rtol=1.2e-7, atol=1e-6)
+    np.testing.assert_allclose(to_np(s.t_u), ref["t_u"], atol=2e-6)
+    np.testing.assert_allclose(to_np(s.t_v), ref["t_v"], atol=2e-6)
+
+
 def test_dsm_init_5m_surfels_on_the_2km_city():
     spec = synth.config(5)
     x0, g, z = dsm_of(spec)
