@@ -60,6 +60,7 @@ struct Layout {
     size_t torder_main, torder_sun, torder_parts;
     size_t inv_order, vis_rank;
     size_t geom_seeds, geom_cams, geom_parts;
+    size_t vr_parts;
     size_t total;
 };
 
@@ -181,6 +182,13 @@ static int64_t max_view_pixels(const ss_plan *p)
     return m;
 }
 
+static int64_t max_view_tiles(const std::vector<ViewDesc> &views)
+{
+    int64_t m = 1;
+    for (const ViewDesc &d : views) m = std::max<int64_t>(m, (int64_t)d.tiles_x * d.tiles_y);
+    return m;
+}
+
 static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs)
 {
     Layout L{};
@@ -235,6 +243,8 @@ static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs)
     L.geom_cams = take(nv * sizeof(GeomCam));
     L.geom_parts = take((size_t)std::max(normal_loss_blocks(p->vmain.data(), p->nv) * 10,
                                          l1_blocks(max_view_pixels(p))) * nv * 8);
+    // chain sums of the backward's per-view reduction
+    L.vr_parts = take(view_reduce_parts(p->nv) * 4);
     L.total = o;
     return L;
 }
@@ -362,9 +372,7 @@ static ss_status bin_views(ss_plan *p, const ss_views *v, bool sun, const uint32
     // bucketing; its last pass also writes each tile's list range.  Views of at most 2^16
     // tiles sort 16-bit keys local to the view (a quarter less traffic per pass).
     const int32_t ntiles = sun ? p->tiles_sun : p->tiles_main;
-    int64_t view_tiles = 1;
-    for (const ViewDesc &d : sun ? p->vsun : p->vmain)
-        view_tiles = std::max<int64_t>(view_tiles, (int64_t)d.tiles_x * d.tiles_y);
+    const int64_t view_tiles = max_view_tiles(sun ? p->vsun : p->vmain);
     const bool keys16 = view_tiles <= 65536;
     SS_HIP(launch_emit(order, p->n, p->nv, views, tiles, counts, offs, (uint64_t)cap, ka, keys16, va,
                        tmask, st));
@@ -775,18 +783,16 @@ static ss_status backward_pass(ss_plan *p, const ss_surfels *s, const ss_views *
                                  cmask_ptr(p), st, dist));
     }
     {
-        StageScope scope(p, SS_STAGE_REDUCE, st);
-        SS_HIP(launch_colour_reduce(p->at<float>(L.colour_parts), p->nv,
-                                    p->at<ViewDesc>(L.views_main), d_colC, d_colc, d_ambient, st));
-    }
-    {
         StageScope scope(p, SS_STAGE_PROJECT_BWD, st);
         SS_HIP(launch_project_bwd(p->at<float>(L.sorted_main), p->n, p->order_main, p->nv, v->Fxy,
                                   v->dF, consts(p->st).det_rel_eps_d, recgrad, d_mean, d_t_u, d_t_v,
                                   d_scale, d_opacity, d_albedo, p->at<float>(L.dF_parts), st));
     }
     StageScope scope(p, SS_STAGE_REDUCE, st);
-    SS_HIP(launch_dF_reduce(p->at<float>(L.dF_parts), project_bwd_blocks(p->n), p->nv, d_dF, st));
+    SS_HIP(launch_view_reduce(p->at<float>(L.colour_parts), max_view_tiles(p->vmain),
+                              p->at<float>(L.dF_parts), project_bwd_blocks(p->n), p->nv,
+                              p->at<ViewDesc>(L.views_main), d_colC, d_colc, d_ambient, d_dF,
+                              p->at<float>(L.vr_parts), st));
     return SS_OK;
 }
 

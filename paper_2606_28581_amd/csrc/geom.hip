@@ -259,19 +259,28 @@ __global__ __launch_bounds__(kGeomThreads) void k_normal_loss_depth(
 
 // Per view: loss[v] = weight / P * sum of the block terms; d_dF[v][:, :3] += the first two
 // rows of dL/dM = -Minv^T dL/dMinv Minv^T (the translation column drops out of the
-// central differences).
-__global__ void k_normal_loss_reduce(const ViewDesc *__restrict__ views,
+// central differences).  One block per view (one thread per view walked the partials of 8
+// views of 1100^2 in 113 us, now 5.9).
+__global__ __launch_bounds__(kGeomThreads) void k_normal_loss_reduce(const ViewDesc *__restrict__ views,
                                      const GeomCam *__restrict__ cams,
                                      const double *__restrict__ partials, int blocks_per_view,
-                                     int32_t nv, double weight, float *__restrict__ loss,
+                                     double weight, float *__restrict__ loss,
                                      float *__restrict__ d_dF)
 {
-    const int v = blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= nv) return;
+    __shared__ double red[kGeomThreads / 64][10];
+    const int v = blockIdx.x;
     double s[10];
     for (int k = 0; k < 10; ++k) s[k] = 0.0;
-    for (int b = 0; b < blocks_per_view; ++b)
+    for (int b = threadIdx.x; b < blocks_per_view; b += kGeomThreads)
         for (int k = 0; k < 10; ++k) s[k] += partials[((size_t)v * blocks_per_view + b) * 10 + k];
+    for (int k = 0; k < 10; ++k) {
+        for (int d = 32; d > 0; d >>= 1) s[k] += __shfl_xor(s[k], d, 64);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][k] = s[k];
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int k = 0; k < 10; ++k)
+        for (int w = 1; w < kGeomThreads / 64; ++w) s[k] += red[w][k];
     const double P = (double)views[v].W * (double)views[v].H;
     loss[v] = (float)(weight / P * s[9]);
     if (!d_dF) return;
@@ -319,8 +328,8 @@ hipError_t launch_normal_loss(const ViewDesc *views, const ViewDesc *host_views,
         hipLaunchKernelGGL(k_normal_loss_depth, dim3((unsigned)dbl, (unsigned)nv), dim3(kGeomThreads),
                            0, st, views, T, (double)tau, seeds, d_depth);
     }
-    hipLaunchKernelGGL(k_normal_loss_reduce, dim3((unsigned)((nv + 63) / 64)), dim3(64), 0, st, views,
-                       cams, partials, bpv, nv, (double)weight, loss, d_dF);
+    hipLaunchKernelGGL(k_normal_loss_reduce, dim3((unsigned)nv), dim3(kGeomThreads), 0, st, views, cams,
+                       partials, bpv, (double)weight, loss, d_dF);
     return hipGetLastError();
 }
 

@@ -5,6 +5,7 @@
 // surfel parameters are gathered once into rank order, so projection, the pair-count
 // scan and the (view, rank) records are contiguous, and tile lists hold ranks.
 #include "ss_internal.h"
+#include <algorithm>
 #include <cmath>
 
 namespace ss {
@@ -1631,41 +1632,6 @@ hipError_t launch_raster_bwd(int ts, bool has_vis, int32_t total_tiles, int32_t 
     return hipGetLastError();
 }
 
-// Per view: sum the per-tile colour partials -> dC (9), dc (3), dL_a (3).
-__global__ void k_colour_reduce(const float *__restrict__ partials,
-                                const ViewDesc *__restrict__ views, int32_t nv,
-                                float *d_colC, float *d_colc, float *d_amb)
-{
-    const int v = blockIdx.x;
-    __shared__ float red[256 / 64][16];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int t0 = views[v].tile_off;
-    const int t1 = t0 + views[v].tiles_x * views[v].tiles_y;
-    float acc[16];
-    for (int k = 0; k < 16; ++k) acc[k] = 0.f;
-    for (int t = t0 + threadIdx.x; t < t1; t += blockDim.x)
-        for (int k = 0; k < 16; ++k) acc[k] += partials[(int64_t)t * 16 + k];
-    const float s = wave_transpose_reduce16(acc, lane);
-    if ((lane & 3) == 0) red[w][lane >> 2] = s;
-    __syncthreads();
-    if (threadIdx.x < 15) {
-        float tot = red[0][threadIdx.x] + red[1][threadIdx.x] + red[2][threadIdx.x] +
-                    red[3][threadIdx.x];
-        const int k = threadIdx.x;
-        if (k < 9) d_colC[9 * v + k] = tot;
-        else if (k < 12) d_colc[3 * v + k - 9] = tot;
-        else d_amb[3 * v + k - 12] = tot;
-    }
-}
-
-hipError_t launch_colour_reduce(const float *partials, int32_t nv, const ViewDesc *views,
-                                float *d_colC, float *d_colc, float *d_amb, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_colour_reduce, dim3((unsigned)nv), dim3(256), 0, st, partials, views, nv,
-                       d_colC, d_colc, d_amb);
-    return hipGetLastError();
-}
-
 // ----------------------------------------------------------- projection backward
 // One thread per rank, looping over views: record gradients -> parameter gradients
 // (summed over views, written once, scattered back to surfel order), and per view the
@@ -1777,7 +1743,7 @@ __global__ __launch_bounds__(kPbThreads) void k_project_bwd(
         if (threadIdx.x < 8) {
             float tot = 0.f;
             for (int k = 0; k < kPbThreads / 64; ++k) tot += red[k][threadIdx.x];
-            dF_partials[((int64_t)blockIdx.x * nv + v) * 8 + threadIdx.x] = tot;
+            dF_partials[((int64_t)v * gridDim.x + blockIdx.x) * 8 + threadIdx.x] = tot;
         }
         __syncthreads();
     }
@@ -1812,29 +1778,104 @@ hipError_t launch_project_bwd(const float *sorted, int64_t n, const uint32_t *or
     return hipGetLastError();
 }
 
-__global__ void k_dF_reduce(const float *__restrict__ partials, int nblocks, int32_t nv,
-                            float *__restrict__ d_dF)
+// Per-view sums of the backward's partial rows: 16 floats per tile (dC 9, dc 3, dL_a 3)
+// and 8 per project_bwd block (dF).  Both are sums of chains with a fixed order (256 chains
+// per colour column, chain t over rows t, t + 256, ...; 32 per dF column), so that the colour
+// terms and camera deltas of a training run do not depend on how the chains are spread over
+// blocks.  Blocks (c, v) with c < chunks carry 256 / chunks colour chains of view v, one
+// thread per chain and column with its loads in flight together; with one chunk the block
+// also adds the chains up, with more k_view_finish does.  Block (chunks, v) sums the view's
+// dF rows.  One block per view, one load at a time, left a single 2048^2 view's 65,536 tile
+// rows to one CU (125 us) and took 29 us for the dF rows of 1M surfels; now 16 us for both
+// (40 views, 2M surfels: 257 -> 36 us).
+constexpr int kVrThreads = 256;
+constexpr int kVrChunks = 16;
+
+// Chain sums of view v (acc of thread t: the 16 columns of chain t) -> d_colC, d_colc, d_amb
+__device__ __forceinline__ void finish_colour(float (&acc)[16], float (*red)[16], int v,
+                                              float *d_colC, float *d_colc, float *d_amb)
 {
-    const int v = blockIdx.x;
-    const int k = threadIdx.x & 7, part = threadIdx.x >> 3;    // 32 parts x 8 values
-    float s = 0.f;
-    for (int b = part; b < nblocks; b += 32) s += partials[((int64_t)b * nv + v) * 8 + k];
-    __shared__ float red[32][8];
-    red[part][k] = s;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const float s = wave_transpose_reduce16(acc, lane);
+    if ((lane & 3) == 0) red[w][lane >> 2] = s;
     __syncthreads();
-    if (threadIdx.x < 8) {
-        float tot = 0.f;
-        for (int q = 0; q < 32; ++q) tot += red[q][threadIdx.x];
-        d_dF[8 * v + threadIdx.x] = tot;
+    if (threadIdx.x < 15) {
+        const int k = threadIdx.x;
+        const float tot = red[0][k] + red[1][k] + red[2][k] + red[3][k];
+        if (k < 9) d_colC[9 * v + k] = tot;
+        else if (k < 12) d_colc[3 * v + k - 9] = tot;
+        else d_amb[3 * v + k - 12] = tot;
     }
 }
 
-hipError_t launch_dF_reduce(const float *partials, int nblocks, int32_t nv, float *d_dF,
-                            hipStream_t st)
+__global__ __launch_bounds__(kVrThreads) void k_view_reduce(
+    const float *__restrict__ colour_rows, const ViewDesc *__restrict__ views,
+    const float *__restrict__ dF_rows, int nblocks, float *__restrict__ d_colC,
+    float *__restrict__ d_colc, float *__restrict__ d_amb, float *__restrict__ d_dF,
+    float *__restrict__ parts)
 {
-    if (nblocks == 0) return fill_f32(d_dF, 0.f, 8 * (int64_t)nv, st);
-    hipLaunchKernelGGL(k_dF_reduce, dim3((unsigned)nv), dim3(256), 0, st, partials, nblocks, nv,
-                       d_dF);
+    __shared__ float red[kVrThreads / 64][16];
+    __shared__ float col[kVrThreads];
+    const int v = blockIdx.y, chunks = gridDim.x - 1, c = blockIdx.x, t = threadIdx.x;
+    if (c == chunks) {
+        const float *p = dF_rows + 8 * (int64_t)v * nblocks + (t & 7);
+        float s = 0.f;
+#pragma unroll 16
+        for (int b = t >> 3; b < nblocks; b += 32) s += p[8 * b];
+        col[t] = s;                                        // 32 x 8 chain sums
+        __syncthreads();
+        if (t < 8) {
+            float x = 0.f;
+            for (int k = 0; k < 32; ++k) x += col[8 * k + t];
+            d_dF[8 * v + t] = x;
+        }
+        return;
+    }
+    const int rows = views[v].tiles_x * views[v].tiles_y;
+    const float *p = colour_rows + 16 * (int64_t)views[v].tile_off;
+    if (chunks == 1) {
+        float acc[16];
+        for (int k = 0; k < 16; ++k) acc[k] = 0.f;
+        for (int r = t; r < rows; r += kVrThreads)
+            for (int k = 0; k < 16; ++k) acc[k] += p[16 * (int64_t)r + k];
+        finish_colour(acc, red, v, d_colC, d_colc, d_amb);
+        return;
+    }
+    // kVrChunks == 16: thread t carries column t % 16 of chain 16 c + t / 16
+    const int chain = 16 * c + (t >> 4);
+    float s = 0.f;
+#pragma unroll 16
+    for (int r = chain; r < rows; r += kVrThreads) s += p[16 * (int64_t)r + (t & 15)];
+    parts[((int64_t)v * kVrThreads + chain) * 16 + (t & 15)] = s;
+}
+
+__global__ __launch_bounds__(kVrThreads) void k_view_finish(const float *__restrict__ parts,
+                                                            float *__restrict__ d_colC,
+                                                            float *__restrict__ d_colc,
+                                                            float *__restrict__ d_amb)
+{
+    __shared__ float red[kVrThreads / 64][16];
+    const float *p = parts + ((int64_t)blockIdx.x * kVrThreads + threadIdx.x) * 16;
+    float acc[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) acc[k] = p[k];
+    finish_colour(acc, red, blockIdx.x, d_colC, d_colc, d_amb);
+}
+
+size_t view_reduce_parts(int32_t nv) { return (size_t)nv * kVrThreads * 16; }
+
+hipError_t launch_view_reduce(const float *colour_rows, int64_t max_view_tiles, const float *dF_rows,
+                              int nblocks, int32_t nv, const ViewDesc *views, float *d_colC,
+                              float *d_colc, float *d_amb, float *d_dF, float *parts, hipStream_t st)
+{
+    if (nv <= 0) return hipSuccess;
+    // up to 8 rows per chain one block per view costs less than a second launch
+    const int chunks = max_view_tiles > 8 * kVrThreads ? kVrChunks : 1;
+    hipLaunchKernelGGL(k_view_reduce, dim3((unsigned)chunks + 1, (unsigned)nv), dim3(kVrThreads), 0, st,
+                       colour_rows, views, dF_rows, nblocks, d_colC, d_colc, d_amb, d_dF, parts);
+    if (chunks > 1)
+        hipLaunchKernelGGL(k_view_finish, dim3((unsigned)nv), dim3(kVrThreads), 0, st, parts, d_colC,
+                           d_colc, d_amb);
     return hipGetLastError();
 }
 

@@ -221,16 +221,19 @@ hipError_t launch_raster_bwd(int ts, bool has_vis, int32_t total_tiles, int32_t 
 // cmask[(s / 64 + t + w) * 64 + l], bit b set iff list position 64 w + b was composited;
 // the ranges of different tiles are disjoint, so (pairs / 64 + tiles + 1) * 64 words suffice.
 size_t cmask_words(int64_t pair_cap, int32_t tiles);
-hipError_t launch_colour_reduce(const float *partials, int32_t nv, const ViewDesc *views,
-                                float *d_colC, float *d_colc, float *d_amb, hipStream_t st);
 int project_bwd_blocks(int64_t n);
 hipError_t launch_project_bwd(const float *sorted, int64_t n, const uint32_t *order,
                               int32_t nv, const float *Fxy, const float *dF, double det_rel_eps,
                               const float *recgrad, float *d_mean, float *d_tu, float *d_tv,
                               float *d_scale, float *d_opac, float *d_alb, float *dF_partials,
                               hipStream_t st);
-hipError_t launch_dF_reduce(const float *partials, int nblocks, int32_t nv, float *d_dF,
-                            hipStream_t st);
+// Per view: the 16-float tile rows of the raster backward summed into d_colC, d_colc and
+// d_amb, the 8-float rows [view][nblocks] of project_bwd into d_dF.  parts:
+// view_reduce_parts(nv) floats.
+size_t view_reduce_parts(int32_t nv);
+hipError_t launch_view_reduce(const float *colour_rows, int64_t max_view_tiles, const float *dF_rows,
+                              int nblocks, int32_t nv, const ViewDesc *views, float *d_colC,
+                              float *d_colc, float *d_amb, float *d_dF, float *parts, hipStream_t st);
 // out row (v, order[r]) = the first row_words words of in row (v, r), in rows in_stride
 // words apart (words past in_stride read as zero)
 hipError_t launch_unpermute_rows(const uint32_t *order, int64_t n, int32_t nv,
