@@ -58,7 +58,7 @@ struct Layout {
     size_t rec_sun, tiles_sun, counts_sun, offs_sun, qk_a, qv_a, qk_b, qv_b, ranges_sun;
     size_t sun_depth, bounds, radix_temp, tmask_sun, cmask, cmask_bytes, stat_main, stat_sun;
     size_t torder_main, torder_sun, torder_parts;
-    size_t inv_order, vis_rank;
+    size_t inv_main, inv_sun, vis_rank;
     size_t geom_seeds, geom_cams, geom_parts;
     size_t vr_parts;
     size_t total;
@@ -210,8 +210,9 @@ static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs)
     L.rec_main = take(vn * kRecStride4 * 16);
     L.tiles_main = take(vn * sizeof(short4));
     L.counts_main = take(vn * 4);
-    L.offs_main = take((vn + 1) * 4);
-    L.scanparts = take(scan_temp_elems((int64_t)vn) * 4);
+    const size_t nrb = (size_t)rank_blocks(p->n) * nv;
+    L.offs_main = take((nrb + 1) * 4);
+    L.scanparts = take(scan_temp_elems((int64_t)nrb) * 4);
     L.pk_a = take((size_t)cm * 4); L.pv_a = take((size_t)cm * 4);
     L.pk_b = take((size_t)cm * 4); L.pv_b = take((size_t)cm * 4);
     L.ranges_main = take((size_t)p->tiles_main_max * 8);
@@ -221,7 +222,7 @@ static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs)
     L.rec_sun = take(vn * kSunRecStride4 * 16);
     L.tiles_sun = take(vn * sizeof(short4));
     L.counts_sun = take(vn * 4);
-    L.offs_sun = take((vn + 1) * 4);
+    L.offs_sun = take((nrb + 1) * 4);
     L.qk_a = take((size_t)cs * 4); L.qv_a = take((size_t)cs * 4);
     L.qk_b = take((size_t)cs * 4); L.qv_b = take((size_t)cs * 4);
     L.ranges_sun = take((size_t)p->tiles_sun_max * 8);
@@ -229,7 +230,8 @@ static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs)
     L.bounds = take((size_t)bounds_blocks(p->n) * 6 * 8);
     L.radix_temp = take(radix_temp_bytes(std::max<int64_t>(p->n, std::max(cm, cs)), p->nv));
     L.tmask_sun = take((size_t)p->tiles_sun_max * 4);
-    L.inv_order = take(n * 4);
+    L.inv_main = take(n * 4);
+    L.inv_sun = take(n * 4);
     L.vis_rank = take(vn * 4);
     // forward -> backward contributor masks of 8x8 tiles (other sizes use the box test)
     L.cmask_bytes = p->st.tile_size == 8 ? cmask_words(cm, p->tiles_main_max) * 8 : 0;
@@ -322,10 +324,9 @@ static ss_status prepare(ss_plan *p, const ss_surfels *s, const ss_views *v, boo
         p->sun_order_shared = false;
     }
     StageScope scope(p, SS_STAGE_DEPTH_SORT, st);
-    SS_HIP(launch_depth_keys(s->mean, p->n, v->b_z, ka, va, st));
     bool in_b = false;
-    SS_HIP(radix_sort_pairs(ka, va, kb, vb, p->n, nullptr, p->n, 32, p->at<void>(L.radix_temp),
-                            &in_b, st));
+    SS_HIP(depth_sort(s->mean, p->n, v->b_z, ka, va, kb, vb, p->at<void>(L.radix_temp),
+                      p->at<uint32_t>(sun ? L.inv_sun : L.inv_main), &in_b, st));
     uint32_t *order = in_b ? vb : va;
     SurfelPtrs sp{s->mean, s->t_u, s->t_v, s->scale, s->opacity, s->albedo, p->n};
     SS_HIP(launch_gather_params(order, sp, sorted, st));
@@ -335,8 +336,8 @@ static ss_status prepare(ss_plan *p, const ss_surfels *s, const ss_views *v, boo
 }
 
 // Projection + pair-count scan (+ emission, tile sort and ranges when `bin`).
-static ss_status bin_views(ss_plan *p, const ss_views *v, bool sun, const uint32_t *order,
-                           const float *sorted, const float *vis, bool bin, hipStream_t st,
+static ss_status bin_views(ss_plan *p, const ss_views *v, bool sun, const float *sorted,
+                           const float *vis, bool bin, hipStream_t st,
                            const uint32_t *tmask = nullptr)
 {
     const Layout &L = p->L;
@@ -349,50 +350,60 @@ static ss_status bin_views(ss_plan *p, const ss_views *v, bool sun, const uint32
     unsigned long long *counters = p->at<unsigned long long>(L.counters);
     uint32_t *flags = p->at<uint32_t>(L.flags);
     const int64_t cap = sun ? p->cap_sun : p->cap_main;
+    const int32_t ntiles = sun ? p->tiles_sun : p->tiles_main;
+    uint32_t *ranges = p->at<uint32_t>(sun ? L.ranges_sun : L.ranges_main);
+    // Views of at most 2^16 tiles sort 16-bit keys local to the view (a quarter less traffic
+    // per pass)
+    const int64_t view_tiles = max_view_tiles(sun ? p->vsun : p->vmain);
+    const bool keys16 = view_tiles <= 65536;
+    const int bits = bits_for(view_tiles);
+    const SmallSort plan = plan_small_sort(cap, p->nv, bits);
+    uint32_t *hist = plan.rows > 0 ? p->at<uint32_t>(L.radix_temp) : nullptr;
     {
         StageScope scope(p, sun ? SS_STAGE_SUN_PROJECT : SS_STAGE_PROJECT, st);
         const float *vis_rank = nullptr;
         if (!sun && vis) {
-            SS_HIP(launch_vis_to_rank(vis, p->n, p->nv, order, p->at<uint32_t>(L.inv_order),
+            SS_HIP(launch_vis_to_rank(vis, p->n, p->nv, p->at<uint32_t>(L.inv_main),
                                       p->at<float>(L.vis_rank), st));
             vis_rank = p->at<float>(L.vis_rank);
         }
         SS_HIP(launch_project(sorted, p->n, p->nv, views, v->Fxy, sun ? nullptr : v->dF,
                               sun ? p->at<SunCam>(L.suncam) : nullptr, vis_rank,
-                              v->b_z, p->st.tile_size, rc, rec, tiles, counts, tmask, st));
+                              v->b_z, p->st.tile_size, rc, rec, tiles, counts, offs, tmask,
+                              bin ? ranges : nullptr, ntiles, st));
     }
     StageScope scope(p, sun ? SS_STAGE_SUN_BIN : SS_STAGE_BIN, st);
-    SS_HIP(scan_pair_counts(counts, p->n, p->nv, offs, p->at<uint32_t>(L.scanparts), counters,
-                            sun ? 1 : 0, flags + (sun ? 1 : 0), bin ? (uint64_t)cap : ~0ull, st));
+    SS_HIP(scan_pair_sums(offs, p->n, p->nv, p->at<uint32_t>(L.scanparts), counters, sun ? 1 : 0,
+                          flags + (sun ? 1 : 0), bin ? (uint64_t)cap : ~0ull, st));
     if (!bin) return SS_OK;
     uint32_t *ka = p->at<uint32_t>(sun ? L.qk_a : L.pk_a), *va = p->at<uint32_t>(sun ? L.qv_a : L.pv_a);
     uint32_t *kb = p->at<uint32_t>(sun ? L.qk_b : L.pk_b), *vb = p->at<uint32_t>(sun ? L.qv_b : L.pv_b);
+    const unsigned long long *npairs = counters + (sun ? 1 : 0);
     // pairs arrive grouped by view (the count scan is view-major) and in depth-rank order
     // inside a view, so a stable sort on the tile id inside each view's run is the whole
-    // bucketing; its last pass also writes each tile's list range.  Views of at most 2^16
-    // tiles sort 16-bit keys local to the view (a quarter less traffic per pass).
-    const int32_t ntiles = sun ? p->tiles_sun : p->tiles_main;
-    const int64_t view_tiles = max_view_tiles(sun ? p->vsun : p->vmain);
-    const bool keys16 = view_tiles <= 65536;
-    SS_HIP(launch_emit(order, p->n, p->nv, views, tiles, counts, offs, (uint64_t)cap, ka, keys16, va,
-                       tmask, st));
-    SortSegments seg{offs, p->n, p->nv, views,
-                     p->at<uint32_t>(sun ? L.ranges_sun : L.ranges_main), ntiles};
+    // bucketing; its last pass also writes each tile's list range.
+    SS_HIP(launch_emit(p->n, p->nv, views, tiles, counts, offs, (uint64_t)cap, ka, keys16, va, tmask,
+                       st));
+    const SortSegments seg{offs, rank_blocks(p->n), p->nv, views, ranges, ntiles};
+    uint16_t *ka16 = reinterpret_cast<uint16_t *>(ka), *kb16 = reinterpret_cast<uint16_t *>(kb);
+    void *temp = p->at<void>(L.radix_temp);
     bool in_b = false;
-    if (keys16)
-        SS_HIP(radix_sort_pairs(reinterpret_cast<uint16_t *>(ka), va, reinterpret_cast<uint16_t *>(kb), vb,
-                                cap, counters + (sun ? 1 : 0), 0, bits_for(view_tiles),
-                                p->at<void>(L.radix_temp), &in_b, st, &seg));
-    else
-        SS_HIP(radix_sort_pairs(ka, va, kb, vb, cap, counters + (sun ? 1 : 0), 0, bits_for(view_tiles),
-                                p->at<void>(L.radix_temp), &in_b, st, &seg));
+    if (p->n > 0 && cap > 0) {
+        if (hist && keys16)
+            SS_HIP(small_sort_tiles(plan, ka16, va, kb16, vb, cap, npairs, bits, hist, &in_b, st, seg));
+        else if (hist)
+            SS_HIP(small_sort_tiles(plan, ka, va, kb, vb, cap, npairs, bits, hist, &in_b, st, seg));
+        else if (keys16)
+            SS_HIP(radix_sort_pairs(ka16, va, kb16, vb, cap, npairs, 0, bits, temp, &in_b, st, &seg));
+        else
+            SS_HIP(radix_sort_pairs(ka, va, kb, vb, cap, npairs, 0, bits, temp, &in_b, st, &seg));
+    }
     uint32_t *lists = in_b ? vb : va;
     if (sun) p->lists_sun = lists; else p->lists_main = lists;
     const uint32_t *torder = nullptr;
     if (p->st.tile_order == 1) {
         uint32_t *o = p->at<uint32_t>(sun ? L.torder_sun : L.torder_main);
-        SS_HIP(launch_tile_order(p->at<uint32_t>(sun ? L.ranges_sun : L.ranges_main), ntiles,
-                                 counters + (sun ? 1 : 0), !sun, o, p->at<uint32_t>(L.torder_parts), st));
+        SS_HIP(launch_tile_order(ranges, ntiles, npairs, !sun, o, p->at<uint32_t>(L.torder_parts), st));
         torder = o;
     }
     if (sun) p->torder_sun = torder; else p->torder_main = torder;
@@ -638,7 +649,7 @@ ss_status ss_count_pairs(ss_plan *p, const ss_surfels *s, const ss_views *v, int
     float *sorted;
     e = prepare(p, s, v, false, &order, &sorted, st);
     if (e != SS_OK) return e;
-    e = bin_views(p, v, false, order, sorted, nullptr, false, st);
+    e = bin_views(p, v, false, sorted, nullptr, false, st);
     if (e != SS_OK) return e;
     if (v->sun) {
         e = prepare(p, s, v, true, &order, &sorted, st);
@@ -646,7 +657,7 @@ ss_status ss_count_pairs(ss_plan *p, const ss_surfels *s, const ss_views *v, int
         SS_HIP(launch_sun_cameras(s->mean, p->n, p->nv, v->Fxy, v->dF, v->sun, v->b_z,
                                   p->st.sun_map_size, p->at<double>(p->L.bounds),
                                   p->at<SunCam>(p->L.suncam), st));
-        e = bin_views(p, v, true, order, sorted, nullptr, false, st);
+        e = bin_views(p, v, true, sorted, nullptr, false, st);
         if (e != SS_OK) return e;
     }
     unsigned long long c[2] = {0, 0};
@@ -686,11 +697,10 @@ static ss_status forward_pass(ss_plan *p, const ss_surfels *s, const ss_views *v
 {
     ss_status e;
     p->fwd_valid = false;
-    SS_HIP(fill_u32(p->at<uint32_t>(p->L.flags), 0u, 1, st));
     unsigned long long *stat = p->at<unsigned long long>(p->L.stat_main);
-    SS_HIP(fill_u32(reinterpret_cast<uint32_t *>(stat), 0u, 2 * kStatSlots * kStatStride, st));
+    SS_HIP(reset_pass(p->at<uint32_t>(p->L.flags), stat, nullptr, st));
     if (!order && (e = prepare(p, s, v, false, &order, &sorted, st)) != SS_OK) return e;
-    if ((e = bin_views(p, v, false, order, sorted, vis, true, st)) != SS_OK) return e;
+    if ((e = bin_views(p, v, false, sorted, vis, true, st)) != SS_OK) return e;
     RasterConsts rc = consts(p->st);
     rc.torder = p->torder_main;
     {
@@ -859,9 +869,8 @@ static ss_status shadow_pass(ss_plan *p, const ss_surfels *s, const ss_views *v,
     ss_status e;
     const Layout &L = p->L;
     p->sun_valid = false;
-    SS_HIP(fill_u32(p->at<uint32_t>(L.flags) + 1, 0u, 1, st));
     unsigned long long *stat = p->at<unsigned long long>(L.stat_sun);
-    SS_HIP(fill_u32(reinterpret_cast<uint32_t *>(stat), 0u, 2 * kStatSlots * kStatStride, st));
+    SS_HIP(reset_pass(p->at<uint32_t>(L.flags) + 1, stat, nullptr, st));
     const bool shared = order != nullptr;
     if (!shared && (e = prepare(p, s, v, true, &order, &sorted, st)) != SS_OK) return e;
     {
@@ -870,7 +879,7 @@ static ss_status shadow_pass(ss_plan *p, const ss_surfels *s, const ss_views *v,
                                   p->st.sun_map_size, p->at<double>(L.bounds),
                                   p->at<SunCam>(L.suncam), st));
     }
-    if ((e = bin_views(p, v, true, order, sorted, nullptr, true, st)) != SS_OK) return e;
+    if ((e = bin_views(p, v, true, sorted, nullptr, true, st)) != SS_OK) return e;
     float *D = sun_depth ? sun_depth : p->at<float>(L.sun_depth);
     RasterConsts rc = consts(p->st);
     rc.torder = p->torder_sun;
@@ -933,6 +942,7 @@ ss_status ss_debug_binning(ss_plan *p, int32_t which, uint32_t *order, int32_t *
     if (surf_tiles && p->n > 0)
         SS_HIP(launch_unpermute_tiles(ord, p->n, p->nv, p->at<short4>(sun ? L.tiles_sun : L.tiles_main),
                                       surf_tiles, st));
+    if (tile_ranges) SS_HIP(finish_ranges(p->at<uint32_t>(sun ? L.ranges_sun : L.ranges_main), nt, st));
     if (tile_ranges)
         SS_HIP(hipMemcpyAsync(tile_ranges, p->at<void>(sun ? L.ranges_sun : L.ranges_main), nt * 8,
                               hipMemcpyDeviceToDevice, st));
@@ -1260,10 +1270,8 @@ ss_status ss_shadow_surrogate(ss_plan *p, ss_mlp *mlp, const float *w, const ss_
     const Layout &L = p->L;
     p->sun_valid = false;
     unsigned long long *counters = p->at<unsigned long long>(L.counters);
-    SS_HIP(fill_u32(p->at<uint32_t>(L.flags) + 1, 0u, 1, st));
-    SS_HIP(fill_u32(reinterpret_cast<uint32_t *>(counters + 6), 0u, 2, st));
     unsigned long long *stat = p->at<unsigned long long>(L.stat_sun);
-    SS_HIP(fill_u32(reinterpret_cast<uint32_t *>(stat), 0u, 2 * kStatSlots * kStatStride, st));
+    SS_HIP(reset_pass(p->at<uint32_t>(L.flags) + 1, stat, counters + 6, st));
     {
         StageScope scope(p, SS_STAGE_MLP, st);
         SS_HIP(launch_mlp_prep(w, mlp->at<uint16_t>(mlp->L.o_wb), mlp->at<float>(mlp->L.o_wf), st));
@@ -1289,7 +1297,7 @@ ss_status ss_shadow_surrogate(ss_plan *p, ss_mlp *mlp, const float *w, const ss_
                                  p->at<ViewDesc>(L.views_sun), p->st.sun_map_size, p->st.tile_size,
                                  vis, band, tmask, counters + 6, st));
     }
-    if ((e = bin_views(p, v, true, order, sorted, nullptr, true, st, tmask)) != SS_OK) return e;
+    if ((e = bin_views(p, v, true, sorted, nullptr, true, st, tmask)) != SS_OK) return e;
     float *D = sun_depth ? sun_depth : p->at<float>(L.sun_depth);
     RasterConsts rc = consts(p->st);
     rc.torder = p->torder_sun;

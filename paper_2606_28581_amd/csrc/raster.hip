@@ -25,29 +25,6 @@ __device__ __forceinline__ int find_view(const ViewDesc *views, int nv, int tile
     return lo;
 }
 
-// ------------------------------------------------------------------ depth keys
-// kappa = fl32(b_z - p_z) (Eq. depth_affine_camera on the centre), mapped to an
-// order-preserving uint32: total order over all finite floats, no altitude limit.
-__global__ void k_depth_keys(const float *__restrict__ mean, int64_t n, float bz,
-                             uint32_t *__restrict__ keys, uint32_t *__restrict__ vals)
-{
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float kap = __fsub_rn(bz, mean[3 * i + 2]);
-    uint32_t b = __float_as_uint(kap);
-    keys[i] = b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);
-    vals[i] = (uint32_t)i;
-}
-
-hipError_t launch_depth_keys(const float *mean, int64_t n, float bz, uint32_t *keys,
-                             uint32_t *vals, hipStream_t st)
-{
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_depth_keys, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, mean,
-                       n, bz, keys, vals);
-    return hipGetLastError();
-}
-
 // ------------------------------------------------------- gather into rank order
 // sorted[r] = (p, t_u, t_v, s_u, s_v, o, albedo) of surfel order[r], 16 floats.
 __global__ void k_gather_params(const uint32_t *__restrict__ order, SurfelPtrs s,
@@ -131,8 +108,13 @@ __global__ __launch_bounds__(256) void k_project(
     const float *__restrict__ dF, const SunCam *__restrict__ sun,
     const float *__restrict__ vis_rank, float bz, int ts, RasterConsts rc,
     float4 *__restrict__ rec, short4 *__restrict__ tiles, uint32_t *__restrict__ counts,
-    const uint32_t *__restrict__ tmask)
+    uint32_t *__restrict__ sums, const uint32_t *__restrict__ tmask, uint2 *__restrict__ ranges,
+    int64_t nranges)
 {
+    // empty ranges for the tile sort
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nranges;
+         i += (int64_t)gridDim.x * blockDim.x)
+        ranges[i] = make_uint2(0xFFFFFFFFu, 0u);
     // the block's 256 records are staged in LDS and written back as one contiguous run.
     // Blocks run view-innermost (block = rank block x views + view), in xcd_tile's chunked
     // order, so the views of one rank block share the surfel parameters in one L2.
@@ -219,7 +201,16 @@ __global__ __launch_bounds__(256) void k_project(
     }
     if (valid) {
         tiles[slot] = tl;
-        counts[slot] = cnt;
+        if (tmask) counts[slot] = cnt;
+    } else {
+        cnt = 0;
+    }
+    // the block's pair count, clamped
+    __shared__ unsigned long long wsum[kRankBlock / 64];
+    {
+        unsigned long long x = cnt;
+        for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
+        if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = x;
     }
     // record
     const float chx = (float)c[0], chy = (float)c[1];
@@ -237,6 +228,10 @@ __global__ __launch_bounds__(256) void k_project(
     const double s = nsign / mn;
     R[5] = make_float4((float)(s * m[0]), (float)(s * m[1]), (float)(s * m[2]), (float)nsign);
     __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned long long x = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+        sums[(int64_t)v * rank_blocks(n) + L / nv] = (uint32_t)min(x, 0xFFFFFFFFull);
+    }
     const int64_t nrec = min((int64_t)blockDim.x, n - r0);
     // whole slots, so every written line is written in full
     if (sun) {
@@ -255,16 +250,17 @@ __global__ __launch_bounds__(256) void k_project(
 hipError_t launch_project(const float *sorted, int64_t n, int32_t nv, const ViewDesc *views,
                           const float *Fxy, const float *dF, const SunCam *sun,
                           const float *vis_rank, float bz, int ts, const RasterConsts &rc,
-                          float *rec, short4 *tiles, uint32_t *counts, const uint32_t *tmask,
-                          hipStream_t st)
+                          float *rec, short4 *tiles, uint32_t *counts, uint32_t *sums,
+                          const uint32_t *tmask, uint32_t *ranges, int64_t nranges, hipStream_t st)
 {
-    if (n <= 0) return hipSuccess;
-    const int64_t blocks = (n + 255) / 256 * nv;
+    if (n <= 0)      // nothing to project: empty tiles only
+        return ranges ? fill_u32(ranges, 0u, 2 * nranges, st) : hipSuccess;
+    const int64_t blocks = rank_blocks(n) * nv;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_project, dim3((unsigned)blocks), dim3(256), 0, st,
+    hipLaunchKernelGGL(k_project, dim3((unsigned)blocks), dim3(kRankBlock), 0, st,
                        reinterpret_cast<const float4 *>(sorted), n, nv, views, Fxy, dF, sun,
-                       vis_rank, bz, ts, rc, reinterpret_cast<float4 *>(rec), tiles, counts,
-                       tmask);
+                       vis_rank, bz, ts, rc, reinterpret_cast<float4 *>(rec), tiles, counts, sums,
+                       tmask, reinterpret_cast<uint2 *>(ranges), ranges ? nranges : 0);
     return hipGetLastError();
 }
 
@@ -272,15 +268,6 @@ hipError_t launch_project(const float *sorted, int64_t n, int32_t nv, const View
 // depth order is one permutation for all views, so one pass over surfels k (coalesced
 // reads of every view's vis[v][k]) writes the nv values of surfel k contiguously at its
 // rank: out[rank(k) * nv + v].
-__global__ void k_inverse_order(const uint32_t *__restrict__ order, int64_t n,
-                                uint32_t *__restrict__ rank)
-{
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    const uint32_t k = order[r];
-    if (k < n) rank[k] = (uint32_t)r;
-}
-
 // A block transposes a chunk of surfels through LDS (rows padded to nv + 1 floats):
 // reads run along k per view, writes along v per surfel (one contiguous run each).
 __global__ __launch_bounds__(256) void k_vis_to_rank(const float *__restrict__ vis, int64_t n,
@@ -304,13 +291,11 @@ __global__ __launch_bounds__(256) void k_vis_to_rank(const float *__restrict__ v
     }
 }
 
-hipError_t launch_vis_to_rank(const float *vis, int64_t n, int32_t nv, const uint32_t *order,
-                              uint32_t *rank, float *out, hipStream_t st)
+hipError_t launch_vis_to_rank(const float *vis, int64_t n, int32_t nv, const uint32_t *rank, float *out,
+                              hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
     if (nv <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_inverse_order, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, order,
-                       n, rank);
     // chunk x (nv + 1) floats of LDS, at most 64 KB
     const int chunk = (int)std::max<int64_t>(1, std::min<int64_t>(64, 16384 / (nv + 1)));
     const size_t lds = (size_t)chunk * (nv + 1) * sizeof(float);
@@ -320,83 +305,82 @@ hipError_t launch_vis_to_rank(const float *vis, int64_t n, int32_t nv, const uin
 }
 
 // ------------------------------------------------------------------------ emit
-// One thread per (rank, view): one (global tile id, rank) pair per overlapped tile at
-// the scanned offset.  A block's 256 ranks own one contiguous run of the output; runs
-// of up to kEmitStage pairs are assembled in LDS and written out coalesced, longer ones
-// go straight to memory.  Pairs beyond the bound capacity are dropped (the scan already
-// raised the overflow flag).
-constexpr int kEmitThreads = 256;
+// One thread per (rank, view): one (tile id, rank) pair per overlapped tile.  A block's 256
+// ranks own one contiguous run of the output, which starts at the block's scanned pair sum;
+// inside it the threads' places come from a scan of their counts here (the tile rectangles
+// give them, or `counts` where a tile mask cut them).  Runs of up to kEmitStage pairs are
+// assembled in LDS and written out coalesced, longer ones go straight to memory.  Pairs
+// beyond the bound capacity are dropped (the scan already raised the overflow flag).
+constexpr int kEmitThreads = kRankBlock;
 constexpr int kEmitStage = 1024;
 
 template <typename KT>
 __global__ __launch_bounds__(kEmitThreads) void k_emit(
     int64_t n, const ViewDesc *__restrict__ views, const short4 *__restrict__ tiles,
-    const uint32_t *__restrict__ counts, const uint32_t *__restrict__ offsets, uint64_t cap,
+    const uint32_t *__restrict__ counts, const uint32_t *__restrict__ base, uint64_t cap,
     KT *__restrict__ keys, uint32_t *__restrict__ vals, const uint32_t *__restrict__ tmask)
 {
     constexpr bool kLocal = sizeof(KT) == 2;   // tile id within the view, else global
     __shared__ KT sk[kEmitStage];
     __shared__ uint32_t sv[kEmitStage];
+    __shared__ uint32_t lds_w[kEmitThreads / 64];
     const int v = blockIdx.y;
-    const int64_t r0 = (int64_t)blockIdx.x * kEmitThreads;
-    const int64_t r = r0 + threadIdx.x;
-    const int64_t rend = min(n, r0 + kEmitThreads);
-    const uint64_t b_lo = offsets[(int64_t)v * n + r0];
-    const uint64_t b_hi = max(b_lo, (uint64_t)offsets[(int64_t)v * n + rend]);
-    const bool staged = b_hi - b_lo <= (uint64_t)kEmitStage;   // uniform over the block
+    const int64_t r = (int64_t)blockIdx.x * kEmitThreads + threadIdx.x;
+    const uint64_t b_lo = base[(int64_t)v * gridDim.x + blockIdx.x];
+    short4 t = make_short4(0, -1, 0, -1);
+    uint32_t cnt = 0;
     if (r < n) {
-        // the three loads are independent: issue them together
-        const int64_t slot = (int64_t)v * n + r;
-        const uint32_t cnt = counts[slot];
-        const short4 t = tiles[slot];
-        uint64_t pos = offsets[slot];
-        if (cnt != 0) {
-            const ViewDesc vd = views[v];
-            for (int ty = t.z; ty <= t.w; ++ty)
-                for (int tx = t.x; tx <= t.y; ++tx) {
-                    const uint32_t lkey = (uint32_t)(ty * vd.tiles_x + tx);
-                    const uint32_t gkey = (uint32_t)vd.tile_off + lkey;
-                    if (tmask && tmask[gkey] == 0u) continue;
-                    const KT key = (KT)(kLocal ? lkey : gkey);
-                    if (staged) {
-                        const uint64_t l = pos - b_lo;
-                        if (l < (uint64_t)kEmitStage) {
-                            sk[l] = key;
-                            sv[l] = (uint32_t)r;
-                        }
-                    } else if (pos < cap) {
-                        keys[pos] = key;
-                        vals[pos] = (uint32_t)r;
+        t = tiles[(int64_t)v * n + r];
+        cnt = counts ? counts[(int64_t)v * n + r]
+                     : (uint32_t)(t.y - t.x + 1) * (uint32_t)(t.w - t.z + 1);
+    }
+    uint32_t total;
+    const uint32_t before = block_exclusive_scan(cnt, lds_w, &total);
+    const ViewDesc vd = views[v];
+    const bool staged = total <= (uint32_t)kEmitStage;   // uniform over the block
+    if (cnt != 0) {
+        uint64_t l = before;
+        for (int ty = t.z; ty <= t.w; ++ty)
+            for (int tx = t.x; tx <= t.y; ++tx) {
+                const uint32_t lkey = (uint32_t)(ty * vd.tiles_x + tx);
+                const uint32_t gkey = (uint32_t)vd.tile_off + lkey;
+                if (tmask && tmask[gkey] == 0u) continue;
+                const KT key = (KT)(kLocal ? lkey : gkey);
+                if (!staged) {
+                    if (b_lo + l < cap) {
+                        keys[b_lo + l] = key;
+                        vals[b_lo + l] = (uint32_t)r;
                     }
-                    ++pos;
+                } else if (l < (uint64_t)kEmitStage) {
+                    sk[l] = key;
+                    sv[l] = (uint32_t)r;
                 }
-        }
+                ++l;
+            }
     }
     if (!staged) return;
     __syncthreads();
-    const int cnt = (int)(b_hi - b_lo);
-    for (int i = threadIdx.x; i < cnt; i += kEmitThreads) {
-        const uint64_t pos = b_lo + (uint64_t)i;
-        if (pos < cap) {
-            keys[pos] = sk[i];
-            vals[pos] = sv[i];
+    for (uint32_t i = threadIdx.x; i < total; i += kEmitThreads) {
+        if (b_lo + i < cap) {
+            keys[b_lo + i] = sk[i];
+            vals[b_lo + i] = sv[i];
         }
     }
 }
 
-hipError_t launch_emit(const uint32_t *, int64_t n, int32_t nv, const ViewDesc *views,
-                       const short4 *tiles, const uint32_t *counts, const uint32_t *offsets,
-                       uint64_t cap, void *keys, bool keys16, uint32_t *vals,
-                       const uint32_t *tmask, hipStream_t st)
+hipError_t launch_emit(int64_t n, int32_t nv, const ViewDesc *views, const short4 *tiles,
+                       const uint32_t *counts, const uint32_t *base, uint64_t cap, void *keys,
+                       bool keys16, uint32_t *vals, const uint32_t *tmask, hipStream_t st)
 {
     if (n <= 0 || cap == 0) return hipSuccess;
-    const dim3 grid((unsigned)((n + kEmitThreads - 1) / kEmitThreads), (unsigned)nv);
+    const dim3 grid((unsigned)rank_blocks(n), (unsigned)nv);
+    const uint32_t *cn = tmask ? counts : nullptr;
     if (keys16)
-        hipLaunchKernelGGL(k_emit<uint16_t>, grid, dim3(kEmitThreads), 0, st, n, views, tiles, counts,
-                           offsets, cap, static_cast<uint16_t *>(keys), vals, tmask);
+        hipLaunchKernelGGL(k_emit<uint16_t>, grid, dim3(kEmitThreads), 0, st, n, views, tiles, cn, base,
+                           cap, static_cast<uint16_t *>(keys), vals, tmask);
     else
-        hipLaunchKernelGGL(k_emit<uint32_t>, grid, dim3(kEmitThreads), 0, st, n, views, tiles, counts,
-                           offsets, cap, static_cast<uint32_t *>(keys), vals, tmask);
+        hipLaunchKernelGGL(k_emit<uint32_t>, grid, dim3(kEmitThreads), 0, st, n, views, tiles, cn, base,
+                           cap, static_cast<uint32_t *>(keys), vals, tmask);
     return hipGetLastError();
 }
 
@@ -421,7 +405,8 @@ __device__ __forceinline__ bool heavy_tile(const uint32_t *ranges, int32_t ntile
     const int b = 8 * i + x;
     if (b >= ntiles) { tile = -1; return false; }
     tile = xcd_tile<CHUNKED>(b, ntiles);
-    const uint64_t len = ranges[2 * tile + 1] - ranges[2 * tile];
+    const uint2 r = tile_range(ranges, tile);
+    const uint64_t len = r.y - r.x;
     // len >= 2 total / ntiles without division
     return len * (uint64_t)ntiles >= 2ull * total && len > 0;
 }
@@ -634,7 +619,8 @@ __global__ __launch_bounds__(TS *TS) void k_raster_fwd(
     const int px = wx0 + (lane & 7), py = wy0 + (lane >> 3);
     const bool inside = px < vd.W && py < vd.H;
     const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
-    const uint32_t start = ranges[2 * tile], end = ranges[2 * tile + 1];
+    const uint2 range = tile_range(ranges, tile);
+    const uint32_t start = range.x, end = range.y;
     constexpr int RS = DEPTH_ONLY ? kSunRecStride4 : kRecStride4;   // record slot
     const float4 *recv = rec + (size_t)v * (size_t)n * RS;
     float Tr = 1.f, aD = 0.f, a0 = 0.f, a1 = 0.f, a2 = 0.f, aV = 0.f, n0 = 0.f, n1 = 0.f, n2 = 0.f;
@@ -1220,8 +1206,9 @@ __global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 8 
     if (mylast > 0) atomicMax(&max_last, mylast);
     __syncthreads();
 
-    const uint32_t start = ranges[2 * tile];
-    const int tile_len = (int)(ranges[2 * tile + 1] - start);
+    const uint2 range = tile_range(ranges, tile);
+    const uint32_t start = range.x;
+    const int tile_len = (int)(range.y - start);
     const float4 *recv = rec + (size_t)v * (size_t)n * kRecStride4;
     float *gv = recgrad + (size_t)v * (size_t)n * kGradFloats;
     float gS = 0.f;
@@ -1437,8 +1424,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         if (pa.last > 0) atomicMax(&max_last, pa.last);
     }
     __syncthreads();
-    const uint32_t start = ranges[2 * tile];
-    const int tile_len = (int)(ranges[2 * tile + 1] - start);
+    const uint2 range = tile_range(ranges, tile);
+    const uint32_t start = range.x;
+    const int tile_len = (int)(range.y - start);
     const float4 *recv = rec + (size_t)v * (size_t)n * kRecStride4;
     float *gv = recgrad + (size_t)v * (size_t)n * kGradFloats;
     const float inv_s2 = rc.two_inv_s2 * 0.5f;

@@ -17,6 +17,7 @@
 // Item counts may live in device memory (pair counts are data dependent), so grids
 // are sized by capacity and blocks past the live count exit at once.
 #include "ss_internal.h"
+#include <algorithm>
 
 namespace ss {
 
@@ -49,37 +50,28 @@ hipError_t fill_u32(uint32_t *p, uint32_t value, int64_t count, hipStream_t st)
     return hipGetLastError();
 }
 
+__global__ void k_reset_pass(uint32_t *flag, unsigned long long *stat, unsigned long long *extra)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < kStatSlots * kStatStride) stat[i] = 0ull;
+    if (i == 0) {
+        *flag = 0u;
+        if (extra) *extra = 0ull;
+    }
+}
+
+hipError_t reset_pass(uint32_t *flag, unsigned long long *stat, unsigned long long *extra, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_reset_pass, dim3((kStatSlots * kStatStride + 255) / 256), dim3(256), 0, st, flag,
+                       stat, extra);
+    return hipGetLastError();
+}
+
 hipError_t fill_f32(float *p, float value, int64_t count, hipStream_t st)
 {
     union { float f; uint32_t u; } cv;
     cv.f = value;
     return fill_u32(reinterpret_cast<uint32_t *>(p), cv.u, count, st);
-}
-
-// ------------------------------------------------------------------ block scan
-// Exclusive scan of one uint32 per thread over a 256-thread block; returns the
-// exclusive prefix, *total gets the block sum.
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t *lds_w,
-                                                         uint32_t *total)
-{
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    uint32_t inc = x;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        uint32_t y = __shfl_up(inc, d, kWave);
-        if (lane >= d) inc += y;
-    }
-    if (lane == kWave - 1) lds_w[w] = inc;
-    __syncthreads();
-    uint32_t wbase = 0, tot = 0;
-    for (int i = 0; i < (int)(blockDim.x / kWave); ++i) {
-        uint32_t t = lds_w[i];
-        if (i < w) wbase += t;
-        tot += t;
-    }
-    __syncthreads();
-    *total = tot;
-    return wbase + inc - x;
 }
 
 // ------------------------------------------------------------- pair-count scan
@@ -118,56 +110,67 @@ __device__ __forceinline__ void store_items(uint32_t *out, int64_t base, int64_t
 
 __global__ void k_scan_reduce(const uint32_t *in, int64_t len, uint32_t *partials)
 {
-    __shared__ uint32_t lds[kSortWaves];
+    __shared__ unsigned long long lds[kSortWaves];
     int64_t base = (int64_t)blockIdx.x * kSortTile + (int64_t)threadIdx.x * kSortItems;
     uint32_t v[kSortItems];
     load_items(in, base, len, v);
-    uint32_t s = 0;
+    unsigned long long s = 0;
 #pragma unroll
     for (int i = 0; i < kSortItems; ++i) s += v[i];
-    uint32_t tot;
-    block_exclusive_scan(s, lds, &tot);
-    if (threadIdx.x == 0) partials[blockIdx.x] = tot;
+    for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, kWave);
+    if ((threadIdx.x & (kWave - 1)) == 0) lds[threadIdx.x / kWave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < kSortWaves; ++k) s += lds[k];
+        partials[blockIdx.x] = (uint32_t)min(s, 0xFFFFFFFFull);
+    }
 }
 
-// One block: exclusive scan of the per-chunk sums in 64-bit, overflow detection.
+// One block: exclusive scan in place in 64-bit (results clamped to 2^32 - 1), overflow
+// detection.
 constexpr int kScanPartialsThreads = 1024;
+constexpr int kScanPartialsItems = 8;
+constexpr int kScanOneBlock = 2 * kScanPartialsThreads * kScanPartialsItems;
 
 __global__ __launch_bounds__(kScanPartialsThreads) void k_scan_partials(
     uint32_t *partials, int64_t nparts, uint32_t *out_total, unsigned long long *counters,
     int which, uint32_t *flags, uint64_t cap)
 {
     __shared__ unsigned long long lds[kScanPartialsThreads / kWave];
-    __shared__ unsigned long long carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-    for (int64_t b0 = 0; b0 < nparts; b0 += blockDim.x) {
-        int64_t i = b0 + threadIdx.x;
-        unsigned long long x = i < nparts ? partials[i] : 0ull;
-        unsigned long long inc = x;
+    unsigned long long carry = 0;
+    for (int64_t b0 = 0; b0 < nparts; b0 += kScanPartialsThreads * kScanPartialsItems) {
+        const int64_t i = b0 + (int64_t)threadIdx.x * kScanPartialsItems;
+        uint32_t x[kScanPartialsItems];
+        unsigned long long sum = 0;
+#pragma unroll
+        for (int k = 0; k < kScanPartialsItems; ++k) {
+            x[k] = i + k < nparts ? partials[i + k] : 0u;
+            sum += x[k];
+        }
+        unsigned long long inc = sum;
         for (int d = 1; d < kWave; d <<= 1) {
             unsigned long long y = __shfl_up(inc, d, kWave);
             if (lane >= d) inc += y;
         }
         if (lane == kWave - 1) lds[w] = inc;
         __syncthreads();
-        unsigned long long wbase = 0, tot = 0;
-        for (int k = 0; k < (int)(blockDim.x / kWave); ++k) {
-            if (k < w) wbase += lds[k];
-            tot += lds[k];
+        unsigned long long run = carry + inc - sum;
+        for (int k = 0; k < kScanPartialsThreads / kWave; ++k) {
+            if (k < w) run += lds[k];
+            carry += lds[k];
         }
-        unsigned long long excl = carry + wbase + inc - x;
-        if (i < nparts) partials[i] = (uint32_t)(excl > 0xFFFFFFFFull ? 0xFFFFFFFFull : excl);
-        __syncthreads();
-        if (threadIdx.x == 0) carry += tot;
+#pragma unroll
+        for (int k = 0; k < kScanPartialsItems; ++k) {
+            if (i + k < nparts) partials[i + k] = (uint32_t)min(run, 0xFFFFFFFFull);
+            run += x[k];
+        }
         __syncthreads();
     }
     if (threadIdx.x == 0) {
-        unsigned long long total = carry;
-        counters[which] = total;
-        *out_total = (uint32_t)(total > 0xFFFFFFFFull ? 0xFFFFFFFFull : total);
-        if (total > 0xFFFFFFFFull || total > cap) flags[0] |= 1u;
+        counters[which] = carry;
+        *out_total = (uint32_t)min(carry, 0xFFFFFFFFull);
+        if (carry > 0xFFFFFFFFull || carry > cap) flags[0] |= 1u;
     }
 }
 
@@ -197,20 +200,23 @@ size_t scan_temp_elems(int64_t len)
     return (size_t)((len + kSortTile - 1) / kSortTile) + 1;
 }
 
-hipError_t scan_pair_counts(const uint32_t *counts, int64_t n, int32_t nv,
-                            uint32_t *out, uint32_t *partials, unsigned long long *counters,
-                            int which, uint32_t *flags, uint64_t cap, hipStream_t st)
+// Up to kScanOneBlock sums (4M (view, rank) pairs) one block scans them all: ~6 us, less
+// than the two further launches of the three-kernel scan.
+hipError_t scan_pair_sums(uint32_t *sums, int64_t n, int32_t nv, uint32_t *partials,
+                          unsigned long long *counters, int which, uint32_t *flags, uint64_t cap,
+                          hipStream_t st)
 {
-    int64_t len = (int64_t)nv * n;
-    int64_t nb = (len + kSortTile - 1) / kSortTile;
-    if (nb > 0)
-        hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kSortThreads), 0, st,
-                           counts, len, partials);
-    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kScanPartialsThreads), 0, st, partials, nb,
-                       out + len, counters, which, flags, cap);
-    if (nb > 0)
-        hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(kSortThreads), 0, st, counts,
-                           len, partials, out);
+    const int64_t len = (int64_t)nv * rank_blocks(n);
+    const bool one = len <= kScanOneBlock;
+    const int64_t nb = (len + kSortTile - 1) / kSortTile;
+    if (!one)
+        hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kSortThreads), 0, st, sums, len,
+                           partials);
+    hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(kScanPartialsThreads), 0, st, one ? sums : partials,
+                       one ? len : nb, sums + len, counters, which, flags, cap);
+    if (!one)
+        hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(kSortThreads), 0, st, sums, len,
+                           partials, sums);
     return hipGetLastError();
 }
 
@@ -429,7 +435,8 @@ template <typename KT>
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const KT *kin, const uint32_t *vin, KT *kout, uint32_t *vout,
     const uint32_t *offs, const SegDesc *segs, int nseg, const unsigned long long *n_dev,
-    int64_t cap, int64_t n_host, int shift, int nbits, uint32_t *ranges, int64_t nkeys)
+    int64_t cap, int64_t n_host, int shift, int nbits, uint32_t *ranges, int64_t nkeys,
+    uint32_t *rank_out)
 {
     constexpr bool kLocal = sizeof(KT) == 2;
     __shared__ uint32_t wcnt[kSortWaves][256];
@@ -511,6 +518,7 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
         if (pos < n_out) {   // always true when histogram and scatter agree
             if (kout) kout[pos] = k;
             vout[pos] = sval[i];
+            if (rank_out && sval[i] < (uint32_t)n_out) rank_out[sval[i]] = pos;
             // the tile a key names: local keys sit on the segment's base
             const int64_t gk = kLocal ? (int64_t)br.base + (int64_t)k : (int64_t)k;
             if (ranges && gk < nkeys) {
@@ -521,12 +529,6 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     }
 }
 
-__global__ void k_ranges_init(uint32_t *ranges, int64_t nkeys)
-{
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < nkeys) reinterpret_cast<uint2 *>(ranges)[k] = make_uint2(0xFFFFFFFFu, 0u);
-}
-
 __global__ void k_ranges_finish(uint32_t *ranges, int64_t nkeys)
 {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -535,32 +537,339 @@ __global__ void k_ranges_finish(uint32_t *ranges, int64_t nkeys)
     if (r.x == 0xFFFFFFFFu) reinterpret_cast<uint2 *>(ranges)[k] = make_uint2(0u, 0u);
 }
 
+hipError_t finish_ranges(uint32_t *ranges, int64_t nkeys, hipStream_t st)
+{
+    if (nkeys <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_ranges_finish, dim3((unsigned)((nkeys + 255) / 256)), dim3(256), 0, st, ranges,
+                       nkeys);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------ sorts of few blocks
+// With few blocks the sort's time is its launches: five per pass above (histogram, three of
+// the scan, scatter).  Here a pass is two.  Digit counts are rows of 256 per block,
+// [block][digit]; a scatter block sums the rows of its segment itself (all of them for the
+// digit totals, those before it for its own offsets).  Block b of segment v has row start_v /
+// TILE + v + (b's place in the segment): rows of different segments are disjoint, and no
+// segment table is needed.  Reading all rows grows with the square of the blocks: up to 128
+// blocks of 1024 items, then up to 256 of 2048 and 4096 (1M items), beyond which the scans
+// above are as fast.  (Counting the next pass's digits while scattering saves the histogram launch, but
+// keys that share a digit then meet on one address: 80 us for a pass of 190,000 pairs.)
+// Depth order of 20,000 surfels: 21 launches, 104 us -> 8 launches, 44 us; of 1M: 145 ->
+// 125 us.
+constexpr int kSmallRows4 = 128, kSmallRows = 256;
+
+SmallSort plan_small_sort(int64_t cap, int32_t nseg, int bits)
+{
+    const int passes = bits <= 8 ? 1 : (bits + 7) / 8;
+    const int64_t extra = nseg > 0 ? nseg + 1 : 1;
+    for (int items : {4, 8, 16}) {
+        const int64_t rows = cap / (items * kSortThreads) + extra;
+        if (rows <= (items == 4 ? kSmallRows4 : kSmallRows)) return SmallSort{items, rows, passes};
+    }
+    return SmallSort{0, 0, passes};
+}
+
+// Depth keys and their first digits' counts
+template <int ITEMS>
+__global__ __launch_bounds__(kSortThreads) void k_depth_keys_hist(const float *__restrict__ mean,
+                                                                  int64_t n, float bz,
+                                                                  uint32_t *__restrict__ keys,
+                                                                  uint32_t *__restrict__ hist)
+{
+    __shared__ uint32_t h[256];
+    h[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t lo = (int64_t)blockIdx.x * (ITEMS * kSortThreads) + threadIdx.x;
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int64_t i = lo + it * kSortThreads;
+        if (i < n) {
+            const uint32_t k = depth_key(bz, mean[3 * i + 2]);
+            keys[i] = k;
+            atomicAdd(&h[k & 255u], 1u);
+        }
+    }
+    __syncthreads();
+    hist[(int64_t)blockIdx.x * 256 + threadIdx.x] = h[threadIdx.x];
+}
+
+// Segments of the tile sort (offs == NULL: one segment of all items)
+struct SmallSegs {
+    const uint32_t *offs;
+    int64_t stride;
+    int32_t nseg;
+    const ViewDesc *views;
+};
+
+// Block b's segment and its items [i0, i1) (none: i0 >= i1)
+struct SmallBlock {
+    int64_t start, end, row0, i0, i1;
+    uint32_t base;
+};
+
+template <int TILE>
+__device__ __forceinline__ SmallBlock small_block(const SmallSegs &sg, int64_t n, int64_t b)
+{
+    SmallBlock s{0, n, 0, 0, 0, 0};
+    if (sg.offs) {
+        int lo = 0, hi = sg.nseg - 1;                 // last segment whose first row is <= b
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (min((int64_t)sg.offs[mid * sg.stride], n) / TILE + mid <= b) lo = mid; else hi = mid - 1;
+        }
+        s.start = min((int64_t)sg.offs[lo * sg.stride], n);
+        s.end = min((int64_t)sg.offs[(lo + 1) * sg.stride], n);
+        s.row0 = s.start / TILE + lo;
+        s.base = (uint32_t)sg.views[lo].tile_off;
+    }
+    s.i0 = s.start + (b - s.row0) * TILE;
+    s.i1 = b < s.row0 ? s.i0 : min(s.end, s.i0 + TILE);
+    return s;
+}
+
+template <typename KT, int ITEMS>
+__global__ __launch_bounds__(kSortThreads) void k_small_hist(const KT *__restrict__ keys, SmallSegs sg,
+                                                             const unsigned long long *__restrict__ n_dev,
+                                                             int64_t cap, int64_t n_host, int shift,
+                                                             uint32_t *__restrict__ hist)
+{
+    __shared__ uint32_t h[256];
+    const SmallBlock s = small_block<ITEMS * kSortThreads>(sg, live_count(n_dev, cap, n_host), blockIdx.x);
+    if (s.i0 >= s.i1) return;                         // uniform over the block; its row is not read
+    uint32_t key[ITEMS];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int64_t i = s.i0 + it * kSortThreads + threadIdx.x;
+        key[it] = i < s.i1 ? (uint32_t)keys[i] : 0u;
+    }
+    h[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it)
+        if (s.i0 + it * kSortThreads + threadIdx.x < s.i1)
+            atomicAdd(&h[key_digit<KT>((KT)key[it], s.base, shift)], 1u);
+    __syncthreads();
+    hist[(int64_t)blockIdx.x * 256 + threadIdx.x] = h[threadIdx.x];
+}
+
+template <typename KT, int ITEMS>
+__global__ __launch_bounds__(kSortThreads) void k_small_scatter(
+    const KT *__restrict__ kin, const uint32_t *__restrict__ vin, KT *__restrict__ kout,
+    uint32_t *__restrict__ vout, const uint32_t *__restrict__ hist, int64_t rows, SmallSegs sg, const unsigned long long *__restrict__ n_dev, int64_t cap,
+    int64_t n_host, int shift, int nbits, uint32_t *__restrict__ ranges, int64_t nkeys,
+    uint32_t *__restrict__ rank_out)
+{
+    constexpr int TILE = ITEMS * kSortThreads;
+    constexpr bool kLocal = sizeof(KT) == 2;
+    __shared__ uint32_t wcnt[kSortWaves][256];
+    __shared__ uint32_t wsink[kSortWaves][kWave];
+    __shared__ uint4 csum[2][kSortWaves][kWave];      // column sums per wave: all rows, rows before
+    __shared__ uint32_t dbase[256], gshift[256];
+    __shared__ uint32_t lds_w[kSortWaves];
+    __shared__ KT skey[TILE];
+    __shared__ uint32_t sval[TILE];
+    const int64_t n = live_count(n_dev, cap, n_host);
+    const SmallBlock sb = small_block<TILE>(sg, n, blockIdx.x);
+    const int64_t start = sb.start, end = sb.end, row0 = sb.row0, i0 = sb.i0, i1 = sb.i1;
+    const int64_t mine = blockIdx.x - row0;
+    const uint32_t base = sb.base;
+    if (i0 >= i1) return;                             // uniform over the block
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const int64_t wbase = i0 + (int64_t)w * (ITEMS * kWave);
+    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
+    uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int64_t i = wbase + it * kWave + lane;
+        const bool valid = i < i1;
+        key[it] = valid ? (uint32_t)kin[i] : 0u;
+        val[it] = valid ? (vin ? vin[i] : (uint32_t)i) : 0u;
+    }
+    for (int i = threadIdx.x; i < kSortWaves * 256; i += kSortThreads) (&wcnt[0][0])[i] = 0;
+    // column sums of the segment's rows, four digits per lane and a quarter of the rows per wave
+    const int64_t nrows = min((end - start + TILE - 1) / TILE, rows - row0);
+    uint4 all = make_uint4(0, 0, 0, 0), bef = make_uint4(0, 0, 0, 0);
+    const uint4 *hrow = reinterpret_cast<const uint4 *>(hist + row0 * 256) + lane;
+#pragma unroll 8
+    for (int64_t r = w; r < nrows; r += kSortWaves) {
+        const uint4 x = hrow[r * 64];
+        all.x += x.x; all.y += x.y; all.z += x.z; all.w += x.w;
+        if (r < mine) { bef.x += x.x; bef.y += x.y; bef.z += x.z; bef.w += x.w; }
+    }
+    csum[0][w][lane] = all;
+    csum[1][w][lane] = bef;
+    __syncthreads();
+    // stable ranks within the wave's rows of items (see k_radix_scatter)
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const bool valid = wbase + it * kWave + lane < i1;
+        const uint32_t d = key_digit<KT>((KT)key[it], base, shift);
+        const uint64_t m = digit_peers(d, valid, nbits);
+        const uint32_t before = __popcll(m & lt_mask);
+        const bool leader = valid && before == 0;
+        uint32_t *cnt = leader ? &wcnt[w][d] : &wsink[w][lane];
+        const uint32_t old = atomicAdd(cnt, leader ? (uint32_t)__popcll(m) : 0u);
+        const int from = m != 0 ? (int)__builtin_ctzll(m) : lane;
+        rank[it] = (uint32_t)__shfl((int)old, from, kWave) + before;
+    }
+    __syncthreads();
+    {
+        const int d = threadIdx.x;
+        const uint32_t *c0 = reinterpret_cast<const uint32_t *>(csum[0]), *c1 = reinterpret_cast<const uint32_t *>(csum[1]);
+        uint32_t total = 0, before = 0, run = 0;
+#pragma unroll
+        for (int k = 0; k < kSortWaves; ++k) {
+            total += c0[k * 256 + d];
+            before += c1[k * 256 + d];
+            const uint32_t c = wcnt[k][d];
+            wcnt[k][d] = run;
+            run += c;
+        }
+        uint32_t tot;
+        const uint32_t below = block_exclusive_scan(total, lds_w, &tot);
+        const uint32_t excl = block_exclusive_scan(run, lds_w, &tot);
+        dbase[d] = excl;
+        gshift[d] = (uint32_t)start + below + before - excl;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int64_t i = wbase + it * kWave + lane;
+        if (i < i1) {
+            const uint32_t d = key_digit<KT>((KT)key[it], base, shift);
+            const uint32_t lp = dbase[d] + wcnt[w][d] + rank[it];
+            if (lp < (uint32_t)TILE) {                // always true when the counts agree
+                skey[lp] = (KT)key[it];
+                sval[lp] = val[it];
+            }
+        }
+    }
+    __syncthreads();
+    const int nloc = (int)(i1 - i0);
+    for (int i = threadIdx.x; i < nloc; i += kSortThreads) {
+        const KT k = skey[i];
+        const int64_t pos = (int64_t)gshift[key_digit<KT>(k, base, shift)] + i;
+        // within the segment whenever counts and items agree
+        const uint32_t p32 = (uint32_t)pos;
+        if (p32 < start || p32 >= end) continue;
+        const uint32_t v = sval[i];
+        if (kout) kout[p32] = k;
+        vout[p32] = v;
+        if (rank_out && v < (uint32_t)n) rank_out[v] = p32;
+        const int64_t gk = kLocal ? (int64_t)base + (int64_t)k : (int64_t)k;
+        if (ranges && gk < nkeys) {
+            if (i == 0 || skey[i - 1] != k) atomicMin(&ranges[2 * gk], p32);
+            if (i == nloc - 1 || skey[i + 1] != k) atomicMax(&ranges[2 * gk + 1], p32 + 1);
+        }
+    }
+}
+
+template <typename KT>
+static void small_passes(const SmallSort &plan, KT *ka, uint32_t *va, KT *kb, uint32_t *vb, bool index_vals,
+                         bool have_hist, int64_t cap, const unsigned long long *n_dev, int64_t n_host, int bits,
+                         uint32_t *hist, const SmallSegs &sg, uint32_t *ranges, int64_t nkeys,
+                         uint32_t *rank_out, bool *result_in_b, hipStream_t st)
+{
+    *result_in_b = false;
+    for (int p = 0; p < plan.passes; ++p) {
+        const bool last = p == plan.passes - 1;
+        const int shift = 8 * p, nbits = std::max(1, std::min(8, bits - shift));
+        const uint32_t *vin = p == 0 && index_vals ? nullptr : va;
+        KT *ko = last ? nullptr : kb;      // nothing reads the sorted keys
+        const dim3 grid((unsigned)plan.rows), blk(kSortThreads);
+        auto pass = [&](auto hist_kernel, auto scatter_kernel) {
+            if (p > 0 || !have_hist)
+                hipLaunchKernelGGL(hist_kernel, grid, blk, 0, st, ka, sg, n_dev, cap, n_host, shift, hist);
+            hipLaunchKernelGGL(scatter_kernel, grid, blk, 0, st, ka, vin, ko, vb, hist, plan.rows, sg,
+                               n_dev, cap, n_host, shift, nbits, last ? ranges : nullptr, nkeys,
+                               last ? rank_out : nullptr);
+        };
+        if (plan.items == 4) pass(k_small_hist<KT, 4>, k_small_scatter<KT, 4>);
+        else if (plan.items == 8) pass(k_small_hist<KT, 8>, k_small_scatter<KT, 8>);
+        else pass(k_small_hist<KT, 16>, k_small_scatter<KT, 16>);
+        std::swap(ka, kb);
+        std::swap(va, vb);
+        *result_in_b = !*result_in_b;
+    }
+}
+
+template <typename KT>
+hipError_t small_sort_tiles(const SmallSort &plan, KT *keys_a, uint32_t *vals_a, KT *keys_b,
+                            uint32_t *vals_b, int64_t cap, const unsigned long long *n_dev, int bits,
+                            uint32_t *hist, bool *result_in_b, hipStream_t st, const SortSegments &seg)
+{
+    const SmallSegs sg{seg.offs, seg.stride, seg.nseg, seg.views};
+    small_passes<KT>(plan, keys_a, vals_a, keys_b, vals_b, false, false, cap, n_dev, 0, bits, hist, sg,
+                     seg.nkeys > 0 ? seg.ranges : nullptr, seg.nkeys, nullptr, result_in_b, st);
+    return hipGetLastError();
+}
+
+template hipError_t small_sort_tiles<uint32_t>(const SmallSort &, uint32_t *, uint32_t *, uint32_t *, uint32_t *,
+                                               int64_t, const unsigned long long *, int, uint32_t *, bool *,
+                                               hipStream_t, const SortSegments &);
+template hipError_t small_sort_tiles<uint16_t>(const SmallSort &, uint16_t *, uint32_t *, uint16_t *, uint32_t *,
+                                               int64_t, const unsigned long long *, int, uint32_t *, bool *,
+                                               hipStream_t, const SortSegments &);
+
+__global__ void k_depth_keys(const float *__restrict__ mean, int64_t n, float bz,
+                             uint32_t *__restrict__ keys, uint32_t *__restrict__ vals)
+{
+    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    keys[i] = depth_key(bz, mean[3 * i + 2]);
+    vals[i] = (uint32_t)i;
+}
+
+hipError_t depth_sort(const float *mean, int64_t n, float bz, uint32_t *keys_a, uint32_t *vals_a,
+                      uint32_t *keys_b, uint32_t *vals_b, void *temp, uint32_t *rank,
+                      bool *result_in_b, hipStream_t st)
+{
+    *result_in_b = false;
+    if (n <= 0) return hipSuccess;
+    const SmallSort plan = plan_small_sort(n, 0, 32);
+    if (plan.rows == 0) {
+        hipLaunchKernelGGL(k_depth_keys, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, mean, n, bz,
+                           keys_a, vals_a);
+        return radix_sort_pairs(keys_a, vals_a, keys_b, vals_b, n, nullptr, n, 32, temp, result_in_b, st,
+                                nullptr, rank);
+    }
+    uint32_t *hist = reinterpret_cast<uint32_t *>(temp);
+    const dim3 grid((unsigned)plan.rows), blk(kSortThreads);
+    if (plan.items == 4)
+        hipLaunchKernelGGL(k_depth_keys_hist<4>, grid, blk, 0, st, mean, n, bz, keys_a, hist);
+    else if (plan.items == 8)
+        hipLaunchKernelGGL(k_depth_keys_hist<8>, grid, blk, 0, st, mean, n, bz, keys_a, hist);
+    else
+        hipLaunchKernelGGL(k_depth_keys_hist<16>, grid, blk, 0, st, mean, n, bz, keys_a, hist);
+    small_passes<uint32_t>(plan, keys_a, vals_a, keys_b, vals_b, true, true, n, nullptr, n, 32, hist,
+                           SmallSegs{nullptr, 0, 0, nullptr}, nullptr, 0, rank, result_in_b, st);
+    return hipGetLastError();
+}
+
 static int64_t sort_blocks(int64_t items) { return (items + kSortTile - 1) / kSortTile; }
 
 size_t radix_temp_bytes(int64_t max_items, int32_t max_segs)
 {
+    const size_t small = (size_t)kSmallRows * 256 * sizeof(uint32_t);
     const int64_t nb = sort_blocks(max_items > 0 ? max_items : 1) + max_segs;
     const int64_t hist = 256 * nb;
     const int64_t parts = (hist + kSortTile - 1) / kSortTile + 1;
-    return (size_t)(hist + parts) * sizeof(uint32_t) + 256 +
-           (size_t)(max_segs + 1) * sizeof(SegDesc) + 256;
+    return std::max(small, (size_t)(hist + parts) * sizeof(uint32_t) + 256 +
+                               (size_t)(max_segs + 1) * sizeof(SegDesc) + 256);
 }
 
 template <typename KT>
 hipError_t radix_sort_pairs(KT *keys_a, uint32_t *vals_a, KT *keys_b,
                             uint32_t *vals_b, int64_t cap, const unsigned long long *n_dev,
                             int64_t n_host, int bits, void *temp, bool *result_in_b,
-                            hipStream_t st, const SortSegments *seg)
+                            hipStream_t st, const SortSegments *seg, uint32_t *rank_out)
 {
     *result_in_b = false;
     const int64_t items = n_dev ? cap : n_host;
     const int32_t nseg = seg ? seg->nseg : 0;
     const int64_t nb = sort_blocks(items) + nseg;
-    if (sort_blocks(items) == 0) {
-        if (seg && seg->ranges && seg->nkeys > 0)
-            return fill_u32(seg->ranges, 0u, 2 * seg->nkeys, st);
-        return hipSuccess;
-    }
+    if (sort_blocks(items) == 0) return hipSuccess;
     uint32_t *hist = reinterpret_cast<uint32_t *>(temp);
     const int64_t hlen = 256 * nb;
     const int64_t nparts = (hlen + kSortTile - 1) / kSortTile;
@@ -571,9 +880,6 @@ hipError_t radix_sort_pairs(KT *keys_a, uint32_t *vals_a, KT *keys_b,
         segs = reinterpret_cast<SegDesc *>(static_cast<char *>(temp) + off);
         hipLaunchKernelGGL(k_seg_table, dim3(1), dim3(kSegThreads), 0, st, seg->offs, seg->stride,
                            nseg, seg->views, n_dev, cap, segs);
-        if (seg->ranges && seg->nkeys > 0)
-            hipLaunchKernelGGL(k_ranges_init, dim3((unsigned)((seg->nkeys + 255) / 256)), dim3(256),
-                               0, st, seg->ranges, seg->nkeys);
     }
     uint32_t *ranges = seg && seg->nkeys > 0 ? seg->ranges : nullptr;
     const int passes = bits <= 8 ? 1 : (bits + 7) / 8;   // one pass at least: ranges come from it
@@ -594,22 +900,20 @@ hipError_t radix_sort_pairs(KT *keys_a, uint32_t *vals_a, KT *keys_b,
         const bool last = p == passes - 1;
         hipLaunchKernelGGL(k_radix_scatter<KT>, dim3((unsigned)nb), dim3(kSortThreads), 0, st, ki,
                            vi, last && ranges ? nullptr : ko, vo, hist, segs, nseg, n_dev, cap,
-                           n_host, shift, nbits, last ? ranges : nullptr, seg ? seg->nkeys : 0);
+                           n_host, shift, nbits, last ? ranges : nullptr, seg ? seg->nkeys : 0,
+                           last ? rank_out : nullptr);
         std::swap(ki, ko);
         std::swap(vi, vo);
         *result_in_b = !*result_in_b;
     }
-    if (ranges)
-        hipLaunchKernelGGL(k_ranges_finish, dim3((unsigned)((seg->nkeys + 255) / 256)), dim3(256),
-                           0, st, ranges, seg->nkeys);
     return hipGetLastError();
 }
 
 template hipError_t radix_sort_pairs<uint32_t>(uint32_t *, uint32_t *, uint32_t *, uint32_t *, int64_t,
                                                const unsigned long long *, int64_t, int, void *, bool *,
-                                               hipStream_t, const SortSegments *);
+                                               hipStream_t, const SortSegments *, uint32_t *);
 template hipError_t radix_sort_pairs<uint16_t>(uint16_t *, uint32_t *, uint16_t *, uint32_t *, int64_t,
                                                const unsigned long long *, int64_t, int, void *, bool *,
-                                               hipStream_t, const SortSegments *);
+                                               hipStream_t, const SortSegments *, uint32_t *);
 
 }  // namespace ss

@@ -140,26 +140,71 @@ hipError_t launch_tile_order(const uint32_t *ranges, int32_t ntiles,
                              const unsigned long long *total_pairs, bool chunked,
                              uint32_t *order, uint32_t *parts, hipStream_t st);
 
+// Exclusive scan of one uint32 per thread over the block (lds_w: one word per wave); *total
+// gets the block sum.
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t *lds_w,
+                                                         uint32_t *total)
+{
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    uint32_t inc = x;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        uint32_t y = __shfl_up(inc, d, kWave);
+        if (lane >= d) inc += y;
+    }
+    if (lane == kWave - 1) lds_w[w] = inc;
+    __syncthreads();
+    uint32_t wbase = 0, tot = 0;
+    for (int i = 0; i < (int)(blockDim.x / kWave); ++i) {
+        uint32_t t = lds_w[i];
+        if (i < w) wbase += t;
+        tot += t;
+    }
+    __syncthreads();
+    *total = tot;
+    return wbase + inc - x;
+}
+
+// The tile lists' ranges hold (first, last + 1) per tile, (2^32 - 1, 0) for an empty one.
+__device__ __forceinline__ uint2 tile_range(const uint32_t *ranges, int tile)
+{
+    const uint2 r = reinterpret_cast<const uint2 *>(ranges)[tile];
+    return r.x < r.y ? r : make_uint2(0u, 0u);
+}
+
+// Depth key: kappa = fl32(b_z - p_z) (Eq. depth_affine_camera on the centre) as an
+// order-preserving uint32: total order over all finite floats, no altitude limit.
+__device__ __forceinline__ uint32_t depth_key(float bz, float pz)
+{
+    const uint32_t b = __float_as_uint(__fsub_rn(bz, pz));
+    return b ^ ((b >> 31) ? 0xFFFFFFFFu : 0x80000000u);
+}
+
 // ------------------------------------------------------------------- launchers
 // sort.hip
-// Temp bytes of radix_sort_pairs for up to max_items items in up to max_segs segments.
+// Temp bytes of the sorts below for up to max_items items in up to max_segs segments.
 size_t radix_temp_bytes(int64_t max_items, int32_t max_segs);
 hipError_t fill_u32(uint32_t *p, uint32_t value, int64_t count, hipStream_t st);
 hipError_t fill_f32(float *p, float value, int64_t count, hipStream_t st);
-// Exclusive scan of per-(view, rank) tile counts (contiguous, depth-rank order):
-// out[v*n + r] = sum of counts before (v, r); out[V*n] = total; flags[0] |= 1 if the
-// total exceeds 2^32-1 or `cap`; counters[which] = total (uint64).
-hipError_t scan_pair_counts(const uint32_t *counts, int64_t n,
-                            int32_t nv, uint32_t *out, uint32_t *partials,
-                            unsigned long long *counters, int which, uint32_t *flags,
-                            uint64_t cap, hipStream_t st);
+// Zeros a pass's overflow flag, its work counters (kStatSlots x kStatStride) and *extra (or
+// NULL) in one launch.
+hipError_t reset_pass(uint32_t *flag, unsigned long long *stat, unsigned long long *extra, hipStream_t st);
+// Pair counts arrive as sums over blocks of kRankBlock ranks of a view (from launch_project),
+// sums[v * rank_blocks(n) + block]; in place they become their exclusive scan (clamped to
+// 2^32 - 1), sums[nv * rank_blocks(n)] = total; flags[0] |= 1 if the total exceeds 2^32-1 or
+// `cap`; counters[which] = total (uint64).
+constexpr int kRankBlock = 256;
+constexpr int64_t rank_blocks(int64_t n) { return (n + kRankBlock - 1) / kRankBlock; }
+hipError_t scan_pair_sums(uint32_t *sums, int64_t n, int32_t nv, uint32_t *partials,
+                          unsigned long long *counters, int which, uint32_t *flags, uint64_t cap,
+                          hipStream_t st);
 size_t scan_temp_elems(int64_t len);
 // Items that arrive grouped in segments, each sorted on its own keys minus a base:
 // segment v holds items [offs[v * stride], offs[(v + 1) * stride]) (clamped to the live
 // count) with keys in [views[v].tile_off, views[v].tile_off + 2^bits).  The result equals
 // a stable sort of the whole array on the key.  With `ranges` (nkeys entries of
-// (begin, end), interleaved), the sort also writes each key's output run; keys with no
-// item get (0, 0).
+// (begin, end), interleaved, set to (2^32 - 1, 0) beforehand), the sort also writes each
+// key's output run.
 struct SortSegments {
     const uint32_t *offs;
     int64_t stride;
@@ -177,29 +222,49 @@ template <typename KT>
 hipError_t radix_sort_pairs(KT *keys_a, uint32_t *vals_a, KT *keys_b,
                             uint32_t *vals_b, int64_t cap, const unsigned long long *n_dev,
                             int64_t n_host, int bits, void *temp, bool *result_in_b,
-                            hipStream_t st, const SortSegments *seg = nullptr);
+                            hipStream_t st, const SortSegments *seg = nullptr,
+                            uint32_t *rank_out = nullptr);
+
+// Sorts of few blocks (see sort.hip): items per thread and rows of 256 digit counts; rows
+// == 0: too many blocks, sort with radix_sort_pairs.
+struct SmallSort {
+    int items;
+    int64_t rows;
+    int passes;
+};
+SmallSort plan_small_sort(int64_t cap, int32_t nseg, int bits);
+// The tile sort of a SmallSort plan; `hist` (rows * 256 words) is scratch.
+template <typename KT>
+hipError_t small_sort_tiles(const SmallSort &plan, KT *keys_a, uint32_t *vals_a, KT *keys_b,
+                            uint32_t *vals_b, int64_t cap, const unsigned long long *n_dev, int bits,
+                            uint32_t *hist, bool *result_in_b, hipStream_t st, const SortSegments &seg);
+// Order of the surfels by depth key (ties by index), and each surfel's rank in it.
+hipError_t depth_sort(const float *mean, int64_t n, float bz, uint32_t *keys_a, uint32_t *vals_a,
+                      uint32_t *keys_b, uint32_t *vals_b, void *temp, uint32_t *rank,
+                      bool *result_in_b, hipStream_t st);
+// ranges of empty tiles from (2^32 - 1, 0) to (0, 0)
+hipError_t finish_ranges(uint32_t *ranges, int64_t nkeys, hipStream_t st);
 
 // raster.hip
-hipError_t launch_depth_keys(const float *mean, int64_t n, float bz, uint32_t *keys,
-                             uint32_t *vals, hipStream_t st);
 hipError_t launch_gather_params(const uint32_t *order, const SurfelPtrs &s, float *out,
                                 hipStream_t st);
-// vis_rank: visibility per (rank, view), [n][nv] (see launch_vis_to_rank), or NULL.
+// vis_rank: visibility per (rank, view), [n][nv] (see launch_vis_to_rank), or NULL.  sums:
+// pair counts per block of kRankBlock ranks, [nv][rank_blocks(n)]; counts (per pair count,
+// [nv][n]) are written only with tmask.  Also sets ranges (nranges entries, or NULL) to
+// empty for the tile sort.
 hipError_t launch_project(const float *sorted, int64_t n, int32_t nv, const ViewDesc *views,
                           const float *Fxy, const float *dF, const SunCam *sun,
                           const float *vis_rank, float bz, int ts, const RasterConsts &rc,
-                          float *rec, short4 *tiles, uint32_t *counts, const uint32_t *tmask,
-                          hipStream_t st);
-// out[rank * nv + v] = vis[v * n + order[rank]]; rank (n entries) is scratch that ends up
-// holding the inverse of order.
-hipError_t launch_vis_to_rank(const float *vis, int64_t n, int32_t nv, const uint32_t *order,
-                              uint32_t *rank, float *out, hipStream_t st);
+                          float *rec, short4 *tiles, uint32_t *counts, uint32_t *sums,
+                          const uint32_t *tmask, uint32_t *ranges, int64_t nranges, hipStream_t st);
+// out[rank[k] * nv + v] = vis[v * n + k]
+hipError_t launch_vis_to_rank(const float *vis, int64_t n, int32_t nv, const uint32_t *rank, float *out,
+                              hipStream_t st);
 // keys16: tile ids local to the view as uint16 (views of at most 2^16 tiles), else the
-// global tile id as uint32; `keys` points at the chosen width.
-hipError_t launch_emit(const uint32_t *order, int64_t n, int32_t nv, const ViewDesc *views,
-                       const short4 *tiles, const uint32_t *counts, const uint32_t *offsets,
-                       uint64_t cap, void *keys, bool keys16, uint32_t *vals,
-                       const uint32_t *tmask, hipStream_t st);
+// global tile id as uint32; `keys` points at the chosen width.  base: scan_pair_sums' output.
+hipError_t launch_emit(int64_t n, int32_t nv, const ViewDesc *views, const short4 *tiles,
+                       const uint32_t *counts, const uint32_t *base, uint64_t cap, void *keys,
+                       bool keys16, uint32_t *vals, const uint32_t *tmask, hipStream_t st);
 hipError_t launch_raster_fwd(int ts, bool depth_only, bool has_vis, int32_t total_tiles,
                              int32_t nv, const ViewDesc *views, const uint32_t *ranges,
                              const uint32_t *lists, const float *rec, int64_t n,

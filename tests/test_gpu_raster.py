@@ -387,3 +387,58 @@ def test_heavy_first_tile_order_changes_no_pixel(ts):
         err = rel_err(g1[k], g0[k])
         print(f"tile order 0 vs 1, ts {ts}: {k} {err:.2e}")
         assert err < 1e-3, k
+
+
+@pytest.mark.parametrize("n,views,slack", [
+    (1, 1, 0),                 # one item
+    (1023, 2, 0), (1025, 2, 0),            # around one block of 1024 items
+    (130_049, 1, 0), (131_073, 3, 0),      # last size of 1024-item blocks, first of 2048
+    (523_000, 1, 0), (523_500, 1, 0),      # 2048 -> 4096 items a block
+    (1_045_000, 1, 0), (1_050_000, 1, 0),  # few blocks -> the three-kernel scans
+    (40_000, 70, 0),                       # more views than some segments have blocks
+    (9_000, 2, 3_000_000)])                # a capacity far beyond the pairs: empty blocks
+def test_depth_order_and_tile_lists_across_sort_sizes(n, views, slack):
+    """Order, tile lists and ranges against a stable numpy sort (integers: exact).  Quantised
+    altitudes give long runs of equal depth keys, which must stay in index order."""
+    rng = np.random.default_rng(n + views)
+    f = lambda a: torch.as_tensor(np.ascontiguousarray(a, np.float32), device="cuda")
+    mean = np.stack([rng.uniform(-30, 30, n), rng.uniform(-30, 30, n), np.round(rng.normal(size=n) * 8) / 4], 1)
+    mean[:, 2] = np.where(rng.uniform(size=n) < 0.5, mean[:, 2], rng.normal(size=n))
+    eye = np.tile(np.eye(3)[None], (n, 1, 1))
+    surf = ss.SurfelTensors(f(mean), f(eye[:, 0]), f(eye[:, 1]), f(rng.uniform(0.02, 0.3, (n, 2))),
+                            f(rng.uniform(0.01, 0.9, n)), f(rng.uniform(size=(n, 3))))
+    W = np.full(views, 61, np.int32)
+    H = np.full(views, 47, np.int32)
+    F = np.zeros((views, 2, 4), np.float32)
+    F[:, 0, 0], F[:, 1, 1] = 1.0, 0.8
+    F[:, 0, 3], F[:, 1, 3] = 30.5 + np.arange(views) * 0.25, 23.5
+    F[views // 2, 0, 3] = 1e6 if views > 2 else F[views // 2, 0, 3]        # one view sees nothing
+    vt = ss.ViewTensors(W, H, f(F), 12.0)
+    plan = ss.Plan(context(), n, W, H, ss.default_settings(tile_size=8, batch_depth=64))
+    plan.ensure_capacity(surf, vt)
+    if slack:
+        plan.bind(plan.cap_main + slack, 0)
+    plan.forward(surf, vt)
+    b = plan.debug_binning(0)
+    key = np.float32(12.0) - mean.astype(np.float32)[:, 2]
+    order = np.argsort(key, kind="stable")
+    np.testing.assert_array_equal(b["order"], order)
+    tx = 8
+    keys, who, off = [], [], 0
+    for v in range(views):
+        t = b["tiles"][v][order]
+        nx, ny = np.maximum(t[:, 1] - t[:, 0] + 1, 0), np.maximum(t[:, 3] - t[:, 2] + 1, 0)
+        for dy in range(int(ny.max(initial=0))):
+            for dx in range(int(nx.max(initial=0))):
+                m = np.nonzero((dx < nx) & (dy < ny))[0]
+                keys.append(off + (t[m, 2] + dy).astype(np.int64) * tx + t[m, 0] + dx)
+                who.append(m)
+        off += tx * 6
+    keys, who = np.concatenate(keys), np.concatenate(who)
+    o = np.lexsort((who, keys))
+    assert b["lists"].shape[0] == keys.size
+    np.testing.assert_array_equal(b["lists"], order[who[o]])
+    cnt = np.bincount(keys, minlength=off)
+    end = np.cumsum(cnt)
+    expect = np.where(cnt[:, None] > 0, np.stack([end - cnt, end], 1), 0)
+    np.testing.assert_array_equal(b["ranges"], expect)
