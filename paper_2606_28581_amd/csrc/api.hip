@@ -325,11 +325,11 @@ static ss_status prepare(ss_plan *p, const ss_surfels *s, const ss_views *v, boo
     }
     StageScope scope(p, SS_STAGE_DEPTH_SORT, st);
     bool in_b = false;
-    SS_HIP(depth_sort(s->mean, p->n, v->b_z, ka, va, kb, vb, p->at<void>(L.radix_temp),
-                      p->at<uint32_t>(sun ? L.inv_sun : L.inv_main), &in_b, st));
+    uint32_t *rank = p->at<uint32_t>(sun ? L.inv_sun : L.inv_main);
+    SS_HIP(depth_sort(s->mean, p->n, v->b_z, ka, va, kb, vb, p->at<void>(L.radix_temp), rank, &in_b, st));
     uint32_t *order = in_b ? vb : va;
     SurfelPtrs sp{s->mean, s->t_u, s->t_v, s->scale, s->opacity, s->albedo, p->n};
-    SS_HIP(launch_gather_params(order, sp, sorted, st));
+    SS_HIP(launch_gather_params(rank, sp, sorted, st));
     *order_out = order;
     *sorted_out = sorted;
     return SS_OK;

@@ -246,7 +246,7 @@ hipError_t depth_sort(const float *mean, int64_t n, float bz, uint32_t *keys_a, 
 hipError_t finish_ranges(uint32_t *ranges, int64_t nkeys, hipStream_t st);
 
 // raster.hip
-hipError_t launch_gather_params(const uint32_t *order, const SurfelPtrs &s, float *out,
+hipError_t launch_gather_params(const uint32_t *rank, const SurfelPtrs &s, float *out,
                                 hipStream_t st);
 // vis_rank: visibility per (rank, view), [n][nv] (see launch_vis_to_rank), or NULL.  sums:
 // pair counts per block of kRankBlock ranks, [nv][rank_blocks(n)]; counts (per pair count,
