@@ -794,8 +794,9 @@ static ss_status backward_pass(ss_plan *p, const ss_surfels *s, const ss_views *
     }
     {
         StageScope scope(p, SS_STAGE_PROJECT_BWD, st);
-        SS_HIP(launch_project_bwd(p->at<float>(L.sorted_main), p->n, p->order_main, p->nv, v->Fxy,
-                                  v->dF, consts(p->st).det_rel_eps_d, recgrad, d_mean, d_t_u, d_t_v,
+        SS_HIP(launch_project_bwd(p->at<float>(L.sorted_main), p->n, p->order_main,
+                                  p->at<uint32_t>(L.inv_main), p->nv, v->Fxy, v->dF,
+                                  consts(p->st).det_rel_eps_d, recgrad, d_mean, d_t_u, d_t_v,
                                   d_scale, d_opacity, d_albedo, p->at<float>(L.dF_parts), st));
     }
     StageScope scope(p, SS_STAGE_REDUCE, st);

@@ -287,9 +287,10 @@ hipError_t launch_raster_bwd(int ts, bool has_vis, int32_t total_tiles, int32_t 
 // the ranges of different tiles are disjoint, so (pairs / 64 + tiles + 1) * 64 words suffice.
 size_t cmask_words(int64_t pair_cap, int32_t tiles);
 int project_bwd_blocks(int64_t n);
+// recgrad is consumed (its first n rows may hold the surfel gradients by rank afterwards).
 hipError_t launch_project_bwd(const float *sorted, int64_t n, const uint32_t *order,
-                              int32_t nv, const float *Fxy, const float *dF, double det_rel_eps,
-                              const float *recgrad, float *d_mean, float *d_tu, float *d_tv,
+                              const uint32_t *rank, int32_t nv, const float *Fxy, const float *dF, double det_rel_eps,
+                              float *recgrad, float *d_mean, float *d_tu, float *d_tv,
                               float *d_scale, float *d_opac, float *d_alb, float *dF_partials,
                               hipStream_t st);
 // Per view: the 16-float tile rows of the raster backward summed into d_colC, d_colc and

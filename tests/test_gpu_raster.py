@@ -442,3 +442,25 @@ def test_depth_order_and_tile_lists_across_sort_sizes(n, views, slack):
     end = np.cumsum(cnt)
     expect = np.where(cnt[:, None] > 0, np.stack([end - cnt, end], 1), 0)
     np.testing.assert_array_equal(b["ranges"], expect)
+
+
+def test_backward_writes_gradients_directly_and_by_rows():
+    """Up to 65,536 surfels the projection backward writes the gradient arrays itself, beyond
+    by way of rank-ordered rows: one transparent surfel more must change nothing."""
+    sc = synth.make_scene(synth.tiny(n_surfels=65_536, views=((131, 120), (90, 77)), extent=120.0, seed=12))
+    more = dict(sc, surfels={k: np.concatenate([a, a[-1:]]) for k, a in sc["surfels"].items()})
+    more["surfels"]["opacity"] = more["surfels"]["opacity"].copy()
+    more["surfels"]["opacity"][-1] = 0.0
+    dI, dD, dN = (torch.as_tensor(a, device="cuda") for a in synth.upstream_grads(sc))
+    out = []
+    for scene in (sc, more):
+        plan, surf, views = make_plan(scene, ts=8)
+        fwd = plan.forward(surf, views)
+        g = plan.backward(surf, views, fwd, dI, dD, dN)
+        out.append({k: to_np(t).copy() for k, t in g.items()})
+    for k in GRAD_KEYS:
+        a, b = out[0][k], out[1][k]
+        if k in ("mean", "t_u", "t_v", "scale", "opacity", "albedo"):
+            assert not b[-1].any()
+            b = b[:-1]
+        assert rel_err(b, a) <= ATOMIC_ORDER_TOL, k
