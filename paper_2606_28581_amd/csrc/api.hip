@@ -217,7 +217,10 @@ static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs)
     L.pk_b = take((size_t)cm * 4); L.pv_b = take((size_t)cm * 4);
     L.ranges_main = take((size_t)p->tiles_main_max * 8);
     L.recgrad = take(vn * kGradFloats * 4);
-    L.colour_parts = take((size_t)p->tiles_main_max * 16 * 4);
+    // a row per 8x8 block of any tile size (sides rounded up to whole 32-pixel tiles)
+    size_t blocks8 = 0;
+    for (int v = 0; v < p->nv; ++v) blocks8 += (size_t)((p->W[v] + 31) / 32) * ((p->H[v] + 31) / 32) * 16;
+    L.colour_parts = take(blocks8 * 16 * 4);
     L.dF_parts = take((size_t)project_bwd_blocks(p->n) * nv * 8 * 4);
     L.rec_sun = take(vn * kSunRecStride4 * 16);
     L.tiles_sun = take(vn * sizeof(short4));
@@ -233,8 +236,8 @@ static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs)
     L.inv_main = take(n * 4);
     L.inv_sun = take(n * 4);
     L.vis_rank = take(vn * 4);
-    // forward -> backward contributor masks of 8x8 tiles (other sizes use the box test)
-    L.cmask_bytes = p->st.tile_size == 8 ? cmask_words(cm, p->tiles_main_max) * 8 : 0;
+    // forward -> backward contributor masks at the current tile size
+    L.cmask_bytes = cmask_words(cm, p->tiles_main, p->st.tile_size) * 8;
     L.cmask = take(L.cmask_bytes);
     // heavy-first raster dispatch orders and their per-XCD block counts
     L.torder_main = take((size_t)p->tiles_main_max * 4);
@@ -410,12 +413,11 @@ static ss_status bin_views(ss_plan *p, const ss_views *v, bool sun, const float 
     return SS_OK;
 }
 
-// Contributor masks exist for 8x8 tiles when the workspace was laid out for them at the
-// current pair capacity (a tile-size change keeps the layout: then the box test is used).
+// Contributor masks: there is room for them unless the tile size grew since the workspace was
+// laid out (then the backward uses the box test).
 static unsigned long long *cmask_ptr(const ss_plan *p)
 {
-    if (p->st.tile_size != 8 || p->L.cmask_bytes < cmask_words(p->cap_main, p->tiles_main_max) * 8)
-        return nullptr;
+    if (p->L.cmask_bytes < cmask_words(p->cap_main, p->tiles_main, p->st.tile_size) * 8) return nullptr;
     return p->at<unsigned long long>(p->L.cmask);
 }
 
@@ -800,7 +802,8 @@ static ss_status backward_pass(ss_plan *p, const ss_surfels *s, const ss_views *
                                   d_scale, d_opacity, d_albedo, p->at<float>(L.dF_parts), st));
     }
     StageScope scope(p, SS_STAGE_REDUCE, st);
-    SS_HIP(launch_view_reduce(p->at<float>(L.colour_parts), max_view_tiles(p->vmain),
+    SS_HIP(launch_view_reduce(p->at<float>(L.colour_parts),
+                              raster_bwd_sub(p->st.tile_size, cmask_ptr(p) != nullptr), max_view_tiles(p->vmain),
                               p->at<float>(L.dF_parts), project_bwd_blocks(p->n), p->nv,
                               p->at<ViewDesc>(L.views_main), d_colC, d_colc, d_ambient, d_dF,
                               p->at<float>(L.vr_parts), st));

@@ -628,9 +628,9 @@ __global__ __launch_bounds__(TS *TS) void k_raster_fwd(
     DistArgs da)
 {
     constexpr int NT = TS * TS;
-    // 8x8 view passes record, per pixel and 64-position word of the tile list, which
-    // records it composited (the backward walks only those)
-    constexpr bool CM = TS == 8 && !DEPTH_ONLY;
+    // view passes record, per pixel and 64-position word of the tile list, which records it
+    // composited (the backward walks only those)
+    constexpr bool CM = !DEPTH_ONLY;
     extern __shared__ float4 lds[];
     // sun maps are equal in size and even in work: one contiguous run of tiles per XCD
     const int tile = rc.torder ? (int)rc.torder[blockIdx.x]
@@ -730,10 +730,7 @@ __global__ __launch_bounds__(TS *TS) void k_raster_fwd(
                 }
                 if (CM) cmc |= take ? 1ull << (jc - c0) : 0ull;
                 Tr = take ? Tn : Tr;
-                if (!CM) {   // with contributor masks both follow from cmc once per chunk
-                    lastpos = take ? pos0 + jc + 1 : lastpos;
-                    ncontrib += take ? 1 : 0;
-                }
+                if (!CM) ncontrib += take ? 1 : 0;   // else it follows from cmc once per chunk
                 done = done || stop;
                 m = stop ? 0ull : m;
             }
@@ -746,13 +743,13 @@ __global__ __launch_bounds__(TS *TS) void k_raster_fwd(
                 // depth does not divide 64, also in the next word
                 const int P0 = pos0 + c0, w = P0 >> 6, sh = P0 & 63;
                 if (w != wcur) {
-                    if (wcur >= 0) cmask[(wbase + wcur) * 64 + tid] = wacc;
+                    if (wcur >= 0) cmask[(wbase + wcur) * NT + tid] = wacc;
                     wacc = 0ull;
                     wcur = w;
                 }
                 wacc |= cmc << sh;
                 if (sh + cnt > 64) {
-                    cmask[(wbase + wcur) * 64 + tid] = wacc;
+                    cmask[(wbase + wcur) * NT + tid] = wacc;
                     wacc = cmc >> (64 - sh);
                     wcur = w + 1;
                 }
@@ -760,7 +757,7 @@ __global__ __launch_bounds__(TS *TS) void k_raster_fwd(
         }
         if (!__syncthreads_or(!done)) break;
     }
-    if (CM && cmask && wcur >= 0) cmask[(wbase + wcur) * 64 + tid] = wacc;
+    if (CM && cmask && wcur >= 0) cmask[(wbase + wcur) * NT + tid] = wacc;
 #undef SS_FETCH_FWD
     {
         // work counters: one 64-bit atomic per wave and counter, into the tile's slot
@@ -829,9 +826,9 @@ static void launch_fwd_t(dim3 grid, size_t lds, hipStream_t st, int32_t nv,
                            colC, colc, amb, sun, image, A, V, D, N, T, last, stats, cmask, da);
 }
 
-size_t cmask_words(int64_t pair_cap, int32_t tiles)
+size_t cmask_words(int64_t pair_cap, int32_t tiles, int ts)
 {
-    return ((size_t)(pair_cap > 0 ? pair_cap : 0) / 64 + (size_t)(tiles > 0 ? tiles : 0) + 1) * 64;
+    return ((size_t)(pair_cap > 0 ? pair_cap : 0) / 64 + (size_t)(tiles > 0 ? tiles : 0) + 1) * ts * ts;
 }
 
 hipError_t launch_raster_fwd(int ts, bool depth_only, bool has_vis, int32_t total_tiles,
@@ -1168,14 +1165,15 @@ __device__ __forceinline__ void pair_gradients(const PairEval &e, bool contrib, 
 // 4x4 quadrant of the wave's 8x8 pixels and walks, back to front, the staged records
 // whose box meets the quadrant (4 ballots per chunk of 64).  A lane takes part in a pair
 // only where the forward composited it - the forward's box and FP32 alpha tests and the
-// pixel's `last` - so the walk revisits exactly the forward's pairs.  (8x8 tiles with
-// the forward's contributor masks use the record-parallel kernel below.)
+// pixel's `last` - so the walk revisits exactly the forward's pairs.  (Only for 16x16 and
+// 32x32 tiles on a workspace laid out for smaller ones, without room for the forward's
+// contributor masks; with them the kernel below runs.)
 // The 16 record-gradient values are reduced within the row and added with one atomic per
 // lane, so one instruction carries the sums of up to four records.
 // The colour adjoint of Eq. image_formation runs first per pixel; its 15 per-view
 // sums are reduced per tile into colour_partials.
 template <int TS, bool HAS_VIS, bool DIST>
-__global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 8 ? 5 : 4))) void k_raster_bwd(
+__global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd(
     int32_t nv, const ViewDesc *__restrict__ views, const uint32_t *__restrict__ ranges,
     const uint32_t *__restrict__ lists, const float4 *__restrict__ rec, int64_t n,
     RasterConsts rc, const float *__restrict__ colC, const float *__restrict__ colc,
@@ -1331,21 +1329,30 @@ __global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 8 
 #undef SS_FETCH_BWD
 }
 
-// ------------------------------------------------- raster backward, 8x8 tiles
-// Record-parallel rows.  With the forward's contributor masks the four 4x4 quadrants of
-// an 8x8 tile are walked one after another, and all four 16-lane rows of the wave work
-// on the *same* quadrant: lane i of every row holds pixel i of the quadrant, and each
-// step takes the next four records of the quadrant's walk (the union of its 16 pixels'
-// masks, back to front), one per row.  The pixel recursion of Eq. rasterization runs
-// across the rows: with rom = 1 / (1 - alpha) for a contributing pair (1 otherwise) and
-// x = w (g . f), row r needs T before its record = T_cur * prod_{k <= r} rom_k and the
-// suffix g . S = gS_cur + sum_{k < r} x_k; both are scans over the four rows, done
-// lane-wise with two lane swaps each (rows 0<->1, 2<->3, then 0,1<->2,3), which also
-// give the totals that advance T_cur and gS_cur.  A step costs ~10 % more VALU than the
-// quadrant-per-row walk but the walk takes sum_q |U_q| / 4 steps instead of
-// sum over chunks of max_q |U_q|, a third fewer on the 2M-surfel views.  Per-pixel state
-// (the adjoint inputs, T, the suffix, the distortion totals) lives in LDS between
-// quadrants.
+// ------------------------------------- raster backward from contributor masks
+// One wave per 8x8 pixel block, record-parallel rows.  The forward's contributor masks say
+// which records of the tile list each pixel composited.  The block's four 4x4 quadrants are
+// walked one after another, and all four 16-lane rows of the wave work on the *same*
+// quadrant: lane i of every row holds pixel i of the quadrant, and each step takes the next
+// four records of the quadrant's walk (the union of its 16 pixels' masks, back to front), one
+// per row.  The pixel recursion of Eq. rasterization runs across the rows: with
+// rom = 1 / (1 - alpha) for a contributing pair (1 otherwise) and x = w (g . f), row r needs T
+// before its record = T_cur * prod_{k <= r} rom_k and the suffix g . S = gS_cur +
+// sum_{k < r} x_k; both are scans over the four rows, done lane-wise with two lane swaps each
+// (rows 0<->1, 2<->3, then 0,1<->2,3), which also give the totals that advance T_cur and
+// gS_cur.  Per-pixel state (the adjoint inputs, T, the suffix, the distortion totals) lives in
+// LDS between quadrants.
+// Only records of the block's union are read.  An 8x8 tile's list is nearly all union, so its
+// 64-position words are staged as they are, a word ahead.  The four (sixteen) blocks of a
+// larger tile share a list of which each composites a part (a third of it at 16x16 on the
+// 0.5 m/px views), so there the records are staged densely, up to 64 from several words: the
+// last step of a quadrant's walk is rarely part-filled.
+// Bound by VALU issue (140 instructions a step, at the issue limit on the 2M-surfel views:
+// 18.8 ms for 40 views).  16x16 tiles, three ~530^2 views of 150k surfels: 244 us, against
+// 430 us for the box-test walk above; 8x8, one 2048^2 view of 1M surfels: 495 us.
+// A step of 16 records x 4 pixels, its scans along the lanes of a row and its sum over pixels
+// on the FP32 matrix cores, issues a quarter fewer VALU instructions but waits on LDS and the
+// matrix pipe at 4 waves per SIMD: 28.3 ms and 749 us.
 constexpr int kPstBase = 10, kPstDist = 5;
 
 __device__ __forceinline__ float swap16_lo_hi(float v, float &hi)
@@ -1390,9 +1397,9 @@ __device__ __forceinline__ float rows_prefix_add(float x, bool odd, bool upper, 
     return upper ? p1 + c : p1;
 }
 
-template <bool HAS_VIS, bool DIST>
+template <int TS, bool HAS_VIS, bool DIST>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd_rp(
-    int32_t nv, const ViewDesc *__restrict__ views, const uint32_t *__restrict__ ranges,
+    int32_t nv, const ViewDesc *__restrict__ views, int32_t ntiles, const uint32_t *__restrict__ ranges,
     const uint32_t *__restrict__ lists, const float4 *__restrict__ rec, int64_t n,
     RasterConsts rc, const float *__restrict__ colC, const float *__restrict__ colc,
     const float *__restrict__ amb, const float *__restrict__ Ain,
@@ -1402,24 +1409,30 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     float *__restrict__ colour_partials, const unsigned long long *__restrict__ cmask,
     DistArgs da)
 {
+    constexpr int WPR = TS / 8, SUB = WPR * WPR, NT = TS * TS;
+    constexpr bool DENSE = TS > 8;
     constexpr int kPst = kPstBase + (DIST ? kPstDist : 0);
-    // LDS: staged records (64 x 6 float4, a record's address is one multiply), their
-    // ranks, the contributor words of the chunk, per-pixel state [field][pixel], the
-    // quadrant's walk list, the tile's largest `last`
-    extern __shared__ float4 lds[];
-    const int batch = min(rc.batch, 64);
-    uint32_t *lds_idx = reinterpret_cast<uint32_t *>(lds + batch * kRecVec4);
-    unsigned long long *ownw = reinterpret_cast<unsigned long long *>(lds_idx + ((batch + 1) & ~1));
-    float *pst = reinterpret_cast<float *>(ownw + 64);
-    uint32_t *qlist = reinterpret_cast<uint32_t *>(pst + kPst * 64);
-    int &max_last = *reinterpret_cast<int *>(qlist + 64);
-    const int tile = rc.torder ? (int)rc.torder[blockIdx.x] : xcd_tile((int)blockIdx.x, (int)gridDim.x);
+    // staged records (a record's address is one multiply), their ranks, the contributor words
+    // of the staged slots, per-pixel state [field][pixel], the quadrant's walk list, the
+    // block's largest `last`
+    __shared__ float4 lds[64 * kRecVec4];
+    __shared__ unsigned long long ownw[64];
+    __shared__ float pst[kPst * 64];
+    __shared__ uint32_t lds_idx[64];
+    __shared__ uint32_t qlist[64];
+    __shared__ int max_last;
+    // blocks go round-robin to the 8 XCDs: the SUB blocks of a tile stay on the tile's XCD
+    const int b = (int)blockIdx.x;
+    const int vb = SUB == 1 ? b : 8 * (b / (8 * SUB)) + b % 8;
+    const int sub = SUB == 1 ? 0 : (b / 8) % SUB;
+    if (vb >= ntiles) return;
+    const int tile = rc.torder ? (int)rc.torder[vb] : xcd_tile(vb, ntiles);
     const int v = find_view(views, nv, tile);
     const ViewDesc vd = views[v];
     const int lt = tile - vd.tile_off;
     const int tx = lt % vd.tiles_x, ty = lt / vd.tiles_x;
     const int lane = threadIdx.x;
-    const int wx0 = tx * 8, wy0 = ty * 8;
+    const int wx0 = tx * TS + (sub % WPR) * 8, wy0 = ty * TS + (sub / WPR) * 8;
     const int row = lane >> 4, li = lane & 15;
     const bool odd = lane & 16, upper = lane & 32;
     // prologue in the owner mapping: lane 16 q + i holds pixel i of quadrant q
@@ -1430,13 +1443,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     const int64_t g = vd.pix_off + local;
     const int64_t b3 = 3 * vd.pix_off + local;
     if (lane == 0) max_last = 0;
-    qlist[lane] = 0u;
     float cg[16];
     {
         const PixelAdjoint pa = pixel_adjoint<HAS_VIS>(inside, v, g, b3, P, colC, colc, amb, Ain, Vin,
                                                        Tin, lastin, dI, dD, dN, cg);
         const float s = wave_transpose_reduce16(cg, lane);
-        if ((lane & 3) == 0) colour_partials[(int64_t)tile * 16 + (lane >> 2)] = s;
+        if ((lane & 3) == 0) colour_partials[((int64_t)tile * SUB + sub) * 16 + (lane >> 2)] = s;
         pst[0 * 64 + lane] = pa.gA0; pst[1 * 64 + lane] = pa.gA1; pst[2 * 64 + lane] = pa.gA2;
         pst[3 * 64 + lane] = pa.gV;  pst[4 * 64 + lane] = pa.gD;
         pst[5 * 64 + lane] = pa.gN0; pst[6 * 64 + lane] = pa.gN1; pst[7 * 64 + lane] = pa.gN2;
@@ -1452,63 +1464,32 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     __syncthreads();
     const uint2 range = tile_range(ranges, tile);
     const uint32_t start = range.x;
-    const int tile_len = (int)(range.y - start);
+    const int blk_last = min(max_last, (int)(range.y - start));   // a stale `last` stays inside the list
+    if (blk_last <= 0) return;
     const float4 *recv = rec + (size_t)v * (size_t)n * kRecStride4;
     float *gv = recgrad + (size_t)v * (size_t)n * kGradFloats;
     const float inv_s2 = rc.two_inv_s2 * 0.5f;
-    const int blk_last = min(max_last, tile_len);
-    const size_t wbase = (size_t)(start >> 6) + (size_t)tile;
-    const int pidx = ((opy - wy0) << 3) | (opx - wx0);
-    // records of the next batch in q0..q5, list entries of the one after in nidx
-    float4 q0, q1, q2, q3, q4, q5;
-    uint32_t qidx = 0, nidx = 0;
-#define SS_FETCH_RP(IDX)                                                               \
-    {                                                                                  \
-        qidx = min((IDX), (uint32_t)(n - 1));                                          \
-        const float4 *src_ = recv + (size_t)qidx * kRecStride4;                        \
-        q0 = src_[0]; q1 = src_[1]; q2 = src_[2]; q3 = src_[3]; q4 = src_[4]; q5 = src_[5]; \
-    }
-    const int nbat = (blk_last + batch - 1) / batch;
-    if (nbat > 0) {
-        const int bb0 = (nbat - 1) * batch;
-        if (lane < blk_last - bb0) SS_FETCH_RP(lists[start + bb0 + lane]);
-    }
-    if (nbat > 1 && lane < batch) nidx = lists[start + (nbat - 2) * batch + lane];
-    for (int kb = nbat - 1; kb >= 0; --kb) {
-        const int bb = kb * batch;
-        const int nb = min(bb + batch, blk_last) - bb;
-        __syncthreads();
-        if (lane < nb) {
-            float4 *dst = lds + lane * kRecVec4;
-            dst[0] = q0; dst[1] = q1; dst[2] = q2; dst[3] = q3; dst[4] = q4; dst[5] = q5;
-            lds_idx[lane] = qidx;
-        }
-        // this lane's pixel's forward mask over the batch's positions [bb, bb + nb)
-        uint64_t own = 0;
-        {
-            const int sh = bb & 63;
-            const unsigned long long *wp = cmask + (wbase + (bb >> 6)) * 64 + pidx;
-            if (inside) {
-                own = wp[0] >> sh;
-                if (sh != 0 && sh + nb > 64) own |= wp[64] << (64 - sh);
-            }
-            own &= nb >= 64 ? ~0ull : ((1ull << nb) - 1ull);
-        }
+    // this lane's pixel's masks: word kb of the list at own_at[kb * NT]
+    const unsigned long long *own_at = cmask + ((size_t)(start >> 6) + (size_t)tile) * NT + sub * 64 +
+                                       (((opy - wy0) << 3) | (opx - wx0));
+
+    // Walks the staged records, highest slot first; `own` holds the slots that this lane's
+    // pixel composited, row q of `un` their union over quadrant q.
+    auto walk = [&](const uint64_t own, const uint64_t un) {
         ownw[lane] = own;
-        const uint64_t un = row_or64(own);          // row q: the union of quadrant q
         __syncthreads();
-        if (kb > 0 && lane < batch) SS_FETCH_RP(nidx);
-        if (kb > 1 && lane < batch) nidx = lists[start + bb - 2 * batch + lane];
         for (int q = 0; q < 4; ++q) {
-            const uint64_t U = ((uint64_t)__builtin_amdgcn_readlane((int)(uint32_t)(un >> 32), 16 * q) << 32) |
+            const uint64_t U = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(un >> 32), 16 * q) << 32) |
                                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)un, 16 * q);
             if (U == 0) continue;                     // uniform
             const int nq = __popcll(U);
-            // walk list of the quadrant: position of the k-th set bit from the top
+            // walk list of the quadrant: slot of the k-th set bit from the top
             {
                 const bool set = (U >> lane) & 1ull;
                 const int k = lane == 63 ? 0 : __popcll(U >> (lane + 1));
                 if (set) qlist[k] = (uint32_t)lane;
+                // rows past the end of the walk read a staged record too (their weight is zero)
+                if (lane >= nq) qlist[lane] = (uint32_t)__builtin_ctzll(U);
             }
             const int p = 16 * q + li;               // the quadrant's pixel of this lane
             const float gA0 = pst[0 * 64 + p], gA1 = pst[1 * 64 + p], gA2 = pst[2 * 64 + p];
@@ -1525,8 +1506,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
             const int qpx = wx0 + 4 * (q & 1) + (li & 3), qpy = wy0 + 4 * (q >> 1) + (li >> 2);
             const float fx = (float)qpx + 0.5f, fy = (float)qpy + 0.5f;
             __syncthreads();                         // the walk list is complete
-            // record positions are read one step ahead; k < 64, and entries past nq are
-            // stale positions of earlier quadrants, all below the batch size
+            // record slots are read one step ahead
             int jl_next = (int)qlist[row];
             for (int s0 = 0; s0 < nq; s0 += 4) {
                 const int k = s0 + row;
@@ -1566,12 +1546,87 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
             }
             __syncthreads();                         // list and state reused by the next quadrant
         }
+    };
+
+    // Words of the list, back to front.  Ahead of the word in work: the records of the next
+    // (q0..q5, of lanes whose position is in the block's union Un), masks and list entries of
+    // the one after.
+    float4 q0, q1, q2, q3, q4, q5;
+    uint32_t qidx = 0, nidx = 0;
+    uint64_t own_n = 0, un_n = 0, Un = 0, own_nn = 0;
+    int kb = (blk_last + 63) >> 6;
+    auto load_word = [&](int k) {                     // masks and list entries of word k
+        const int nb = blk_last - 64 * k;
+        own_nn = inside ? own_at[(size_t)k * NT] : 0ull;
+        if (nb < 64) own_nn &= (1ull << nb) - 1ull;
+        if (lane < nb) nidx = lists[start + 64 * k + lane];
+    };
+    auto fetch_word = [&]() {                         // unions and records of the loaded word
+        own_n = own_nn;
+        un_n = row_or64(own_n);
+        Un = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            Un |= ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(un_n >> 32), 16 * q) << 32) |
+                  (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)un_n, 16 * q);
+        qidx = min(nidx, (uint32_t)(n - 1));
+        if ((Un >> lane) & 1ull) {
+            const float4 *src = recv + (size_t)qidx * kRecStride4;
+            q0 = src[0]; q1 = src[1]; q2 = src[2]; q3 = src[3]; q4 = src[4]; q5 = src[5];
+        }
+    };
+    auto stage = [&](int slot) {
+        float4 *dst = lds + slot * kRecVec4;
+        dst[0] = q0; dst[1] = q1; dst[2] = q2; dst[3] = q3; dst[4] = q4; dst[5] = q5;
+        lds_idx[slot] = qidx;
+    };
+    load_word(kb - 1);
+    fetch_word();
+    if (kb > 1) load_word(kb - 2);
+    if constexpr (!DENSE) {
+        while (--kb >= 0) {
+            if ((Un >> lane) & 1ull) stage(lane);
+            const uint64_t own = own_n, un = un_n;
+            if (kb > 0) fetch_word();
+            if (kb > 1) load_word(kb - 2);
+            walk(own, un);
+        }
+    } else {
+        int staged = 0;                               // slots 63, 62, ... are taken in turn
+        uint64_t own_s = 0;
+        --kb;
+        for (;;) {
+            if (kb >= 0) {
+                // the last records of the word that still fit
+                const int top = lane == 63 ? 0 : __popcll(Un >> (lane + 1));
+                const bool sel = ((Un >> lane) & 1ull) && top < 64 - staged;
+                uint64_t take = __ballot(sel);
+                Un &= ~take;
+                if (sel) stage(63 - staged - top);
+                while (take != 0) {                   // this pixel's bits to the records' slots
+                    const int j = 63 - (int)__builtin_clzll(take);
+                    take &= ~(1ull << j);
+                    own_s |= ((own_n >> j) & 1ull) << (63 - staged);
+                    ++staged;
+                }
+                if (Un == 0) {
+                    if (--kb >= 0) {
+                        fetch_word();
+                        if (kb > 0) load_word(kb - 1);
+                    }
+                }
+                if (staged < 64 && kb >= 0) continue;
+            }
+            if (staged > 0) walk(own_s, row_or64(own_s));
+            if (kb < 0) break;
+            staged = 0;
+            own_s = 0;
+        }
     }
-#undef SS_FETCH_RP
 }
 
 template <int TS, bool HV, bool DIST>
-static void launch_bwd_d(dim3 grid, size_t lds, hipStream_t st, int32_t nv,
+static void launch_bwd_d(size_t lds, hipStream_t st, int32_t ntiles, int32_t nv,
                          const ViewDesc *views, const uint32_t *ranges, const uint32_t *lists,
                          const float *rec, int64_t n, const RasterConsts &rc,
                          const float *colC, const float *colc, const float *amb,
@@ -1579,27 +1634,22 @@ static void launch_bwd_d(dim3 grid, size_t lds, hipStream_t st, int32_t nv,
                          const float *dI, const float *dD, const float *dN, float *recgrad,
                          float *cp, const unsigned long long *cmask, const DistArgs &da)
 {
-    if constexpr (TS == 8) {
-        if (cmask) {
-            constexpr int kPst = kPstBase + (DIST ? kPstDist : 0);
-            const int b = min(rc.batch, 64);
-            const size_t lds_rp = (size_t)b * kRecVec4 * sizeof(float4) +
-                                  (size_t)((b + 1) & ~1) * sizeof(uint32_t) +
-                                  (size_t)64 * (sizeof(unsigned long long) + kPst * sizeof(float) +
-                                                sizeof(uint32_t)) + sizeof(int);
-            hipLaunchKernelGGL((k_raster_bwd_rp<HV, DIST>), grid, dim3(64), lds_rp, st, nv, views,
-                               ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc, colC,
-                               colc, amb, A, V, T, last, dI, dD, dN, recgrad, cp, cmask, da);
-            return;
-        }
+    if (cmask) {
+        constexpr int SUB = (TS / 8) * (TS / 8);
+        const int64_t blocks = SUB == 1 ? ntiles : ((int64_t)ntiles + 7) / 8 * 8 * SUB;
+        hipLaunchKernelGGL((k_raster_bwd_rp<TS, HV, DIST>), dim3((unsigned)blocks), dim3(64), 0, st, nv,
+                           views, ntiles, ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc,
+                           colC, colc, amb, A, V, T, last, dI, dD, dN, recgrad, cp, cmask, da);
+        return;
     }
-    hipLaunchKernelGGL((k_raster_bwd<TS, HV, DIST>), grid, dim3(TS * TS), lds, st, nv, views,
-                       ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc, colC, colc, amb,
-                       A, V, T, last, dI, dD, dN, recgrad, cp, da);
+    if constexpr (TS != 8)     // 8x8 tiles always have their masks
+        hipLaunchKernelGGL((k_raster_bwd<TS, HV, DIST>), dim3((unsigned)ntiles), dim3(TS * TS), lds, st, nv,
+                           views, ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc, colC, colc,
+                           amb, A, V, T, last, dI, dD, dN, recgrad, cp, da);
 }
 
 template <int TS, bool HV>
-static void launch_bwd_t(dim3 grid, size_t lds, hipStream_t st, int32_t nv,
+static void launch_bwd_t(size_t lds, hipStream_t st, int32_t ntiles, int32_t nv,
                          const ViewDesc *views, const uint32_t *ranges, const uint32_t *lists,
                          const float *rec, int64_t n, const RasterConsts &rc,
                          const float *colC, const float *colc, const float *amb,
@@ -1609,10 +1659,10 @@ static void launch_bwd_t(dim3 grid, size_t lds, hipStream_t st, int32_t nv,
 {
     const DistArgs da = dist ? *dist : DistArgs{0.f, nullptr, nullptr, nullptr, 0};
     if (dist)
-        launch_bwd_d<TS, HV, true>(grid, lds, st, nv, views, ranges, lists, rec, n, rc, colC, colc,
+        launch_bwd_d<TS, HV, true>(lds, st, ntiles, nv, views, ranges, lists, rec, n, rc, colC, colc,
                                    amb, A, V, T, last, dI, dD, dN, recgrad, cp, cmask, da);
     else
-        launch_bwd_d<TS, HV, false>(grid, lds, st, nv, views, ranges, lists, rec, n, rc, colC, colc,
+        launch_bwd_d<TS, HV, false>(lds, st, ntiles, nv, views, ranges, lists, rec, n, rc, colC, colc,
                                     amb, A, V, T, last, dI, dD, dN, recgrad, cp, cmask, da);
 }
 
@@ -1627,24 +1677,26 @@ hipError_t launch_raster_bwd(int ts, bool has_vis, int32_t total_tiles, int32_t 
                              hipStream_t st, const DistArgs *dist)
 {
     if (total_tiles <= 0) return hipSuccess;
-    const dim3 grid((unsigned)total_tiles);
     const size_t lds = (size_t)min(rc.batch, ts * ts) * (kRecVec4 * sizeof(float4) + sizeof(uint32_t)) +
                        (size_t)(ts * ts / 64) * 16 * sizeof(float) + sizeof(int);
+    if (ts == 8 && !cmask) return hipErrorInvalidValue;
 #define SS_BWD(TS_)                                                                          \
     if (ts == TS_) {                                                                         \
         if (has_vis)                                                                         \
-            launch_bwd_t<TS_, true>(grid, lds, st, nv, views, ranges, lists, rec, n, rc,      \
+            launch_bwd_t<TS_, true>(lds, st, total_tiles, nv, views, ranges, lists, rec, n, rc, \
                                     colC, colc, amb, A, V, T, last, dI, dD, dN, recgrad,     \
-                                    colour_partials, cmask, dist);                                 \
+                                    colour_partials, cmask, dist);                           \
         else                                                                                 \
-            launch_bwd_t<TS_, false>(grid, lds, st, nv, views, ranges, lists, rec, n, rc,     \
+            launch_bwd_t<TS_, false>(lds, st, total_tiles, nv, views, ranges, lists, rec, n, rc, \
                                      colC, colc, amb, A, V, T, last, dI, dD, dN, recgrad,    \
-                                     colour_partials, cmask, dist);                                \
+                                     colour_partials, cmask, dist);                          \
     }
     SS_BWD(8) else SS_BWD(16) else SS_BWD(32) else return hipErrorInvalidValue;
 #undef SS_BWD
     return hipGetLastError();
 }
+
+int raster_bwd_sub(int ts, bool masks) { return masks ? (ts / 8) * (ts / 8) : 1; }
 
 // ----------------------------------------------------------- projection backward
 // One thread per rank, looping over views: record gradients -> parameter gradients
@@ -1836,8 +1888,8 @@ hipError_t launch_project_bwd(const float *sorted, int64_t n, const uint32_t *or
     return hipGetLastError();
 }
 
-// Per-view sums of the backward's partial rows: 16 floats per tile (dC 9, dc 3, dL_a 3)
-// and 8 per project_bwd block (dF).  Both are sums of chains with a fixed order (256 chains
+// Per-view sums of the backward's partial rows: `sub` x 16 floats per tile (dC 9, dc 3, dL_a
+// 3) and 8 per project_bwd block (dF).  Both are sums of chains with a fixed order (256 chains
 // per colour column, chain t over rows t, t + 256, ...; 32 per dF column), so that the colour
 // terms and camera deltas of a training run do not depend on how the chains are spread over
 // blocks.  Blocks (c, v) with c < chunks carry 256 / chunks colour chains of view v, one
@@ -1866,6 +1918,7 @@ __device__ __forceinline__ void finish_colour(float (&acc)[16], float (*red)[16]
     }
 }
 
+template <int SUB>
 __global__ __launch_bounds__(kVrThreads) void k_view_reduce(
     const float *__restrict__ colour_rows, const ViewDesc *__restrict__ views,
     const float *__restrict__ dF_rows, int nblocks, float *__restrict__ d_colC,
@@ -1890,20 +1943,28 @@ __global__ __launch_bounds__(kVrThreads) void k_view_reduce(
         return;
     }
     const int rows = views[v].tiles_x * views[v].tiles_y;
-    const float *p = colour_rows + 16 * (int64_t)views[v].tile_off;
+    const float *p = colour_rows + 16 * (int64_t)views[v].tile_off * SUB;
+    // a tile's row is the sum of its SUB rows, in order
+    auto row = [&](int r, int k) {
+        const float *q = p + 16 * (int64_t)r * SUB + k;
+        float x = q[0];
+#pragma unroll
+        for (int w = 1; w < SUB; ++w) x += q[16 * w];
+        return x;
+    };
     if (chunks == 1) {
         float acc[16];
         for (int k = 0; k < 16; ++k) acc[k] = 0.f;
         for (int r = t; r < rows; r += kVrThreads)
-            for (int k = 0; k < 16; ++k) acc[k] += p[16 * (int64_t)r + k];
+            for (int k = 0; k < 16; ++k) acc[k] += row(r, k);
         finish_colour(acc, red, v, d_colC, d_colc, d_amb);
         return;
     }
     // kVrChunks == 16: thread t carries column t % 16 of chain 16 c + t / 16
     const int chain = 16 * c + (t >> 4);
     float s = 0.f;
-#pragma unroll 16
-    for (int r = chain; r < rows; r += kVrThreads) s += p[16 * (int64_t)r + (t & 15)];
+#pragma unroll 16 / SUB
+    for (int r = chain; r < rows; r += kVrThreads) s += row(r, t & 15);
     parts[((int64_t)v * kVrThreads + chain) * 16 + (t & 15)] = s;
 }
 
@@ -1922,15 +1983,22 @@ __global__ __launch_bounds__(kVrThreads) void k_view_finish(const float *__restr
 
 size_t view_reduce_parts(int32_t nv) { return (size_t)nv * kVrThreads * 16; }
 
-hipError_t launch_view_reduce(const float *colour_rows, int64_t max_view_tiles, const float *dF_rows,
+hipError_t launch_view_reduce(const float *colour_rows, int sub, int64_t max_view_tiles, const float *dF_rows,
                               int nblocks, int32_t nv, const ViewDesc *views, float *d_colC,
                               float *d_colc, float *d_amb, float *d_dF, float *parts, hipStream_t st)
 {
     if (nv <= 0) return hipSuccess;
     // up to 8 rows per chain one block per view costs less than a second launch
-    const int chunks = max_view_tiles > 8 * kVrThreads ? kVrChunks : 1;
-    hipLaunchKernelGGL(k_view_reduce, dim3((unsigned)chunks + 1, (unsigned)nv), dim3(kVrThreads), 0, st,
-                       colour_rows, views, dF_rows, nblocks, d_colC, d_colc, d_amb, d_dF, parts);
+    const int chunks = max_view_tiles * sub > 8 * kVrThreads ? kVrChunks : 1;
+    const dim3 grid((unsigned)chunks + 1, (unsigned)nv);
+#define SS_VR(SUB_)                                                                                  \
+    hipLaunchKernelGGL((k_view_reduce<SUB_>), grid, dim3(kVrThreads), 0, st, colour_rows, views, dF_rows, \
+                       nblocks, d_colC, d_colc, d_amb, d_dF, parts)
+    if (sub == 1) SS_VR(1);
+    else if (sub == 4) SS_VR(4);
+    else if (sub == 16) SS_VR(16);
+    else return hipErrorInvalidValue;
+#undef SS_VR
     if (chunks > 1)
         hipLaunchKernelGGL(k_view_finish, dim3((unsigned)nv), dim3(kVrThreads), 0, st, parts, d_colC,
                            d_colc, d_amb);

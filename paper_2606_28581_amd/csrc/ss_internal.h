@@ -282,10 +282,13 @@ hipError_t launch_raster_bwd(int ts, bool has_vis, int32_t total_tiles, int32_t 
                              const float *dD, const float *dN, float *recgrad,
                              float *colour_partials, const unsigned long long *cmask,
                              hipStream_t st, const DistArgs *dist = nullptr);
-// Contributor masks (8x8 tiles): for tile t with list start s, word w of pixel (lane) l is
-// cmask[(s / 64 + t + w) * 64 + l], bit b set iff list position 64 w + b was composited;
-// the ranges of different tiles are disjoint, so (pairs / 64 + tiles + 1) * 64 words suffice.
-size_t cmask_words(int64_t pair_cap, int32_t tiles);
+// Rows of 16 colour partials per tile that launch_raster_bwd writes with or without masks.
+int raster_bwd_sub(int ts, bool masks);
+// Contributor masks: for tile t with list start s, word w of pixel (thread of the forward's
+// block) l is cmask[(s / 64 + t + w) * ts^2 + l], bit b set iff list position 64 w + b was
+// composited; the ranges of different tiles are disjoint, so (pairs / 64 + tiles + 1) * ts^2
+// words suffice.
+size_t cmask_words(int64_t pair_cap, int32_t tiles, int ts);
 int project_bwd_blocks(int64_t n);
 // recgrad is consumed (its first n rows may hold the surfel gradients by rank afterwards).
 hipError_t launch_project_bwd(const float *sorted, int64_t n, const uint32_t *order,
@@ -293,11 +296,11 @@ hipError_t launch_project_bwd(const float *sorted, int64_t n, const uint32_t *or
                               float *recgrad, float *d_mean, float *d_tu, float *d_tv,
                               float *d_scale, float *d_opac, float *d_alb, float *dF_partials,
                               hipStream_t st);
-// Per view: the 16-float tile rows of the raster backward summed into d_colC, d_colc and
+// Per view: the raster backward's colour rows (sub per tile, 16 floats each) summed into d_colC, d_colc and
 // d_amb, the 8-float rows [view][nblocks] of project_bwd into d_dF.  parts:
 // view_reduce_parts(nv) floats.
 size_t view_reduce_parts(int32_t nv);
-hipError_t launch_view_reduce(const float *colour_rows, int64_t max_view_tiles, const float *dF_rows,
+hipError_t launch_view_reduce(const float *colour_rows, int sub, int64_t max_view_tiles, const float *dF_rows,
                               int nblocks, int32_t nv, const ViewDesc *views, float *d_colC,
                               float *d_colc, float *d_amb, float *d_dF, float *parts, hipStream_t st);
 // out row (v, order[r]) = the first row_words words of in row (v, r), in rows in_stride

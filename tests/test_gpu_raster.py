@@ -187,6 +187,26 @@ def test_backward_8x8_without_contributor_masks():
     check_backward(sc, plan, surf, views, out, ref, vis=vis)
 
 
+@pytest.mark.parametrize("ts,bound_at,n,mean_list", [
+    (16, 16, 400, 0), (16, 16, 3000, 300),   # staged batches part-filled, and split across words
+    (32, 32, 400, 0), (32, 32, 3000, 300),
+    (16, 8, 3000, 300), (32, 8, 400, 0),     # no room for contributor masks: the box-test walk
+])
+def test_backward_of_larger_tiles_with_and_without_masks(ts, bound_at, n, mean_list):
+    sc = scene_tiny(seed=15, n=n)
+    vis = np.random.default_rng(5).uniform(size=(len(sc["width"]), n)).astype(np.float32)
+    plan, surf, views = make_plan(sc, ts=bound_at)
+    if ts != bound_at:
+        plan.set_settings(ss.default_settings(tile_size=ts, batch_depth=64))
+    m, _ = plan.count_pairs(surf, views)
+    assert m <= plan.cap_main
+    tiles = sum(-(-int(w) // ts) * -(-int(h) // ts) for w, h in zip(sc["width"], sc["height"]))
+    assert m >= mean_list * tiles
+    out = plan.forward(surf, views, torch.as_tensor(vis, device="cuda"))
+    ref = oracle.forward(sc, oracle_settings(ts=ts), vis=vis)
+    check_backward(sc, plan, surf, views, out, ref, vis=vis)
+
+
 def test_backward_config1():
     sc = synth.make_scene(synth.config(1))
     plan, surf, views = make_plan(sc)
