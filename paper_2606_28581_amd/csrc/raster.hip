@@ -573,10 +573,6 @@ __device__ __forceinline__ bool box_hits(float bx, float by, int wx0, int wy0)
 
 
 // ------------------------------------------------------------- per-pixel coverage
-// Records of a batch sit in LDS as structure of arrays by float4 group: group g of
-// record j at lds4[g * B + j] (B = batch), so lanes that read different records touch
-// consecutive 16-byte slots.
-//
 // chunk_mask: lane t holds record c0 + t of a chunk of up to 64 (valid = t < count);
 // returns, for the calling lane's pixel (wx0 + lane % 8, wy0 + lane / 8), the 64-bit
 // mask of chunk records whose pixel box contains that pixel.  A box is separable into a
@@ -584,12 +580,12 @@ __device__ __forceinline__ bool box_hits(float bx, float by, int wx0, int wy0)
 // the whole 64 x 64 coverage matrix; lane p keeps column mask p % 8 AND row mask p / 8.
 // Outside the box alpha < alpha_min holds exactly (the box bounds both rho branches at
 // the alpha_min level), so skipping those pairs changes no result.
-__device__ __forceinline__ uint64_t chunk_mask(float4 head, bool valid, int wx0, int wy0,
+__device__ __forceinline__ uint64_t chunk_mask(float box_x, float box_y, bool valid, int wx0, int wy0,
                                                int lane)
 {
     uint32_t colbits = 0, rowbits = 0;
     if (valid) {
-        const uint32_t x = __float_as_uint(head.x), y = __float_as_uint(head.y);
+        const uint32_t x = __float_as_uint(box_x), y = __float_as_uint(box_y);
         const int clo = max((int)(int16_t)(x & 0xFFFFu) - wx0, 0);
         const int chi = min((int)(int16_t)(x >> 16) - wx0, 7);
         const int rlo = max((int)(int16_t)(y & 0xFFFFu) - wy0, 0);
@@ -610,15 +606,126 @@ __device__ __forceinline__ uint64_t chunk_mask(float4 head, bool valid, int wx0,
 }
 
 // ---------------------------------------------------------------- raster forward
-// One block per tile (TS x TS threads, one pixel each); wave w owns an 8x8 sub-block.
-// Records of the tile list are staged in LDS in batches (one record per thread, the
-// next batch prefetched into registers).  Per chunk of 64 staged records each lane
-// builds the mask of records covering its pixel and composites only those, front to
-// back, until its transmittance would drop below T_min; a wave whose 64 pixels all
-// stopped skips the rest, the block stops when all waves have.
-template <int TS, bool DEPTH_ONLY, bool HAS_VIS, bool DIST>
-__global__ __launch_bounds__(TS *TS) void k_raster_fwd(
-    int32_t nv, const ViewDesc *__restrict__ views, const uint32_t *__restrict__ ranges,
+// A pixel's running sums.
+struct PixelSums {
+    float Tr = 1.f, aD = 0.f, a0 = 0.f, a1 = 0.f, a2 = 0.f, aV = 0.f, n0 = 0.f, n1 = 0.f, n2 = 0.f;
+    // distortion: accumulated value, reference depth, shifted first and second moments
+    float dacc = 0.f, zref = 0.f, M1 = 0.f, M2 = 0.f;
+    bool has_ref = false, done;
+    int ncontrib = 0, neval = 0;
+};
+
+// A record in LDS, as structure of arrays: centre (high and low part), Q, (o, z0, k) as one
+// float4 each, and for views albedo with visibility, and the normal.  The record's two branch
+// biases are folded in: a record without an ellipse has Q = NaN, so that its low-pass branch
+// is taken by comparison, and without the low-pass filter (FILT false) every other one takes
+// the ellipse.  48 bytes for a depth-only pair and 76 for a view's instead of 56 and 84: the
+// reads of 64 lanes, each at its own record, are what the walk waits for besides VALU issue
+// (40 views of 2M surfels: 8.19 -> 7.85 ms, their sun maps 4.46 -> 4.35 ms).
+constexpr int kFwdSlots = 64;
+
+template <bool DEPTH_ONLY>
+__device__ __forceinline__ void stage_record(float4 *lds, int slot, float4 r0, float4 r1, float4 r2,
+                                             float4 r3, float4 r4, float4 r5)
+{
+    const float none = r1.z > 0.f ? __uint_as_float(0x7FC00000u) : 0.f;
+    lds[slot] = make_float4(r0.z, r0.w, r1.x, r1.y);
+    lds[kFwdSlots + slot] = r1.z > 0.f ? make_float4(none, none, none, none) : r2;
+    lds[2 * kFwdSlots + slot] = r3;
+    if (!DEPTH_ONLY) { lds[3 * kFwdSlots + slot] = r4; lds[4 * kFwdSlots + slot] = r5; }
+}
+
+// eval_pair's arithmetic on a staged record.
+template <bool FILT>
+__device__ __forceinline__ PairEval eval_staged(const float4 c, const float4 q, float o, float fx, float fy,
+                                                const RasterConsts &rc)
+{
+    PairEval e;
+    e.dx = __fsub_rn(__fsub_rn(fx, c.x), c.z);
+    e.dy = __fsub_rn(__fsub_rn(fy, c.y), c.w);
+    e.u0 = __fmaf_rn(q.y, e.dy, __fmul_rn(q.x, e.dx));
+    e.u1 = __fmaf_rn(q.w, e.dy, __fmul_rn(q.z, e.dx));
+    const float ru = __fmaf_rn(e.u0, e.u0, __fmul_rn(e.u1, e.u1));
+    const float rf = __fmul_rn(__fmaf_rn(e.dx, e.dx, __fmul_rn(e.dy, e.dy)), rc.inv_s2);
+    e.ub = FILT ? ru <= rf : ru == ru;
+    e.G = ex2(__fmul_rn(e.ub ? ru : rf, kNegHalfLog2e));
+    e.oG = __fmul_rn(o, e.G);
+    e.alpha = __builtin_amdgcn_fmed3f(e.oG, 0.f, rc.alpha_max);
+    return e;
+}
+
+// Composites the staged records of mask m (bit j: slot j) onto this lane's pixel, front to
+// back, until its transmittance would drop below T_min.  Returns the composited ones
+// (counted in ncontrib instead when CM is false).
+template <bool DEPTH_ONLY, bool HAS_VIS, bool DIST, bool FILT>
+__device__ __forceinline__ unsigned long long composite(const float4 *lds, uint64_t m, float fx,
+                                                        float fy, const RasterConsts &rc, float ds,
+                                                        PixelSums &p)
+{
+    constexpr int BS = kFwdSlots;
+    constexpr bool CM = !DEPTH_ONLY;
+    unsigned long long cmc = 0ull;
+    while (m != 0) {
+        const int jc = (int)__builtin_ctzll(m);
+        m &= m - 1;
+        const float4 c = lds[jc], q = lds[BS + jc], r3 = lds[2 * BS + jc];
+        ++p.neval;
+        const PairEval e = eval_staged<FILT>(c, q, r3.x, fx, fy, rc);
+        // branch-free: a skipped pair accumulates with weight 0 (w * x + a == a
+        // exactly for the finite record fields), so no exec-mask juggling per pair
+        const bool hit = e.alpha >= rc.alpha_min;
+        const float Tn = __fmul_rn(p.Tr, __fsub_rn(1.f, e.alpha));
+        const bool stop = hit && Tn < rc.T_min;
+        const bool take = hit && !stop;
+        const float w = take ? __fmul_rn(e.alpha, p.Tr) : 0.f;
+        const float z = e.ub ? __fmaf_rn(-r3.z, e.u0, __fmaf_rn(-r3.w, e.u1, r3.y)) : r3.y;
+        p.aD = __fmaf_rn(w, z, p.aD);
+        if (!DEPTH_ONLY) {
+            const float4 r4 = lds[3 * BS + jc], r5 = lds[4 * BS + jc];
+            p.a0 = __fmaf_rn(w, r4.x, p.a0);
+            p.a1 = __fmaf_rn(w, r4.y, p.a1);
+            p.a2 = __fmaf_rn(w, r4.z, p.a2);
+            if (HAS_VIS) p.aV = __fmaf_rn(w, r4.w, p.aV);
+            p.n0 = __fmaf_rn(w, r5.x, p.n0);
+            p.n1 = __fmaf_rn(w, r5.y, p.n1);
+            p.n2 = __fmaf_rn(w, r5.z, p.n2);
+        }
+        if (DIST) {
+            // sum_{j<i} w_j (m_i - m_j)^2 = m'(m' (1 - T) - 2 M1) + M2 with m' the
+            // depth relative to the first contributor
+            p.zref = (take && !p.has_ref) ? z : p.zref;
+            p.has_ref = p.has_ref || take;
+            const float mp = (z - p.zref) * ds;
+            p.dacc = fmaf(w, fmaf(mp, fmaf(mp, 1.f - p.Tr, -2.f * p.M1), p.M2), p.dacc);
+            p.M1 = fmaf(w, mp, p.M1);
+            p.M2 = fmaf(w * mp, mp, p.M2);
+        }
+        if (CM) cmc |= take ? 1ull << jc : 0ull;
+        p.Tr = take ? Tn : p.Tr;
+        if (!CM) p.ncontrib += take ? 1 : 0;   // else it follows from cmc once per chunk
+        p.done = p.done || stop;
+        m = stop ? 0ull : m;
+    }
+    return cmc;
+}
+
+// One wave per 8x8 pixel block of a tile.  Records are staged in LDS, up to 64 at a time;
+// each lane builds the mask of those that cover its pixel and composites them front to
+// back until its transmittance would drop below T_min; a wave whose 64 pixels all stopped
+// is done.
+// 8x8 tiles stage their list as it is, in batches of rc.batch, the next batch prefetched
+// into registers.  The blocks of a larger tile share its list but each is covered by a part
+// of it (about a third at 16x16), so a block first tests the records' boxes, 64 positions at a
+// time, and stages the ones that meet it densely: the walk takes the longest pixel of every
+// staged batch, and that is shorter for 64 records at once than for three times 20.  16x16
+// tiles against one block of four waves that shared the staged list: 20 sun maps of 1M
+// surfels 2175 -> 1578 us, three ~530^2 views of 150k surfels 141 -> 129 us.
+// The loop over a lane's own mask diverges on purpose: a uniform loop (idle lanes on a zeroed
+// slot, work counters in scalar registers) issues 8 % fewer VALU instructions and runs 3-8 %
+// longer, since idle lanes then read LDS too.
+template <int TS, bool DEPTH_ONLY, bool HAS_VIS, bool DIST, bool FILT>
+__global__ __launch_bounds__(64) void k_raster_fwd(
+    int32_t nv, const ViewDesc *__restrict__ views, int32_t ntiles, const uint32_t *__restrict__ ranges,
     const uint32_t *__restrict__ lists, const float4 *__restrict__ rec, int64_t n,
     RasterConsts rc, const float *__restrict__ colC, const float *__restrict__ colc,
     const float *__restrict__ amb, const SunCam *__restrict__ sun, float *__restrict__ image,
@@ -627,141 +734,181 @@ __global__ __launch_bounds__(TS *TS) void k_raster_fwd(
     unsigned long long *__restrict__ stats, unsigned long long *__restrict__ cmask,
     DistArgs da)
 {
-    constexpr int NT = TS * TS;
+    constexpr int WPR = TS / 8, SUB = WPR * WPR, NT = TS * TS;
+    constexpr bool DENSE = TS > 8;
     // view passes record, per pixel and 64-position word of the tile list, which records it
     // composited (the backward walks only those)
     constexpr bool CM = !DEPTH_ONLY;
-    extern __shared__ float4 lds[];
+    constexpr int RS = DEPTH_ONLY ? kSunRecStride4 : kRecStride4;   // record slot
+    __shared__ float4 lds[kFwdSlots * (DEPTH_ONLY ? 3 : 5)];
+    // blocks go round-robin to the 8 XCDs: the SUB blocks of a tile stay on the tile's XCD
+    const int b = (int)blockIdx.x;
+    const int vb = SUB == 1 ? b : 8 * (b / (8 * SUB)) + b % 8;
+    const int sub = SUB == 1 ? 0 : (b / 8) % SUB;
+    if (vb >= ntiles) return;
     // sun maps are equal in size and even in work: one contiguous run of tiles per XCD
-    const int tile = rc.torder ? (int)rc.torder[blockIdx.x]
-                               : xcd_tile<!DEPTH_ONLY>((int)blockIdx.x, (int)gridDim.x);
+    const int tile = rc.torder ? (int)rc.torder[vb] : xcd_tile<!DEPTH_ONLY>(vb, ntiles);
     const int v = find_view(views, nv, tile);
     const ViewDesc vd = views[v];
     const int lt = tile - vd.tile_off;
     const int tx = lt % vd.tiles_x, ty = lt / vd.tiles_x;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    constexpr int WPR = TS / 8;
-    const int wx0 = tx * TS + (wave % WPR) * 8, wy0 = ty * TS + (wave / WPR) * 8;
+    const int lane = threadIdx.x;
+    const int wx0 = tx * TS + (sub % WPR) * 8, wy0 = ty * TS + (sub / WPR) * 8;
     const int px = wx0 + (lane & 7), py = wy0 + (lane >> 3);
     const bool inside = px < vd.W && py < vd.H;
     const float fx = (float)px + 0.5f, fy = (float)py + 0.5f;
     const uint2 range = tile_range(ranges, tile);
     const uint32_t start = range.x, end = range.y;
-    constexpr int RS = DEPTH_ONLY ? kSunRecStride4 : kRecStride4;   // record slot
     const float4 *recv = rec + (size_t)v * (size_t)n * RS;
-    float Tr = 1.f, aD = 0.f, a0 = 0.f, a1 = 0.f, a2 = 0.f, aV = 0.f, n0 = 0.f, n1 = 0.f, n2 = 0.f;
-    // distortion: accumulated value, reference depth, shifted first and second moments
-    float dacc = 0.f, zref = 0.f, M1 = 0.f, M2 = 0.f;
-    bool has_ref = false;
-    int lastpos = 0, ncontrib = 0, neval = 0;
-    bool done = !inside;
-    const int B = min(rc.batch, NT);
-    // LDS stride between a record's float4 groups: a compile-time constant (>= every
-    // batch) so that the group reads are immediate offsets from one address
-    constexpr int BS = NT < 256 ? NT : 256;
-    // records of the next batch in q0..q5, list entries of the one after in nidx: the
-    // gather never waits for the list load it depends on
-    float4 q0, q1, q2, q3, q4, q5;
-    uint32_t nidx = 0;
+    PixelSums p;
+    p.done = !inside;
+    int lastpos = 0;
+    float4 q0, q1, q2, q3, q4, q5;               // records on their way to LDS
+    const size_t wbase = (size_t)(start >> 6) + (size_t)tile;   // tiles' word ranges are disjoint
+    unsigned long long *const word_at = CM && cmask ? cmask + wbase * NT + sub * 64 + lane : nullptr;
+    unsigned long long wacc = 0ull;
+    if constexpr (!DENSE) {
+        int wcur = -1;
+        const int B = min(rc.batch, 64);
+        uint32_t nidx = 0;                        // list entries of the batch after the prefetched one
 #define SS_FETCH_FWD(IDX)                                                              \
     {                                                                                  \
         const float4 *src_ = recv + (size_t)min((IDX), (uint32_t)(n - 1)) * RS;       \
         q0 = src_[0]; q1 = src_[1]; q2 = src_[2]; q3 = src_[3];                        \
         if (!DEPTH_ONLY) { q4 = src_[4]; q5 = src_[5]; }                               \
     }
-    if (start < end && tid < (int)min((uint32_t)B, end - start)) SS_FETCH_FWD(lists[start + tid]);
-    if (start + B < end && tid < (int)min((uint32_t)B, end - start - B)) nidx = lists[start + B + tid];
-    const size_t wbase = (size_t)(start >> 6) + (size_t)tile;   // tiles' word ranges are disjoint
-    unsigned long long wacc = 0ull;
-    int wcur = -1;
-    for (uint32_t b0 = start; b0 < end; b0 += B) {
-        const int nb = (int)min((uint32_t)B, end - b0);
-        __syncthreads();
-        if (tid < nb) {
-            lds[tid] = q0; lds[BS + tid] = q1; lds[2 * BS + tid] = q2; lds[3 * BS + tid] = q3;
-            if (!DEPTH_ONLY) { lds[4 * BS + tid] = q4; lds[5 * BS + tid] = q5; }
-        }
-        __syncthreads();
-        const uint32_t b1 = b0 + B, b2 = b1 + B;
-        if (b1 < end && tid < (int)min((uint32_t)B, end - b1)) SS_FETCH_FWD(nidx);
-        if (b2 < end && tid < (int)min((uint32_t)B, end - b2)) nidx = lists[b2 + tid];
-        const int pos0 = (int)(b0 - start);
-        for (int c0 = 0; c0 < nb; c0 += 64) {
-            if (__ballot(!done) == 0) break;
-            const int cnt = min(64, nb - c0);
-            const float4 head = lds[c0 + (lane < cnt ? lane : 0)];
-            uint64_t m = chunk_mask(head, lane < cnt, wx0, wy0, lane);
-            if (done) m = 0;
-            unsigned long long cmc = 0ull;
-            while (m != 0) {
-                const int jc = c0 + (int)__builtin_ctzll(m);
-                m &= m - 1;
-                const float4 r0 = lds[jc], r1 = lds[BS + jc], r2 = lds[2 * BS + jc], r3 = lds[3 * BS + jc];
-                ++neval;
-                const PairEval e = eval_pair(r0, r1, r2, r3, fx, fy, rc);
-                // branch-free: a skipped pair accumulates with weight 0 (w * x + a == a
-                // exactly for the finite record fields), so no exec-mask juggling per pair
-                const bool hit = e.alpha >= rc.alpha_min;
-                const float Tn = __fmul_rn(Tr, __fsub_rn(1.f, e.alpha));
-                const bool stop = hit && Tn < rc.T_min;
-                const bool take = hit && !stop;
-                const float w = take ? __fmul_rn(e.alpha, Tr) : 0.f;
-                const float z = e.ub ? __fmaf_rn(-r3.z, e.u0, __fmaf_rn(-r3.w, e.u1, r3.y)) : r3.y;
-                aD = __fmaf_rn(w, z, aD);
-                if (!DEPTH_ONLY) {
-                    const float4 r4 = lds[4 * BS + jc], r5 = lds[5 * BS + jc];
-                    a0 = __fmaf_rn(w, r4.x, a0);
-                    a1 = __fmaf_rn(w, r4.y, a1);
-                    a2 = __fmaf_rn(w, r4.z, a2);
-                    if (HAS_VIS) aV = __fmaf_rn(w, r4.w, aV);
-                    n0 = __fmaf_rn(w, r5.x, n0);
-                    n1 = __fmaf_rn(w, r5.y, n1);
-                    n2 = __fmaf_rn(w, r5.z, n2);
-                }
-                if (DIST) {
-                    // sum_{j<i} w_j (m_i - m_j)^2 = m'(m' (1 - T) - 2 M1) + M2 with m' the
-                    // depth relative to the first contributor
-                    zref = (take && !has_ref) ? z : zref;
-                    has_ref = has_ref || take;
-                    const float mp = (z - zref) * da.ds;
-                    dacc = fmaf(w, fmaf(mp, fmaf(mp, 1.f - Tr, -2.f * M1), M2), dacc);
-                    M1 = fmaf(w, mp, M1);
-                    M2 = fmaf(w * mp, mp, M2);
-                }
-                if (CM) cmc |= take ? 1ull << (jc - c0) : 0ull;
-                Tr = take ? Tn : Tr;
-                if (!CM) ncontrib += take ? 1 : 0;   // else it follows from cmc once per chunk
-                done = done || stop;
-                m = stop ? 0ull : m;
-            }
+        if (start < end && lane < (int)min((uint32_t)B, end - start)) SS_FETCH_FWD(lists[start + lane]);
+        if (start + B < end && lane < (int)min((uint32_t)B, end - start - B)) nidx = lists[start + B + lane];
+        for (uint32_t b0 = start; b0 < end; b0 += B) {
+            const int nb = (int)min((uint32_t)B, end - b0);
+            __syncthreads();
+            if (lane < nb) stage_record<DEPTH_ONLY>(lds, lane, q0, q1, q2, q3, q4, q5);
+            const float box_x = q0.x, box_y = q0.y;
+            __syncthreads();
+            const uint32_t b1 = b0 + B, b2 = b1 + B;
+            if (b1 < end && lane < (int)min((uint32_t)B, end - b1)) SS_FETCH_FWD(nidx);
+            if (b2 < end && lane < (int)min((uint32_t)B, end - b2)) nidx = lists[b2 + lane];
+            if (__ballot(!p.done) == 0) break;
+            uint64_t m = chunk_mask(box_x, box_y, lane < nb, wx0, wy0, lane);
+            if (p.done) m = 0;
+            const unsigned long long cmc = composite<DEPTH_ONLY, HAS_VIS, DIST, FILT>(lds, m, fx, fy, rc, da.ds, p);
+            const int P0 = (int)(b0 - start);
             if (CM && cmc != 0ull) {
-                lastpos = pos0 + c0 + 64 - (int)__builtin_clzll(cmc);
-                ncontrib += (int)__popcll(cmc);
+                lastpos = P0 + 64 - (int)__builtin_clzll(cmc);
+                p.ncontrib += (int)__popcll(cmc);
             }
             if (CM && cmask) {
-                // chunk positions [P0, P0 + cnt) fall in word P0 / 64 and, when the batch
-                // depth does not divide 64, also in the next word
-                const int P0 = pos0 + c0, w = P0 >> 6, sh = P0 & 63;
+                // positions [P0, P0 + nb) fall in word P0 / 64 and, when the batch depth does
+                // not divide 64, also in the next word
+                const int w = P0 >> 6, sh = P0 & 63;
                 if (w != wcur) {
-                    if (wcur >= 0) cmask[(wbase + wcur) * NT + tid] = wacc;
+                    if (wcur >= 0) word_at[(size_t)wcur * NT] = wacc;
                     wacc = 0ull;
                     wcur = w;
                 }
                 wacc |= cmc << sh;
-                if (sh + cnt > 64) {
-                    cmask[(wbase + wcur) * NT + tid] = wacc;
+                if (sh + nb > 64) {
+                    word_at[(size_t)wcur * NT] = wacc;
                     wacc = cmc >> (64 - sh);
                     wcur = w + 1;
                 }
             }
         }
-        if (!__syncthreads_or(!done)) break;
+        if (CM && cmask && wcur >= 0) word_at[(size_t)wcur * NT] = wacc;
+    } else {
+        // staged positions of up to 64 consecutive words of the list, one mask each
+        __shared__ unsigned long long segs[CM ? 64 : 1];
+        __shared__ float2 boxes[64];
+        const int nw = (int)((end - start + 63) >> 6);
+        auto entry = [&](int w) {                 // the lane's list entry in word w (0 past the end)
+            const uint32_t k = start + 64u * (uint32_t)w + (uint32_t)lane;
+            return k < end ? lists[k] : 0u;
+        };
+        auto slot = [&](uint32_t idx) { return recv + (size_t)min(idx, (uint32_t)(n - 1)) * RS; };
+        // heads (box and centre) of word wq + 1, list entries of word wq + 2
+        uint32_t idx_h = nw > 0 ? entry(0) : 0u, idx_n = nw > 1 ? entry(1) : 0u;
+        float4 head = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (nw > 0) head = slot(idx_h)[0];
+        int wq = -1, staged = 0, nseg = 0, w0 = 0;
+        uint64_t U = 0;                           // records of word wq still to stage (uniform)
+        for (;;) {
+            if (U == 0 && ++wq < nw) {
+                const int x = __float_as_int(head.x), y = __float_as_int(head.y);
+                const bool meets = ((x << 16) >> 16) <= wx0 + 7 && (x >> 16) >= wx0 &&
+                                   ((y << 16) >> 16) <= wy0 + 7 && (y >> 16) >= wy0 &&
+                                   start + 64u * (uint32_t)wq + (uint32_t)lane < end;
+                U = __ballot(meets);
+                if (meets) {
+                    const float4 *src = slot(idx_h);
+                    q0 = head; q1 = src[1]; q2 = src[2]; q3 = src[3];
+                    if (!DEPTH_ONLY) { q4 = src[4]; q5 = src[5]; }
+                }
+                idx_h = idx_n;
+                if (wq + 1 < nw) head = slot(idx_h)[0];
+                if (wq + 2 < nw) idx_n = entry(wq + 2);
+                if (U == 0) {
+                    if (!CM) continue;
+                    if (lane == 0) segs[nseg] = 0ull;
+                    if (++nseg < 64) continue;
+                }
+            }
+            if (U != 0) {
+                const int k = staged + __popcll(U & ((1ull << lane) - 1ull));
+                const bool sel = ((U >> lane) & 1ull) && k < 64;
+                const uint64_t take = __ballot(sel);
+                U &= ~take;
+                if (sel) {
+                    stage_record<DEPTH_ONLY>(lds, k, q0, q1, q2, q3, q4, q5);
+                    boxes[k] = make_float2(q0.x, q0.y);
+                }
+                staged += (int)__popcll(take);
+                if (CM) {
+                    if (lane == 0) segs[nseg] = take;
+                    ++nseg;
+                }
+                if (staged < 64 && (!CM || nseg < 64)) continue;
+            }
+            __syncthreads();
+            unsigned long long cmc = 0ull;
+            if (staged > 0) {
+                const float2 box = boxes[lane < staged ? lane : 0];
+                uint64_t m = chunk_mask(box.x, box.y, lane < staged, wx0, wy0, lane);
+                if (p.done) m = 0;
+                cmc = composite<DEPTH_ONLY, HAS_VIS, DIST, FILT>(lds, m, fx, fy, rc, da.ds, p);
+            }
+            const bool all_done = __ballot(!p.done) == 0;
+            if (CM) {
+                // slots back to the positions that they came from, word by word
+                p.ncontrib += (int)__popcll(cmc);
+                int s = 0;
+                for (int k = 0; k < nseg; ++k) {
+                    const unsigned long long sg = segs[k];
+                    uint64_t mask = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(sg >> 32)) << 32) |
+                                    (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)sg);
+                    while (mask != 0) {
+                        const int j = (int)__builtin_ctzll(mask);
+                        mask &= mask - 1;
+                        wacc |= ((cmc >> s) & 1ull) << j;
+                        ++s;
+                    }
+                    if (k < nseg - 1 || U == 0 || all_done) {
+                        if (wacc != 0ull) lastpos = 64 * (w0 + k) + 64 - (int)__builtin_clzll(wacc);
+                        if (cmask) word_at[(size_t)(w0 + k) * NT] = wacc;
+                        wacc = 0ull;
+                    }
+                }
+                w0 += U != 0 ? nseg - 1 : nseg;   // a word cut short goes on in the next batch
+                nseg = 0;
+            }
+            __syncthreads();
+            staged = 0;
+            if (wq >= nw || all_done) break;
+        }
     }
-    if (CM && cmask && wcur >= 0) cmask[(wbase + wcur) * NT + tid] = wacc;
 #undef SS_FETCH_FWD
     {
         // work counters: one 64-bit atomic per wave and counter, into the tile's slot
-        unsigned long long c = (unsigned long long)ncontrib, e = (unsigned long long)neval;
+        unsigned long long c = (unsigned long long)p.ncontrib, e = (unsigned long long)p.neval;
         for (int d = 32; d > 0; d >>= 1) {
             c += __shfl_xor(c, d, 64);
             e += __shfl_xor(e, d, 64);
@@ -777,15 +924,15 @@ __global__ __launch_bounds__(TS *TS) void k_raster_fwd(
     const int64_t local = (int64_t)py * vd.W + px;
     const int64_t g = vd.pix_off + local;
     if (DEPTH_ONLY) {
-        Dout[g] = (float)((double)aD + (double)Tr * sun[v].zfar);
+        Dout[g] = (float)((double)p.aD + (double)p.Tr * sun[v].zfar);
         return;
     }
     float C[9] = {1, 0, 0, 0, 1, 0, 0, 0, 1}, cb[3] = {0, 0, 0}, La[3] = {0, 0, 0};
     if (colC) for (int k = 0; k < 9; ++k) C[k] = colC[9 * v + k];
     if (colc) for (int k = 0; k < 3; ++k) cb[k] = colc[3 * v + k];
     if (amb) for (int k = 0; k < 3; ++k) La[k] = amb[3 * v + k];
-    const float Vp = HAS_VIS ? aV : 1.f;
-    const float A[3] = {a0, a1, a2};
+    const float Vp = HAS_VIS ? p.aV : 1.f;
+    const float A[3] = {p.a0, p.a1, p.a2};
     const int64_t b3 = 3 * vd.pix_off + local;
 #pragma unroll
     for (int ch = 0; ch < 3; ++ch) {
@@ -793,21 +940,28 @@ __global__ __launch_bounds__(TS *TS) void k_raster_fwd(
         image[b3 + ch * P] = ca * (Vp + (1.f - Vp) * La[ch]);
         Aout[b3 + ch * P] = A[ch];
     }
-    Nout[b3] = n0; Nout[b3 + P] = n1; Nout[b3 + 2 * P] = n2;
+    Nout[b3] = p.n0; Nout[b3 + P] = p.n1; Nout[b3 + 2 * P] = p.n2;
     Vout[g] = Vp;
-    Dout[g] = aD;
-    Tout[g] = Tr;
+    Dout[g] = p.aD;
+    Tout[g] = p.Tr;
     lastout[g] = lastpos;
     if (DIST) {
-        da.dist[g] = dacc;
-        da.aux[g] = zref;
-        da.aux[da.P + g] = M1;
-        da.aux[2 * da.P + g] = M2;
+        da.dist[g] = p.dacc;
+        da.aux[g] = p.zref;
+        da.aux[da.P + g] = p.M1;
+        da.aux[2 * da.P + g] = p.M2;
     }
 }
 
+// 8x8 blocks of a tile, and the grid of a kernel that runs one wave for each of them.
+constexpr int ts_sub(int ts) { return (ts / 8) * (ts / 8); }
+static int64_t raster_blocks(int sub, int32_t ntiles)
+{
+    return sub == 1 ? ntiles : ((int64_t)ntiles + 7) / 8 * 8 * sub;
+}
+
 template <int TS, bool DO, bool HV>
-static void launch_fwd_t(dim3 grid, size_t lds, hipStream_t st, int32_t nv,
+static void launch_fwd_t(int32_t ntiles, hipStream_t st, int32_t nv,
                          const ViewDesc *views, const uint32_t *ranges, const uint32_t *lists,
                          const float *rec, int64_t n, const RasterConsts &rc,
                          const float *colC, const float *colc, const float *amb,
@@ -816,14 +970,19 @@ static void launch_fwd_t(dim3 grid, size_t lds, hipStream_t st, int32_t nv,
                          unsigned long long *cmask, const DistArgs *dist)
 {
     const DistArgs da = dist ? *dist : DistArgs{0.f, nullptr, nullptr, nullptr, 0};
-    if (!DO && dist)
-        hipLaunchKernelGGL((k_raster_fwd<TS, DO, HV, true>), grid, dim3(TS * TS), lds, st, nv,
-                           views, ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc,
-                           colC, colc, amb, sun, image, A, V, D, N, T, last, stats, cmask, da);
-    else
-        hipLaunchKernelGGL((k_raster_fwd<TS, DO, HV, false>), grid, dim3(TS * TS), lds, st, nv,
-                           views, ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc,
-                           colC, colc, amb, sun, image, A, V, D, N, T, last, stats, cmask, da);
+    const dim3 grid((unsigned)raster_blocks(ts_sub(TS), ntiles));
+#define SS_FWD_LAUNCH(DIST_, FILT_)                                                                    \
+    hipLaunchKernelGGL((k_raster_fwd<TS, DO, HV, DIST_, FILT_>), grid, dim3(64), 0, st, nv, views,     \
+                       ntiles, ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc, colC, colc, \
+                       amb, sun, image, A, V, D, N, T, last, stats, cmask, da)
+    if (!DO && dist) {
+        if (rc.lowpass_mode == 0) SS_FWD_LAUNCH(!DO, true);
+        else SS_FWD_LAUNCH(!DO, false);
+    } else {
+        if (rc.lowpass_mode == 0) SS_FWD_LAUNCH(false, true);
+        else SS_FWD_LAUNCH(false, false);
+    }
+#undef SS_FWD_LAUNCH
 }
 
 size_t cmask_words(int64_t pair_cap, int32_t tiles, int ts)
@@ -841,20 +1000,16 @@ hipError_t launch_raster_fwd(int ts, bool depth_only, bool has_vis, int32_t tota
                              const DistArgs *dist)
 {
     if (total_tiles <= 0) return hipSuccess;
-    const dim3 grid((unsigned)total_tiles);
-    // records staged at a fixed stride of min(ts^2, 256) float4 per field group; the
-    // depth-only pass stages the first 4 of a record's 6 groups
-    const size_t lds = (size_t)min(ts * ts, 256) * (depth_only ? 4 : kRecVec4) * sizeof(float4);
 #define SS_FWD(TS_)                                                                              \
     if (ts == TS_) {                                                                             \
         if (depth_only)                                                                          \
-            launch_fwd_t<TS_, true, false>(grid, lds, st, nv, views, ranges, lists, rec, n, rc,   \
+            launch_fwd_t<TS_, true, false>(total_tiles, st, nv, views, ranges, lists, rec, n, rc,   \
                                            colC, colc, amb, sun, image, A, V, D, N, T, last, stats, cmask, dist);\
         else if (has_vis)                                                                        \
-            launch_fwd_t<TS_, false, true>(grid, lds, st, nv, views, ranges, lists, rec, n, rc,   \
+            launch_fwd_t<TS_, false, true>(total_tiles, st, nv, views, ranges, lists, rec, n, rc,   \
                                            colC, colc, amb, sun, image, A, V, D, N, T, last, stats, cmask, dist);\
         else                                                                                     \
-            launch_fwd_t<TS_, false, false>(grid, lds, st, nv, views, ranges, lists, rec, n, rc,  \
+            launch_fwd_t<TS_, false, false>(total_tiles, st, nv, views, ranges, lists, rec, n, rc,  \
                                             colC, colc, amb, sun, image, A, V, D, N, T, last, stats, cmask, dist);\
     }
     SS_FWD(8) else SS_FWD(16) else SS_FWD(32) else return hipErrorInvalidValue;
@@ -1635,9 +1790,8 @@ static void launch_bwd_d(size_t lds, hipStream_t st, int32_t ntiles, int32_t nv,
                          float *cp, const unsigned long long *cmask, const DistArgs &da)
 {
     if (cmask) {
-        constexpr int SUB = (TS / 8) * (TS / 8);
-        const int64_t blocks = SUB == 1 ? ntiles : ((int64_t)ntiles + 7) / 8 * 8 * SUB;
-        hipLaunchKernelGGL((k_raster_bwd_rp<TS, HV, DIST>), dim3((unsigned)blocks), dim3(64), 0, st, nv,
+        hipLaunchKernelGGL((k_raster_bwd_rp<TS, HV, DIST>), dim3((unsigned)raster_blocks(ts_sub(TS), ntiles)),
+                           dim3(64), 0, st, nv,
                            views, ntiles, ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc,
                            colC, colc, amb, A, V, T, last, dI, dD, dN, recgrad, cp, cmask, da);
         return;
@@ -1696,7 +1850,7 @@ hipError_t launch_raster_bwd(int ts, bool has_vis, int32_t total_tiles, int32_t 
     return hipGetLastError();
 }
 
-int raster_bwd_sub(int ts, bool masks) { return masks ? (ts / 8) * (ts / 8) : 1; }
+int raster_bwd_sub(int ts, bool masks) { return masks ? ts_sub(ts) : 1; }
 
 // ----------------------------------------------------------- projection backward
 // One thread per rank, looping over views: record gradients -> parameter gradients

@@ -207,6 +207,30 @@ def test_backward_of_larger_tiles_with_and_without_masks(ts, bound_at, n, mean_l
     check_backward(sc, plan, surf, views, out, ref, vis=vis)
 
 
+@pytest.mark.parametrize("ts,n", [(16, 6000), (32, 6000), (32, 700)])
+def test_blocks_of_a_tile_that_see_little_of_its_list(ts, n):
+    """All surfels in a few pixels: most 8x8 blocks of a tile stage nothing from a list of more
+    than 64 words, one stages nearly all of it.  Every pixel composites the same pairs in the
+    same order at every tile size, so the forward's results are equal to the bit."""
+    sc = scene_tiny(seed=16, views=((64, 64),), n=n)
+    s = sc["surfels"]
+    s["mean"][:, :2] = s["mean"][:, :2].mean(0) + 0.1 * (s["mean"][:, :2] - s["mean"][:, :2].mean(0))
+    s["opacity"] *= 0.05
+    t = lambda a: torch.as_tensor(a, device="cuda")
+    up = [t(x) for x in synth.upstream_grads(sc)]
+    res = {}
+    for size in (8, ts):
+        plan, surf, views = make_plan(sc, ts=size)
+        out = plan.forward(surf, views)
+        res[size] = out, plan.backward(surf, views, out, *up)
+    b = plan.debug_binning(0)["ranges"].astype(np.int64)
+    assert (b[:, 1] - b[:, 0]).max() > 0.7 * n
+    for k in ("image", "albedo", "depth", "normal", "T"):
+        assert torch.equal(res[ts][0][k], res[8][0][k]), k
+    for k in GRAD_KEYS:      # each within 1e-3 of the oracle by the bar of these tests
+        assert rel_err(to_np(res[ts][1][k]), to_np(res[8][1][k])) < 2e-3, k
+
+
 def test_backward_config1():
     sc = synth.make_scene(synth.config(1))
     plan, surf, views = make_plan(sc)
