@@ -637,8 +637,8 @@ __device__ __forceinline__ void stage_record(float4 *lds, int slot, float4 r0, f
 
 // eval_pair's arithmetic on a staged record.
 template <bool FILT>
-__device__ __forceinline__ PairEval eval_staged(const float4 c, const float4 q, float o, float fx, float fy,
-                                                const RasterConsts &rc)
+__device__ __forceinline__ PairEval eval_staged(const float4 c, const float4 q, float o, bool ell, float fx,
+                                                float fy, const RasterConsts &rc)
 {
     PairEval e;
     e.dx = __fsub_rn(__fsub_rn(fx, c.x), c.z);
@@ -647,7 +647,7 @@ __device__ __forceinline__ PairEval eval_staged(const float4 c, const float4 q, 
     e.u1 = __fmaf_rn(q.w, e.dy, __fmul_rn(q.z, e.dx));
     const float ru = __fmaf_rn(e.u0, e.u0, __fmul_rn(e.u1, e.u1));
     const float rf = __fmul_rn(__fmaf_rn(e.dx, e.dx, __fmul_rn(e.dy, e.dy)), rc.inv_s2);
-    e.ub = FILT ? ru <= rf : ru == ru;
+    e.ub = FILT ? ell && ru <= rf : ell;
     e.G = ex2(__fmul_rn(e.ub ? ru : rf, kNegHalfLog2e));
     e.oG = __fmul_rn(o, e.G);
     e.alpha = __builtin_amdgcn_fmed3f(e.oG, 0.f, rc.alpha_max);
@@ -670,7 +670,7 @@ __device__ __forceinline__ unsigned long long composite(const float4 *lds, uint6
         m &= m - 1;
         const float4 c = lds[jc], q = lds[BS + jc], r3 = lds[2 * BS + jc];
         ++p.neval;
-        const PairEval e = eval_staged<FILT>(c, q, r3.x, fx, fy, rc);
+        const PairEval e = eval_staged<FILT>(c, q, r3.x, FILT || q.x == q.x, fx, fy, rc);
         // branch-free: a skipped pair accumulates with weight 0 (w * x + a == a
         // exactly for the finite record fields), so no exec-mask juggling per pair
         const bool hit = e.alpha >= rc.alpha_min;
@@ -1502,9 +1502,13 @@ __global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(4))) voi
 // larger tile share a list of which each composites a part (a third of it at 16x16 on the
 // 0.5 m/px views), so there the records are staged densely, up to 64 from several words: the
 // last step of a quadrant's walk is rarely part-filled.
-// Bound by VALU issue (140 instructions a step, at the issue limit on the 2M-surfel views:
-// 18.8 ms for 40 views).  16x16 tiles, three ~530^2 views of 150k surfels: 244 us, against
-// 430 us for the box-test walk above; 8x8, one 2048^2 view of 1M surfels: 495 us.
+// Bound by VALU issue (140 instructions a step; the pipes are 92 % busy).  One 2048^2 view of
+// 1M surfels 495 -> 471 us, 40 views of 2M 18.6 -> 17.8 ms with 80-byte records in LDS (20
+// blocks of 8 KB fit a CU) and without the registers that held the next word's records (5 waves
+// per SIMD instead of 4).  With the distortion's state in LDS only 16 blocks fit, and with 16x16
+// tiles there are few blocks, so those keep the records ahead: 8 training views of 500k surfels
+// 1300 -> 1200 us, three ~530^2 views of 150k surfels at 16x16 234 us (273 us without;
+// 430 us for the box-test walk above).
 // A step of 16 records x 4 pixels, its scans along the lanes of a row and its sum over pixels
 // on the FP32 matrix cores, issues a quarter fewer VALU instructions but waits on LDS and the
 // matrix pipe at 4 waves per SIMD: 28.3 ms and 749 us.
@@ -1552,8 +1556,12 @@ __device__ __forceinline__ float rows_prefix_add(float x, bool odd, bool upper, 
     return upper ? p1 + c : p1;
 }
 
-template <int TS, bool HAS_VIS, bool DIST>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd_rp(
+// A staged record: centre, Q, (o, z0, k) with o negative where the record has no ellipse,
+// albedo with visibility, normal with the record's rank.
+constexpr int kBwdVec4 = 5;
+
+template <int TS, bool HAS_VIS, bool DIST, bool FILT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DIST || TS > 8 ? 4 : 5))) void k_raster_bwd_rp(
     int32_t nv, const ViewDesc *__restrict__ views, int32_t ntiles, const uint32_t *__restrict__ ranges,
     const uint32_t *__restrict__ lists, const float4 *__restrict__ rec, int64_t n,
     RasterConsts rc, const float *__restrict__ colC, const float *__restrict__ colc,
@@ -1565,16 +1573,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     DistArgs da)
 {
     constexpr int WPR = TS / 8, SUB = WPR * WPR, NT = TS * TS;
-    constexpr bool DENSE = TS > 8;
+    constexpr bool DENSE = TS > 8, AHEAD = DIST || DENSE;
     constexpr int kPst = kPstBase + (DIST ? kPstDist : 0);
-    // staged records (a record's address is one multiply), their ranks, the contributor words
-    // of the staged slots, per-pixel state [field][pixel], the quadrant's walk list, the
-    // block's largest `last`
-    __shared__ float4 lds[64 * kRecVec4];
-    __shared__ unsigned long long ownw[64];
+    // staged records (a record's address is one multiply), per-pixel state [field][pixel], the
+    // quadrant's walk list, the block's largest `last`
+    __shared__ float4 lds[64 * kBwdVec4];
     __shared__ float pst[kPst * 64];
-    __shared__ uint32_t lds_idx[64];
-    __shared__ uint32_t qlist[64];
+    __shared__ uint32_t qlist[68];
     __shared__ int max_last;
     // blocks go round-robin to the 8 XCDs: the SUB blocks of a tile stay on the tile's XCD
     const int b = (int)blockIdx.x;
@@ -1631,7 +1636,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     // Walks the staged records, highest slot first; `own` holds the slots that this lane's
     // pixel composited, row q of `un` their union over quadrant q.
     auto walk = [&](const uint64_t own, const uint64_t un) {
-        ownw[lane] = own;
         __syncthreads();
         for (int q = 0; q < 4; ++q) {
             const uint64_t U = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(un >> 32), 16 * q) << 32) |
@@ -1644,7 +1648,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 const int k = lane == 63 ? 0 : __popcll(U >> (lane + 1));
                 if (set) qlist[k] = (uint32_t)lane;
                 // rows past the end of the walk read a staged record too (their weight is zero)
-                if (lane >= nq) qlist[lane] = (uint32_t)__builtin_ctzll(U);
+                const uint32_t spare = (uint32_t)__builtin_ctzll(U);
+                if (lane >= nq) qlist[lane] = spare;
+                if (lane < 4) qlist[64 + lane] = spare;
             }
             const int p = 16 * q + li;               // the quadrant's pixel of this lane
             const float gA0 = pst[0 * 64 + p], gA1 = pst[1 * 64 + p], gA2 = pst[2 * 64 + p];
@@ -1656,21 +1662,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 dp.gDist = pst[10 * 64 + p]; dp.zref = pst[11 * 64 + p]; dp.At = pst[12 * 64 + p];
                 dp.M1 = pst[13 * 64 + p]; dp.M2 = pst[14 * 64 + p];
             }
-            const uint64_t ownq = ownw[p];
+            const uint64_t ownq =
+                ((uint64_t)(uint32_t)__builtin_amdgcn_ds_bpermute(4 * p, (int)(uint32_t)(own >> 32)) << 32) |
+                (uint32_t)__builtin_amdgcn_ds_bpermute(4 * p, (int)(uint32_t)own);
             const PixelAdjoint pa{gA0, gA1, gA2, gV, gD, gN0, gN1, gN2, Tr, 0};
             const int qpx = wx0 + 4 * (q & 1) + (li & 3), qpy = wy0 + 4 * (q >> 1) + (li >> 2);
             const float fx = (float)qpx + 0.5f, fy = (float)qpy + 0.5f;
             __syncthreads();                         // the walk list is complete
             // record slots are read one step ahead
-            int jl_next = (int)qlist[row];
-            for (int s0 = 0; s0 < nq; s0 += 4) {
-                const int k = s0 + row;
-                const bool act = k < nq;
+            const uint32_t *next = qlist + row;
+            int jl_next = (int)*next;
+            for (int left = nq; left > 0; left -= 4) {
+                const bool act = row < left;
                 const int jl = jl_next;
-                jl_next = (int)qlist[min(k + 4, 63)];
-                const float4 *R = lds + __mul24(jl, kRecVec4);
-                const float4 r0 = R[0], r1 = R[1], r2 = R[2], r3 = R[3], r4 = R[4], r5 = R[5];
-                const PairEval e = eval_pair(r0, r1, r2, r3, fx, fy, rc);
+                next += 4;
+                jl_next = (int)*next;
+                const float4 *R = lds + __mul24(jl, kBwdVec4);
+                const float4 c = R[0], r2 = R[1], r3 = R[2], r4 = R[3], r5 = R[4];
+                const PairEval e = eval_staged<FILT>(c, r2, fabsf(r3.x), r3.x > 0.f, fx, fy, rc);
                 const bool contrib = act && ((ownq >> jl) & 1ull);
                 const PairTerms t = pair_terms<DIST>(e, r3, r4, r5, pa, dp, HAS_VIS, da.ds);
                 const float f = contrib ? t.rom : 1.f;
@@ -1685,15 +1694,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 const float dal = contrib ? fmaf(Tb, t.gf, -gSb * t.rom) : 0.f;
                 Tr *= ptot;
                 gS += stot;
-                // every walked record is composited by some pixel of the quadrant, so each
-                // step has work; a row past the end of the list adds nothing
                 float gr[16];
                 pair_record_grads(e, w, dal, w * t.gDe, t.u0, t.u1, r2, r3, pa, inv_s2,
                                   rc.alpha_max, gr);
                 const float sum = row_transpose_reduce16(gr, lane);
-                const uint64_t cb = __ballot(contrib);
-                if (((cb >> (row * 16)) & 0xFFFFull) != 0)
-                    atomicAdd(gv + (size_t)lds_idx[jl] * kGradFloats + li, sum);
+                // every walked record is composited by some pixel of the quadrant
+                if (act) atomicAdd(gv + (size_t)__float_as_uint(r5.w) * kGradFloats + li, sum);
             }
             if (row == 0) {
                 pst[8 * 64 + p] = Tr;
@@ -1703,10 +1709,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         }
     };
 
-    // Words of the list, back to front.  Ahead of the word in work: the records of the next
-    // (q0..q5, of lanes whose position is in the block's union Un), masks and list entries of
-    // the one after.
-    float4 q0, q1, q2, q3, q4, q5;
+    // Words of the list, back to front.  Ahead of the word in work (AHEAD): the records of the
+    // next, of lanes whose position is in the block's union Un, and masks and list entries of the
+    // one after; otherwise the next word's masks and list entries only.
+    float2 qc;                                        // record on its way to LDS: centre,
+    float3 qb, qn;                                    // its low part and a bias; normal
+    float4 q2, q3, q4;
     uint32_t qidx = 0, nidx = 0;
     uint64_t own_n = 0, un_n = 0, Un = 0, own_nn = 0;
     int kb = (blk_last + 63) >> 6;
@@ -1727,23 +1735,35 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         qidx = min(nidx, (uint32_t)(n - 1));
         if ((Un >> lane) & 1ull) {
             const float4 *src = recv + (size_t)qidx * kRecStride4;
-            q0 = src[0]; q1 = src[1]; q2 = src[2]; q3 = src[3]; q4 = src[4]; q5 = src[5];
+            const float *f = reinterpret_cast<const float *>(src);
+            qc = *reinterpret_cast<const float2 *>(f + 2);
+            qb = *reinterpret_cast<const float3 *>(f + 4);
+            q2 = src[2]; q3 = src[3]; q4 = src[4];
+            qn = *reinterpret_cast<const float3 *>(f + 20);
         }
     };
     auto stage = [&](int slot) {
-        float4 *dst = lds + slot * kRecVec4;
-        dst[0] = q0; dst[1] = q1; dst[2] = q2; dst[3] = q3; dst[4] = q4; dst[5] = q5;
-        lds_idx[slot] = qidx;
+        float4 *dst = lds + slot * kBwdVec4;
+        dst[0] = make_float4(qc.x, qc.y, qb.x, qb.y);
+        dst[1] = q2; dst[3] = q4;
+        dst[2] = make_float4(qb.z > 0.f ? -q3.x : q3.x, q3.y, q3.z, q3.w);
+        dst[4] = make_float4(qn.x, qn.y, qn.z, __uint_as_float(qidx));
     };
     load_word(kb - 1);
-    fetch_word();
-    if (kb > 1) load_word(kb - 2);
+    if (AHEAD) {
+        fetch_word();
+        if (kb > 1) load_word(kb - 2);
+    }
     if constexpr (!DENSE) {
         while (--kb >= 0) {
+            if (!AHEAD) {
+                fetch_word();
+                if (kb > 0) load_word(kb - 1);
+            }
             if ((Un >> lane) & 1ull) stage(lane);
             const uint64_t own = own_n, un = un_n;
-            if (kb > 0) fetch_word();
-            if (kb > 1) load_word(kb - 2);
+            if (AHEAD && kb > 0) fetch_word();
+            if (AHEAD && kb > 1) load_word(kb - 2);
             walk(own, un);
         }
     } else {
@@ -1790,10 +1810,14 @@ static void launch_bwd_d(size_t lds, hipStream_t st, int32_t ntiles, int32_t nv,
                          float *cp, const unsigned long long *cmask, const DistArgs &da)
 {
     if (cmask) {
-        hipLaunchKernelGGL((k_raster_bwd_rp<TS, HV, DIST>), dim3((unsigned)raster_blocks(ts_sub(TS), ntiles)),
-                           dim3(64), 0, st, nv,
-                           views, ntiles, ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc,
-                           colC, colc, amb, A, V, T, last, dI, dD, dN, recgrad, cp, cmask, da);
+        const dim3 grid((unsigned)raster_blocks(ts_sub(TS), ntiles));
+#define SS_BWD_LAUNCH(FILT_)                                                                         \
+    hipLaunchKernelGGL((k_raster_bwd_rp<TS, HV, DIST, FILT_>), grid, dim3(64), 0, st, nv, views,     \
+                       ntiles, ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc, colC,    \
+                       colc, amb, A, V, T, last, dI, dD, dN, recgrad, cp, cmask, da)
+        if (rc.lowpass_mode == 0) SS_BWD_LAUNCH(true);
+        else SS_BWD_LAUNCH(false);
+#undef SS_BWD_LAUNCH
         return;
     }
     if constexpr (TS != 8)     // 8x8 tiles always have their masks
