@@ -104,7 +104,30 @@ __device__ __forceinline__ void adam_one(float &theta, float &m, float &v, float
     theta -= lr * mh / (sqrtf(vh) + a.eps);
 }
 
-// activation adjoint + Adam + re-activation, one thread per surfel
+// A block's surfels' columns c .. c + C - 1 between LDS rows of `kActRow` floats and an
+// [n, C] array, coalesced.
+constexpr int kActRow = 15;      // mean 3, t_u 3, t_v 3, scale 2, opacity, albedo 3
+
+template <int C>
+__device__ __forceinline__ void cols_in(float *rows, const float *__restrict__ src, int64_t i0, int cnt, int c)
+{
+    for (int e = threadIdx.x; e < cnt * C; e += kTrainThreads)
+        rows[(e / C) * kActRow + c + e % C] = src[C * i0 + e];
+}
+
+template <int C>
+__device__ __forceinline__ void cols_out(const float *rows, float *__restrict__ dst, int64_t i0, int cnt, int c)
+{
+    for (int e = threadIdx.x; e < cnt * C; e += kTrainThreads)
+        dst[C * i0 + e] = rows[(e / C) * kActRow + c + e % C];
+}
+
+// Activation adjoint + Adam + re-activation, 256 surfels per block.  Bound by HBM (436 bytes
+// per surfel).  Every array passes through LDS, so that memory sees contiguous runs: raw
+// parameters and activated gradients in, a thread per surfel for the adjoint, a thread per
+// parameter for the moments and the step (they are never grouped by surfel), a thread per
+// surfel for the activation, activated arrays out.  With a thread per surfel throughout, a
+// load's 64 lanes lay 52 or 12 bytes apart: 500k surfels 129 us, now 63 us (3.5 TB/s).
 __global__ __launch_bounds__(kTrainThreads) void k_adam_surfels(
     int64_t n, float *__restrict__ raw, float *__restrict__ m, float *__restrict__ v,
     const float *__restrict__ g_mean, const float *__restrict__ g_tu,
@@ -114,24 +137,35 @@ __global__ __launch_bounds__(kTrainThreads) void k_adam_surfels(
     float *__restrict__ tv, float *__restrict__ scale, float *__restrict__ opacity,
     float *__restrict__ albedo)
 {
-    const int64_t i = (int64_t)blockIdx.x * kTrainThreads + threadIdx.x;
-    if (i >= n) return;
-    float r[kRaw], g[kRaw];
-    for (int k = 0; k < kRaw; ++k) r[k] = raw[kRaw * i + k];
-    for (int k = 0; k < 3; ++k) {
-        g[k] = g_mean[3 * i + k];
-        g[10 + k] = g_albedo[3 * i + k];
-    }
-    g[3] = g_scale[2 * i] * expf(r[3]);
-    g[4] = g_scale[2 * i + 1] * expf(r[4]);
-    const float o = 1.f / (1.f + expf(-r[5]));
-    g[5] = g_opacity[i] * o * (1.f - o);
-    {
+    __shared__ float sraw[kTrainThreads * kRaw], act[kTrainThreads * kActRow];
+    float *const sg = act;                       // raw gradients, kRaw per surfel, over the activated ones
+    const int64_t i0 = (int64_t)blockIdx.x * kTrainThreads;
+    const int cnt = (int)min((int64_t)kTrainThreads, n - i0);
+    const int t = threadIdx.x;
+    for (int e = t; e < cnt * kRaw; e += kTrainThreads) sraw[e] = raw[kRaw * i0 + e];
+    cols_in<3>(act, g_mean, i0, cnt, 0);
+    cols_in<3>(act, g_tu, i0, cnt, 3);
+    cols_in<3>(act, g_tv, i0, cnt, 6);
+    cols_in<2>(act, g_scale, i0, cnt, 9);
+    cols_in<1>(act, g_opacity, i0, cnt, 11);
+    cols_in<3>(act, g_albedo, i0, cnt, 12);
+    __syncthreads();
+    float g[kRaw];
+    if (t < cnt) {
+        const float *r = sraw + t * kRaw, *ga = act + t * kActRow;
+        for (int k = 0; k < 3; ++k) {
+            g[k] = ga[k];
+            g[10 + k] = ga[12 + k];
+        }
+        g[3] = ga[9] * expf(r[3]);
+        g[4] = ga[10] * expf(r[4]);
+        const float o = 1.f / (1.f + expf(-r[5]));
+        g[5] = ga[11] * o * (1.f - o);
         // d(t_u, t_v)/d(q / |q|), then the projection of the normalisation
         const float nq = sqrtf(r[6] * r[6] + r[7] * r[7] + r[8] * r[8] + r[9] * r[9]);
         const float w = r[6] / nq, x = r[7] / nq, y = r[8] / nq, z = r[9] / nq;
-        const float gu0 = g_tu[3 * i], gu1 = g_tu[3 * i + 1], gu2 = g_tu[3 * i + 2];
-        const float gv0 = g_tv[3 * i], gv1 = g_tv[3 * i + 1], gv2 = g_tv[3 * i + 2];
+        const float gu0 = ga[3], gu1 = ga[4], gu2 = ga[5];
+        const float gv0 = ga[6], gv1 = ga[7], gv2 = ga[8];
         float gq[4];
         gq[0] = 2.f * (z * gu1 - y * gu2) + 2.f * (-z * gv0 + x * gv2);
         gq[1] = 2.f * (y * gu1 + z * gu2) + (2.f * y * gv0 - 4.f * x * gv1 + 2.f * w * gv2);
@@ -143,15 +177,35 @@ __global__ __launch_bounds__(kTrainThreads) void k_adam_surfels(
         g[8] = (gq[2] - y * pr) / nq;
         g[9] = (gq[3] - z * pr) / nq;
     }
-    for (int k = 0; k < kRaw; ++k) {
+    __syncthreads();
+    if (t < cnt)
+        for (int k = 0; k < kRaw; ++k) sg[t * kRaw + k] = g[k];
+    __syncthreads();
+#pragma unroll 4
+    for (int e = t; e < cnt * kRaw; e += kTrainThreads) {
+        const int k = e % kRaw;
         const float lr = k < 3 ? a.lr[0] : k < 5 ? a.lr[1] : k < 6 ? a.lr[2] : k < 10 ? a.lr[3] : a.lr[4];
-        float mm = m[kRaw * i + k], vv = v[kRaw * i + k];
-        adam_one(r[k], mm, vv, g[k], lr, a, bc1, bc2);
-        m[kRaw * i + k] = mm;
-        v[kRaw * i + k] = vv;
-        raw[kRaw * i + k] = r[k];
+        float r = sraw[e], mm = m[kRaw * i0 + e], vv = v[kRaw * i0 + e];
+        adam_one(r, mm, vv, sg[e], lr, a, bc1, bc2);
+        m[kRaw * i0 + e] = mm;
+        v[kRaw * i0 + e] = vv;
+        raw[kRaw * i0 + e] = r;
+        sraw[e] = r;
     }
-    write_activated(i, r, mean, tu, tv, scale, opacity, albedo);
+    __syncthreads();
+    if (t < cnt) {
+        float r[kRaw];
+        for (int k = 0; k < kRaw; ++k) r[k] = sraw[t * kRaw + k];
+        float *o = act + t * kActRow;
+        write_activated(0, r, o, o + 3, o + 6, o + 9, o + 11, o + 12);
+    }
+    __syncthreads();
+    cols_out<3>(act, mean, i0, cnt, 0);
+    cols_out<3>(act, tu, i0, cnt, 3);
+    cols_out<3>(act, tv, i0, cnt, 6);
+    cols_out<2>(act, scale, i0, cnt, 9);
+    cols_out<1>(act, opacity, i0, cnt, 11);
+    cols_out<3>(act, albedo, i0, cnt, 12);
 }
 
 // per-view camera delta (8 floats, from camera_start on) and colour gain / bias (9 + 3)

@@ -115,6 +115,28 @@ def test_adam_views_camera_start_and_colour():
                                rtol=1e-5, atol=1e-6)
 
 
+@pytest.mark.parametrize("cut", [1, 255, 256, 257])
+def test_adam_of_the_first_surfels_alone(cut):
+    """The update is per surfel: over a prefix (one, a block less one, a block, a block and one)
+    it gives the prefix of the whole update, to the bit."""
+    n, t = 600, 2
+    rng = np.random.default_rng(11)
+    raw = random_raw(n, 4)
+    mom = [(rng.standard_normal((n, 13)) * 0.1).astype(np.float32),
+           (rng.uniform(size=(n, 13)) * 0.01).astype(np.float32)]
+    g = {k: rng.standard_normal(sh).astype(np.float32) for k, sh in
+         (("mean", (n, 3)), ("t_u", (n, 3)), ("t_v", (n, 3)), ("scale", (n, 2)), ("opacity", (n,)),
+          ("albedo", (n, 3)))}
+    res = []
+    for k in (n, cut):
+        ts = [cuda(x[:k].copy()) for x in (raw, *mom)]
+        s = empty_surfels(k)
+        tr.adam_surfels(*ts, {key: cuda(x[:k].copy()) for key, x in g.items()}, tr.adam_config(), t, s)
+        res.append([to_np(x)[:cut] for x in (*ts, s.mean, s.t_u, s.t_v, s.scale, s.opacity, s.albedo)])
+    for whole, part in zip(*res):
+        np.testing.assert_array_equal(whole, part)
+
+
 def test_l1_loss_matches_oracle():
     sc = synth.make_scene(synth.tiny(n_surfels=50, views=((31, 17), (12, 29)), seed=3))
     plan, surf, views = make_plan(sc)
