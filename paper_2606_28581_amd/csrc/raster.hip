@@ -121,13 +121,20 @@ __device__ __forceinline__ SurfelAffine surfel_affine(const double (&B)[2][3], c
 }
 
 // ------------------------------------------------------------------- projection
-// One thread per (rank r, view v).  Geometry in FP64 (the binning contract: tile
+// One thread per rank r and VPT views.  Geometry in FP64 (the binning contract: tile
 // ranges must be bit-identical to an FP64 reference), records rounded to FP32.
 //   T = B'_xy [s_u t_u, s_v t_v]   c = B'_xy p + b'_xy   Q = T^-1   (Eq. affine2dgs_Qq)
 //   degenerate iff |det T| <= eps |T|_F^2 ("Degenerate Solutions")
 //   support: alpha >= alpha_min needs rho <= 2 ln(o / alpha_min); the uv-ellipse
 //   {T w : |w|^2 <= rho_max} has x half-extent r |T row 0|, the low-pass disk radius
 //   sigma r; pixel i is in the box iff i + 0.5 lies within the half-extent of c.
+// Bound by its writes (128 + 8 bytes per view record, 64 + 8 per sun record) once the FP64
+// work that all views of a surfel share - the logarithm of r, the normal's root and division,
+// products of the frame - is done for four of them at a time: 2M surfels x (40 views + 40
+// suns) 3.88 -> 3.39 ms (4.9 TB/s), x (8 + 8) of 500k 220 -> 177 us, 20 suns of 1M 465 -> 405 us.
+// Eight views at a time: 3.49 ms and 181 us.  View records at their 96 bytes instead of 128-byte
+// slots: 2.85 ms, which the raster kernels' gathers, then over two lines, give back.
+template <int VPT>
 __global__ __launch_bounds__(256) void k_project(
     const float4 *__restrict__ sp, int64_t n, int32_t nv,
     const ViewDesc *__restrict__ views, const float *__restrict__ Fxy,
@@ -141,134 +148,146 @@ __global__ __launch_bounds__(256) void k_project(
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nranges;
          i += (int64_t)gridDim.x * blockDim.x)
         ranges[i] = make_uint2(0xFFFFFFFFu, 0u);
-    // the block's 256 records are staged in LDS and written back as one contiguous run.
-    // Blocks run view-innermost (block = rank block x views + view), in xcd_tile's chunked
-    // order, so the views of one rank block share the surfel parameters in one L2.
+    // The block's 256 records are staged in LDS and written back as one contiguous run per view.
+    // Blocks run view-innermost (block = rank block x groups of VPT views + group), in
+    // xcd_tile's chunked order, so the views of one rank block share the surfel parameters in
+    // one L2.
     __shared__ float4 srec[256 * kRecVec4];
+    __shared__ unsigned long long wsum[kRankBlock / 64];
     const int64_t L = xcd_tile((int)blockIdx.x, (int)gridDim.x);
-    const int v = (int)(L % nv);
-    const int64_t r0 = (L / nv) * blockDim.x;
+    const int groups = (nv + VPT - 1) / VPT;
+    const int64_t rb = L / groups, r0 = rb * blockDim.x;
+    const int v0 = (int)(L - rb * groups) * VPT;
     const bool valid = r0 + threadIdx.x < n;
     const int64_t r = valid ? r0 + threadIdx.x : n - 1;   // lanes past the end repeat the last
-    const ViewDesc vd = views[v];
-    double B[2][3], b[2];
-    if (sun) {
-        for (int q = 0; q < 3; ++q) { B[0][q] = sun[v].B[q]; B[1][q] = sun[v].B[3 + q]; }
-        b[0] = sun[v].b[0]; b[1] = sun[v].b[1];
-    } else {
-        for (int row = 0; row < 2; ++row) {
-            for (int q = 0; q < 3; ++q)
-                B[row][q] = (double)Fxy[8 * v + 4 * row + q] +
-                            (dF ? (double)dF[8 * v + 4 * row + q] : 0.0);
-            b[row] = (double)Fxy[8 * v + 4 * row + 3] + (dF ? (double)dF[8 * v + 4 * row + 3] : 0.0);
-        }
-    }
     const float4 pa = sp[4 * r], pb = sp[4 * r + 1], pc = sp[4 * r + 2], pd = sp[4 * r + 3];
     const double p[3] = {pa.x, pa.y, pa.z};
     const double tu[3] = {pa.w, pb.x, pb.y};
     const double tv[3] = {pb.z, pb.w, pc.x};
     const double su = pc.y, sv = pc.z, o = pc.w;
-    const SurfelAffine sa = surfel_affine(B, tu, tv, su, sv, rc.det_rel_eps_d);
-    const double(&M)[3][2] = sa.M;
-    const double(&T)[2][2] = sa.T;
-    const double(&Q)[2][2] = sa.Q;
-    const double(&m)[3] = sa.m;
-    const bool deg = sa.deg;
-    const double nsign = sa.nsign;
-    double c[2];
-    for (int row = 0; row < 2; ++row) {
-        double acc = b[row];
-        for (int i = 0; i < 3; ++i) acc += B[row][i] * p[i];
-        c[row] = acc;
+    // the same for every view: the support radius and the normal up to its sign
+    const double rr = o >= rc.alpha_min_d ? sqrt(2.0 * log(o / rc.alpha_min_d)) : 0.0;
+    float nrm[3];
+    {
+        const double m[3] = {tu[1] * tv[2] - tu[2] * tv[1], tu[2] * tv[0] - tu[0] * tv[2],
+                             tu[0] * tv[1] - tu[1] * tv[0]};
+        const double s = 1.0 / sqrt(m[0] * m[0] + m[1] * m[1] + m[2] * m[2]);
+        for (int k = 0; k < 3; ++k) nrm[k] = (float)(s * m[k]);
     }
-    const bool filt = (rc.lowpass_mode == 0) || deg;
-    const double mn = sqrt(m[0] * m[0] + m[1] * m[1] + m[2] * m[2]);
-    // support box -> pixel and tile ranges
-    int ilo = 0, ihi = -1, jlo = 0, jhi = -1;
-    if (o >= rc.alpha_min_d) {
-        const double rr = sqrt(2.0 * log(o / rc.alpha_min_d));
-        double hx = 0.0, hy = 0.0;
-        if (!deg) {
-            hx = rr * sqrt(T[0][0] * T[0][0] + T[0][1] * T[0][1]);
-            hy = rr * sqrt(T[1][0] * T[1][0] + T[1][1] * T[1][1]);
-        }
-        if (filt) {
-            const double f = rc.sigma_d * rr;
-            if (f > hx) hx = f;
-            if (f > hy) hy = f;
-        }
-        double xl = ceil(c[0] - hx - 0.5), xh = floor(c[0] + hx - 0.5);
-        double yl = ceil(c[1] - hy - 0.5), yh = floor(c[1] + hy - 0.5);
-        if (isfinite(xl) && isfinite(xh) && isfinite(yl) && isfinite(yh)) {
-            if (xl < 0) xl = 0;
-            if (yl < 0) yl = 0;
-            if (xh > vd.W - 1) xh = vd.W - 1;
-            if (yh > vd.H - 1) yh = vd.H - 1;
-            if (xl <= xh && yl <= yh) {
-                ilo = (int)xl; ihi = (int)xh; jlo = (int)yl; jhi = (int)yh;
+#pragma unroll 1
+    for (int v = v0; v < min(v0 + VPT, nv); ++v) {
+        if (VPT > 1 && v > v0) __syncthreads();           // the last view's records are out
+        const ViewDesc vd = views[v];
+        double B[2][3], b[2];
+        if (sun) {
+            for (int q = 0; q < 3; ++q) { B[0][q] = sun[v].B[q]; B[1][q] = sun[v].B[3 + q]; }
+            b[0] = sun[v].b[0]; b[1] = sun[v].b[1];
+        } else {
+            for (int row = 0; row < 2; ++row) {
+                for (int q = 0; q < 3; ++q)
+                    B[row][q] = (double)Fxy[8 * v + 4 * row + q] +
+                                (dF ? (double)dF[8 * v + 4 * row + q] : 0.0);
+                b[row] = (double)Fxy[8 * v + 4 * row + 3] + (dF ? (double)dF[8 * v + 4 * row + 3] : 0.0);
             }
         }
-    }
-    const int64_t slot = (int64_t)v * n + r;
-    short4 tl;
-    uint32_t cnt = 0;
-    if (ilo <= ihi) {
-        tl.x = (short)(ilo / ts); tl.y = (short)(ihi / ts);
-        tl.z = (short)(jlo / ts); tl.w = (short)(jhi / ts);
-        if (tmask) {
-            for (int ty = tl.z; ty <= tl.w; ++ty)
-                for (int tx = tl.x; tx <= tl.y; ++tx)
-                    cnt += tmask[vd.tile_off + ty * vd.tiles_x + tx] != 0u;
-        } else {
-            cnt = (uint32_t)(tl.y - tl.x + 1) * (uint32_t)(tl.w - tl.z + 1);
+        const SurfelAffine sa = surfel_affine(B, tu, tv, su, sv, rc.det_rel_eps_d);
+        const double(&M)[3][2] = sa.M;
+        const double(&T)[2][2] = sa.T;
+        const double(&Q)[2][2] = sa.Q;
+        const bool deg = sa.deg;
+        const double nsign = sa.nsign;
+        double c[2];
+        for (int row = 0; row < 2; ++row) {
+            double acc = b[row];
+            for (int i = 0; i < 3; ++i) acc += B[row][i] * p[i];
+            c[row] = acc;
         }
-    } else {
-        tl.x = 0; tl.y = -1; tl.z = 0; tl.w = -1;
-    }
-    if (valid) {
-        tiles[slot] = tl;
-        if (tmask) counts[slot] = cnt;
-    } else {
-        cnt = 0;
-    }
-    // the block's pair count, clamped
-    __shared__ unsigned long long wsum[kRankBlock / 64];
-    {
-        unsigned long long x = cnt;
-        for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
-        if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = x;
-    }
-    // record
-    const float chx = (float)c[0], chy = (float)c[1];
-    const uint32_t boxx = ((uint32_t)(uint16_t)ilo) | ((uint32_t)(uint16_t)ihi << 16);
-    const uint32_t boxy = ((uint32_t)(uint16_t)jlo) | ((uint32_t)(uint16_t)jhi << 16);
-    const float inf = __builtin_inff();
-    float4 *R = srec + kRecVec4 * threadIdx.x;
-    R[0] = make_float4(__uint_as_float(boxx), __uint_as_float(boxy), chx, chy);
-    R[1] = make_float4((float)(c[0] - (double)chx), (float)(c[1] - (double)chy),
-                       deg ? inf : 0.f, filt ? 0.f : inf);
-    R[2] = make_float4((float)Q[0][0], (float)Q[0][1], (float)Q[1][0], (float)Q[1][1]);
-    R[3] = make_float4((float)o, (float)((double)bz - p[2]), (float)M[2][0], (float)M[2][1]);
-    const float vv = vis_rank ? vis_rank[r * nv + v] : 1.f;
-    R[4] = make_float4(pd.x, pd.y, pd.z, vv);
-    const double s = nsign / mn;
-    R[5] = make_float4((float)(s * m[0]), (float)(s * m[1]), (float)(s * m[2]), (float)nsign);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned long long x = wsum[0] + wsum[1] + wsum[2] + wsum[3];
-        sums[(int64_t)v * rank_blocks(n) + L / nv] = (uint32_t)min(x, 0xFFFFFFFFull);
-    }
-    const int64_t nrec = min((int64_t)blockDim.x, n - r0);
-    // whole slots, so every written line is written in full
-    if (sun) {
-        float4 *dst = rec + ((size_t)v * (size_t)n + (size_t)r0) * kSunRecStride4;
-        for (int i = threadIdx.x; i < nrec * kSunRecStride4; i += blockDim.x)
-            dst[i] = srec[(i >> 2) * kRecVec4 + (i & 3)];
-    } else {
-        float4 *dst = rec + ((size_t)v * (size_t)n + (size_t)r0) * kRecStride4;
-        for (int i = threadIdx.x; i < nrec * kRecStride4; i += blockDim.x) {
-            const int k = i & 7;
-            dst[i] = k < kRecVec4 ? srec[(i >> 3) * kRecVec4 + k] : make_float4(0.f, 0.f, 0.f, 0.f);
+        const bool filt = (rc.lowpass_mode == 0) || deg;
+        // support box -> pixel and tile ranges
+        int ilo = 0, ihi = -1, jlo = 0, jhi = -1;
+        if (o >= rc.alpha_min_d) {
+            double hx = 0.0, hy = 0.0;
+            if (!deg) {
+                hx = rr * sqrt(T[0][0] * T[0][0] + T[0][1] * T[0][1]);
+                hy = rr * sqrt(T[1][0] * T[1][0] + T[1][1] * T[1][1]);
+            }
+            if (filt) {
+                const double f = rc.sigma_d * rr;
+                if (f > hx) hx = f;
+                if (f > hy) hy = f;
+            }
+            double xl = ceil(c[0] - hx - 0.5), xh = floor(c[0] + hx - 0.5);
+            double yl = ceil(c[1] - hy - 0.5), yh = floor(c[1] + hy - 0.5);
+            if (isfinite(xl) && isfinite(xh) && isfinite(yl) && isfinite(yh)) {
+                if (xl < 0) xl = 0;
+                if (yl < 0) yl = 0;
+                if (xh > vd.W - 1) xh = vd.W - 1;
+                if (yh > vd.H - 1) yh = vd.H - 1;
+                if (xl <= xh && yl <= yh) {
+                    ilo = (int)xl; ihi = (int)xh; jlo = (int)yl; jhi = (int)yh;
+                }
+            }
+        }
+        const int64_t slot = (int64_t)v * n + r;
+        short4 tl;
+        uint32_t cnt = 0;
+        if (ilo <= ihi) {
+            tl.x = (short)(ilo / ts); tl.y = (short)(ihi / ts);
+            tl.z = (short)(jlo / ts); tl.w = (short)(jhi / ts);
+            if (tmask) {
+                for (int ty = tl.z; ty <= tl.w; ++ty)
+                    for (int tx = tl.x; tx <= tl.y; ++tx)
+                        cnt += tmask[vd.tile_off + ty * vd.tiles_x + tx] != 0u;
+            } else {
+                cnt = (uint32_t)(tl.y - tl.x + 1) * (uint32_t)(tl.w - tl.z + 1);
+            }
+        } else {
+            tl.x = 0; tl.y = -1; tl.z = 0; tl.w = -1;
+        }
+        if (valid) {
+            tiles[slot] = tl;
+            if (tmask) counts[slot] = cnt;
+        } else {
+            cnt = 0;
+        }
+        // the block's pair count, clamped
+        {
+            unsigned long long x = cnt;
+            for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
+            if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = x;
+        }
+        // record
+        const float chx = (float)c[0], chy = (float)c[1];
+        const uint32_t boxx = ((uint32_t)(uint16_t)ilo) | ((uint32_t)(uint16_t)ihi << 16);
+        const uint32_t boxy = ((uint32_t)(uint16_t)jlo) | ((uint32_t)(uint16_t)jhi << 16);
+        const float inf = __builtin_inff();
+        float4 *R = srec + kRecVec4 * threadIdx.x;
+        R[0] = make_float4(__uint_as_float(boxx), __uint_as_float(boxy), chx, chy);
+        R[1] = make_float4((float)(c[0] - (double)chx), (float)(c[1] - (double)chy),
+                           deg ? inf : 0.f, filt ? 0.f : inf);
+        R[2] = make_float4((float)Q[0][0], (float)Q[0][1], (float)Q[1][0], (float)Q[1][1]);
+        R[3] = make_float4((float)o, (float)((double)bz - p[2]), (float)M[2][0], (float)M[2][1]);
+        const float vv = vis_rank ? vis_rank[r * nv + v] : 1.f;
+        R[4] = make_float4(pd.x, pd.y, pd.z, vv);
+        const float sg = (float)nsign;                    // +-1: the products are exact
+        R[5] = make_float4(sg * nrm[0], sg * nrm[1], sg * nrm[2], sg);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const unsigned long long x = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+            sums[(int64_t)v * rank_blocks(n) + rb] = (uint32_t)min(x, 0xFFFFFFFFull);
+        }
+        const int64_t nrec = min((int64_t)blockDim.x, n - r0);
+        // whole slots, so every written line is written in full
+        if (sun) {
+            float4 *dst = rec + ((size_t)v * (size_t)n + (size_t)r0) * kSunRecStride4;
+            for (int i = threadIdx.x; i < nrec * kSunRecStride4; i += blockDim.x)
+                dst[i] = srec[(i >> 2) * kRecVec4 + (i & 3)];
+        } else {
+            float4 *dst = rec + ((size_t)v * (size_t)n + (size_t)r0) * kRecStride4;
+            for (int i = threadIdx.x; i < nrec * kRecStride4; i += blockDim.x) {
+                const int k = i & 7;
+                dst[i] = k < kRecVec4 ? srec[(i >> 3) * kRecVec4 + k] : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
         }
     }
 }
@@ -283,10 +302,16 @@ hipError_t launch_project(const float *sorted, int64_t n, int32_t nv, const View
         return ranges ? fill_u32(ranges, 0u, 2 * nranges, st) : hipSuccess;
     const int64_t blocks = rank_blocks(n) * nv;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_project, dim3((unsigned)blocks), dim3(kRankBlock), 0, st,
-                       reinterpret_cast<const float4 *>(sorted), n, nv, views, Fxy, dF, sun,
-                       vis_rank, bz, ts, rc, reinterpret_cast<float4 *>(rec), tiles, counts, sums,
-                       tmask, reinterpret_cast<uint2 *>(ranges), ranges ? nranges : 0);
+#define SS_PROJECT(VPT_, BLOCKS_)                                                                      \
+    hipLaunchKernelGGL((k_project<VPT_>), dim3((unsigned)(BLOCKS_)), dim3(kRankBlock), 0, st,          \
+                       reinterpret_cast<const float4 *>(sorted), n, nv, views, Fxy, dF, sun, vis_rank, \
+                       bz, ts, rc, reinterpret_cast<float4 *>(rec), tiles, counts, sums, tmask,        \
+                       reinterpret_cast<uint2 *>(ranges), ranges ? nranges : 0)
+    // four views a block once that still leaves 8 blocks for every CU
+    const int64_t grouped = rank_blocks(n) * ((nv + 3) / 4);
+    if (nv >= 4 && grouped >= 2048) SS_PROJECT(4, grouped);
+    else SS_PROJECT(1, blocks);
+#undef SS_PROJECT
     return hipGetLastError();
 }
 

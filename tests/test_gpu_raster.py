@@ -80,6 +80,24 @@ def test_binning_bit_exact_with_32_bit_tile_keys():
     assert min(pairs) > 0
 
 
+@pytest.mark.parametrize("n,nv", [(70_100, 30), (131_073, 13)])
+def test_projection_of_several_views_a_block_equals_one_view_a_block(n, nv):
+    """Many views of many surfels are projected four a block (the last group part-filled);
+    a plan of some of the same views, one a block, must get the same records and tile ranges."""
+    sc = scene_tiny(seed=17, n=n, views=tuple((9 + v % 3, 8 + v % 4) for v in range(nv)))
+    plan, surf, views = make_plan(sc)
+    plan.forward(surf, views)
+    whole = plan.debug_binning(0, records=True)
+    keys = ("width", "height", "Fxy", "dF", "colC", "colc", "ambient", "sun")
+    for part in (slice(0, 2), slice(nv - 1, nv)):
+        few = dict(sc, **{k: sc[k][part] for k in keys})
+        plan, surf, views = make_plan(few)
+        plan.forward(surf, views)
+        b = plan.debug_binning(0, records=True)
+        for k in ("tiles", "records"):
+            np.testing.assert_array_equal(b[k], whole[k][part], k)
+
+
 def test_records_centre_matches_fp64():
     sc = scene_tiny(seed=5)
     plan, surf, views = make_plan(sc)
