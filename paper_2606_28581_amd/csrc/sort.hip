@@ -3,14 +3,12 @@
 // depth, organise into tiles).
 //
 // Radix sort: 8-bit digits, 256 threads x 16 items = 4096 items per block.
-//   hist    : per-block digit histogram in LDS (one add per group of lanes holding the
-//             same digit) -> hist[digit * nblocks + block], or per segment (below)
+//   hist    : per-block digit histogram in LDS -> hist[digit * nblocks + block], or per
+//             segment (below)
 //   scan    : exclusive scan of hist (digit-major) -> global base of (digit, block)
-//   scatter : per-wave stable multisplit with 8 ballots per item (lanes holding the
-//             same digit form a mask; rank = popcount of lower lanes in the mask); the
-//             group's lowest lane adds the group size to the wave's running count of
-//             that digit in LDS and hands the old count to the group, then a prefix
-//             over the 4 waves places each digit's run inside the block.
+//   scatter : per-wave stable multisplit through a table of lane masks and counts in LDS
+//             (rank_rows), then a prefix over the 4 waves places each digit's run inside the
+//             block.
 // Tile bucketing sorts within segments (one per view) on key minus the segment's base,
 // so the number of passes follows the largest view's tile count; its last pass also
 // writes each tile's [begin, end) range.
@@ -282,19 +280,6 @@ __device__ __forceinline__ BlockRange block_range(const SegDesc *segs, int nseg,
     return r;
 }
 
-// Lanes of the wave whose `valid` item has the same digit as this lane (over the low
-// `nbits` bits of d).
-__device__ __forceinline__ uint64_t digit_peers(uint32_t d, bool valid, int nbits)
-{
-    uint64_t m = __ballot(valid);
-    for (int b = 0; b < nbits; ++b) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t bb = __ballot(bit);
-        m &= bit ? bb : ~bb;
-    }
-    return m;
-}
-
 // One block: segment table from view-major pair offsets.  Segment v holds the items
 // [offs[v * stride], offs[(v + 1) * stride]) clamped to the live count; its keys are
 // based at views[v].tile_off.
@@ -350,6 +335,17 @@ __device__ __forceinline__ uint32_t key_digit(KT key, uint32_t base, int shift)
     return (((uint32_t)key - (kLocal ? 0u : base)) >> shift) & 255u;
 }
 
+// Runs of 16 consecutive tiles on one XCD (blocks go round-robin to the 8): a digit's runs of
+// neighbouring tiles meet in one L2, which then writes whole lines (those scatters 2.98 -> 2.61
+// ms, the histograms 0.71 -> 0.67; runs of 32: 2.64 ms).
+__device__ __forceinline__ int sort_block(int b, int nblocks)
+{
+    constexpr int kRun = 16;
+    if (b >= nblocks - nblocks % (8 * kRun)) return b;
+    const int x = b % 8, i = b / 8;
+    return ((i / kRun) * 8 + x) * kRun + i % kRun;
+}
+
 template <typename KT>
 __global__ __launch_bounds__(kSortThreads) void k_radix_hist(
     const KT *keys, const SegDesc *segs, int nseg, const unsigned long long *n_dev,
@@ -358,7 +354,7 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(
     __shared__ uint32_t h[256];
     h[threadIdx.x] = 0;
     __syncthreads();
-    const BlockRange br = block_range(segs, nseg, n_dev, cap, n_host, blockIdx.x);
+    const BlockRange br = block_range(segs, nseg, n_dev, cap, n_host, sort_block(blockIdx.x, gridDim.x));
     if (br.live) {
         const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
         const int64_t wbase = br.lo + (int64_t)w * (kSortItems * kWave);
@@ -427,6 +423,45 @@ __global__ __launch_bounds__(kScanPartialsThreads) void k_hist_scan_partials(uin
     }
 }
 
+// Stable ranks of a wave's rows of items within their digits; entry d of the wave's table in
+// LDS holds the lanes of the row in work that have digit d, and the items of digit d in the
+// rows before.  Every lane sets its bit, reads the entry - its peers, so its place among them -
+// and the lowest peer writes the entry back with the row counted.  LDS instructions of one wave
+// take effect in issue order.  (Finding the peers by a ballot per digit bit took 48 vector
+// instructions a row: the scatters of 193M view pairs and 40 sun maps 3.8 ms, now 3.0.)
+// 16-bit keys carry their rank in the upper half (a wave has at most 1024 items).
+template <typename KT, int ITEMS>
+__device__ __forceinline__ void rank_rows(uint32_t (&key)[ITEMS], uint32_t (&rank)[ITEMS],
+                                          uint4 *wtab, int64_t wbase, int64_t hi, uint32_t base, int shift)
+{
+    static_assert(ITEMS * kWave <= 65536);
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint64_t bit = 1ull << lane;
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const bool valid = wbase + it * kWave + lane < hi;
+        uint4 *const e = wtab + key_digit<KT>((KT)key[it], base, shift);
+        if (valid) atomicOr(reinterpret_cast<unsigned long long *>(e), bit);
+        __builtin_amdgcn_wave_barrier();
+        const uint4 x = *e;
+        const uint64_t m = ((uint64_t)x.y << 32) | x.x;
+        const uint32_t before = __popcll(m & (bit - 1));
+        if (valid && before == 0) *e = make_uint4(0, 0, x.z + (uint32_t)__popcll(m), 0);
+        __builtin_amdgcn_wave_barrier();
+        if (sizeof(KT) == 2) key[it] |= (x.z + before) << 16;
+        else rank[it] = x.z + before;
+    }
+    // the digits are taken from the keys again, not kept
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) asm("" : "+v"(key[it]));
+}
+
+template <typename KT>
+__device__ __forceinline__ uint32_t rank_of(uint32_t key, uint32_t rank)
+{
+    return sizeof(KT) == 2 ? key >> 16 : rank;
+}
+
 // With `ranges` (the last pass), every block also reports, per key, the first and last
 // output position of its run: ranges[2k] = min over blocks, ranges[2k + 1] = max + 1.
 // A block holds its items in LDS sorted by the whole key (stable on the top digit of
@@ -435,24 +470,25 @@ template <typename KT>
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const KT *kin, const uint32_t *vin, KT *kout, uint32_t *vout,
     const uint32_t *offs, const SegDesc *segs, int nseg, const unsigned long long *n_dev,
-    int64_t cap, int64_t n_host, int shift, int nbits, uint32_t *ranges, int64_t nkeys,
+    int64_t cap, int64_t n_host, int shift, uint32_t *ranges, int64_t nkeys,
     uint32_t *rank_out)
 {
     constexpr bool kLocal = sizeof(KT) == 2;
     __shared__ uint32_t wcnt[kSortWaves][256];
-    __shared__ uint32_t wsink[kSortWaves][kWave];  // target of the lanes that are not group leaders
     __shared__ uint32_t dbase[256];          // block-local start of each digit's run
     __shared__ uint32_t gshift[256];         // global start minus local start, per digit
     __shared__ uint32_t lds_w[kSortWaves];
     __shared__ KT skey[kSortTile];
-    __shared__ uint32_t sval[kSortTile];
-    const BlockRange br = block_range(segs, nseg, n_dev, cap, n_host, blockIdx.x);
+    // per wave and digit, the row's lanes and the count before it (ranking); later the values
+    __shared__ uint4 tab[kSortWaves * 256];
+    uint32_t *const sval = reinterpret_cast<uint32_t *>(tab);
+    static_assert(sizeof(tab) >= sizeof(uint32_t) * kSortTile);
+    const BlockRange br = block_range(segs, nseg, n_dev, cap, n_host, sort_block(blockIdx.x, gridDim.x));
     if (!br.live) return;   // uniform over the block
-    for (int i = threadIdx.x; i < kSortWaves * 256; i += kSortThreads) (&wcnt[0][0])[i] = 0;
-    __syncthreads();
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const int64_t wbase = br.lo + (int64_t)w * (kSortItems * kWave);
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
+    uint4 *const wtab = tab + w * 256;
+    for (int i = lane; i < 256; i += kWave) wtab[i] = make_uint4(0, 0, 0, 0);
     uint32_t key[kSortItems], val[kSortItems], rank[kSortItems];
 #pragma unroll
     for (int it = 0; it < kSortItems; ++it) {
@@ -461,22 +497,8 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
         key[it] = valid ? (uint32_t)kin[i] : 0u;
         val[it] = valid ? vin[i] : 0u;
     }
-    // stable ranks: per item row, the lowest lane of each equal-digit group adds the group
-    // size to the wave's running count of that digit and receives the count before it (LDS
-    // atomics of one wave take effect in issue order, row after row); the other lanes add
-    // to a private word so that no two lanes of an instruction share an address
-#pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
-        const bool valid = wbase + it * kWave + lane < br.hi;
-        const uint32_t d = key_digit<KT>((KT)key[it], br.base, shift);
-        const uint64_t m = digit_peers(d, valid, nbits);
-        const uint32_t before = __popcll(m & lt_mask);
-        const bool leader = valid && before == 0;
-        uint32_t *cnt = leader ? &wcnt[w][d] : &wsink[w][lane];
-        const uint32_t old = atomicAdd(cnt, leader ? (uint32_t)__popcll(m) : 0u);
-        const int from = m != 0 ? (int)__builtin_ctzll(m) : lane;
-        rank[it] = (uint32_t)__shfl((int)old, from, kWave) + before;
-    }
+    rank_rows<KT, kSortItems>(key, rank, wtab, wbase, br.hi, br.base, shift);
+    for (int i = lane; i < 256; i += kWave) wcnt[w][i] = wtab[i].z;
     __syncthreads();
     {
         // per digit: prefix over the waves, then an exclusive scan over the digits gives
@@ -500,7 +522,7 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
         const int64_t i = wbase + it * kWave + lane;
         if (i < br.hi) {
             const uint32_t d = key_digit<KT>((KT)key[it], br.base, shift);
-            const uint32_t lp = dbase[d] + wcnt[w][d] + rank[it];
+            const uint32_t lp = dbase[d] + wcnt[w][d] + rank_of<KT>(key[it], rank[it]);
             if (lp < (uint32_t)kSortTile) {   // always true when the counts agree
                 skey[lp] = (KT)key[it];
                 sval[lp] = val[it];
@@ -657,18 +679,20 @@ template <typename KT, int ITEMS>
 __global__ __launch_bounds__(kSortThreads) void k_small_scatter(
     const KT *__restrict__ kin, const uint32_t *__restrict__ vin, KT *__restrict__ kout,
     uint32_t *__restrict__ vout, const uint32_t *__restrict__ hist, int64_t rows, SmallSegs sg, const unsigned long long *__restrict__ n_dev, int64_t cap,
-    int64_t n_host, int shift, int nbits, uint32_t *__restrict__ ranges, int64_t nkeys,
+    int64_t n_host, int shift, uint32_t *__restrict__ ranges, int64_t nkeys,
     uint32_t *__restrict__ rank_out)
 {
     constexpr int TILE = ITEMS * kSortThreads;
     constexpr bool kLocal = sizeof(KT) == 2;
     __shared__ uint32_t wcnt[kSortWaves][256];
-    __shared__ uint32_t wsink[kSortWaves][kWave];
     __shared__ uint4 csum[2][kSortWaves][kWave];      // column sums per wave: all rows, rows before
     __shared__ uint32_t dbase[256], gshift[256];
     __shared__ uint32_t lds_w[kSortWaves];
-    __shared__ KT skey[TILE];
-    __shared__ uint32_t sval[TILE];
+    // the waves' ranking tables (see rank_rows); later the values and keys in digit order
+    constexpr int kTab = kSortWaves * 256, kOut = (int)(sizeof(KT) + 4) * TILE / 16;
+    __shared__ uint4 tab[kTab > kOut ? kTab : kOut];
+    uint32_t *const sval = reinterpret_cast<uint32_t *>(tab);
+    KT *const skey = reinterpret_cast<KT *>(sval + TILE);
     const int64_t n = live_count(n_dev, cap, n_host);
     const SmallBlock sb = small_block<TILE>(sg, n, blockIdx.x);
     const int64_t start = sb.start, end = sb.end, row0 = sb.row0, i0 = sb.i0, i1 = sb.i1;
@@ -677,7 +701,6 @@ __global__ __launch_bounds__(kSortThreads) void k_small_scatter(
     if (i0 >= i1) return;                             // uniform over the block
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const int64_t wbase = i0 + (int64_t)w * (ITEMS * kWave);
-    const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
     uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
@@ -686,7 +709,8 @@ __global__ __launch_bounds__(kSortThreads) void k_small_scatter(
         key[it] = valid ? (uint32_t)kin[i] : 0u;
         val[it] = valid ? (vin ? vin[i] : (uint32_t)i) : 0u;
     }
-    for (int i = threadIdx.x; i < kSortWaves * 256; i += kSortThreads) (&wcnt[0][0])[i] = 0;
+    uint4 *const wtab = tab + w * 256;
+    for (int i = lane; i < 256; i += kWave) wtab[i] = make_uint4(0, 0, 0, 0);
     // column sums of the segment's rows, four digits per lane and a quarter of the rows per wave
     const int64_t nrows = min((end - start + TILE - 1) / TILE, rows - row0);
     uint4 all = make_uint4(0, 0, 0, 0), bef = make_uint4(0, 0, 0, 0);
@@ -700,19 +724,8 @@ __global__ __launch_bounds__(kSortThreads) void k_small_scatter(
     csum[0][w][lane] = all;
     csum[1][w][lane] = bef;
     __syncthreads();
-    // stable ranks within the wave's rows of items (see k_radix_scatter)
-#pragma unroll
-    for (int it = 0; it < ITEMS; ++it) {
-        const bool valid = wbase + it * kWave + lane < i1;
-        const uint32_t d = key_digit<KT>((KT)key[it], base, shift);
-        const uint64_t m = digit_peers(d, valid, nbits);
-        const uint32_t before = __popcll(m & lt_mask);
-        const bool leader = valid && before == 0;
-        uint32_t *cnt = leader ? &wcnt[w][d] : &wsink[w][lane];
-        const uint32_t old = atomicAdd(cnt, leader ? (uint32_t)__popcll(m) : 0u);
-        const int from = m != 0 ? (int)__builtin_ctzll(m) : lane;
-        rank[it] = (uint32_t)__shfl((int)old, from, kWave) + before;
-    }
+    rank_rows<KT, ITEMS>(key, rank, wtab, wbase, i1, base, shift);
+    for (int i = lane; i < 256; i += kWave) wcnt[w][i] = wtab[i].z;
     __syncthreads();
     {
         const int d = threadIdx.x;
@@ -738,7 +751,7 @@ __global__ __launch_bounds__(kSortThreads) void k_small_scatter(
         const int64_t i = wbase + it * kWave + lane;
         if (i < i1) {
             const uint32_t d = key_digit<KT>((KT)key[it], base, shift);
-            const uint32_t lp = dbase[d] + wcnt[w][d] + rank[it];
+            const uint32_t lp = dbase[d] + wcnt[w][d] + rank_of<KT>(key[it], rank[it]);
             if (lp < (uint32_t)TILE) {                // always true when the counts agree
                 skey[lp] = (KT)key[it];
                 sval[lp] = val[it];
@@ -767,14 +780,14 @@ __global__ __launch_bounds__(kSortThreads) void k_small_scatter(
 
 template <typename KT>
 static void small_passes(const SmallSort &plan, KT *ka, uint32_t *va, KT *kb, uint32_t *vb, bool index_vals,
-                         bool have_hist, int64_t cap, const unsigned long long *n_dev, int64_t n_host, int bits,
+                         bool have_hist, int64_t cap, const unsigned long long *n_dev, int64_t n_host,
                          uint32_t *hist, const SmallSegs &sg, uint32_t *ranges, int64_t nkeys,
                          uint32_t *rank_out, bool *result_in_b, hipStream_t st)
 {
     *result_in_b = false;
     for (int p = 0; p < plan.passes; ++p) {
         const bool last = p == plan.passes - 1;
-        const int shift = 8 * p, nbits = std::max(1, std::min(8, bits - shift));
+        const int shift = 8 * p;
         const uint32_t *vin = p == 0 && index_vals ? nullptr : va;
         KT *ko = last ? nullptr : kb;      // nothing reads the sorted keys
         const dim3 grid((unsigned)plan.rows), blk(kSortThreads);
@@ -782,7 +795,7 @@ static void small_passes(const SmallSort &plan, KT *ka, uint32_t *va, KT *kb, ui
             if (p > 0 || !have_hist)
                 hipLaunchKernelGGL(hist_kernel, grid, blk, 0, st, ka, sg, n_dev, cap, n_host, shift, hist);
             hipLaunchKernelGGL(scatter_kernel, grid, blk, 0, st, ka, vin, ko, vb, hist, plan.rows, sg,
-                               n_dev, cap, n_host, shift, nbits, last ? ranges : nullptr, nkeys,
+                               n_dev, cap, n_host, shift, last ? ranges : nullptr, nkeys,
                                last ? rank_out : nullptr);
         };
         if (plan.items == 4) pass(k_small_hist<KT, 4>, k_small_scatter<KT, 4>);
@@ -800,7 +813,7 @@ hipError_t small_sort_tiles(const SmallSort &plan, KT *keys_a, uint32_t *vals_a,
                             uint32_t *hist, bool *result_in_b, hipStream_t st, const SortSegments &seg)
 {
     const SmallSegs sg{seg.offs, seg.stride, seg.nseg, seg.views};
-    small_passes<KT>(plan, keys_a, vals_a, keys_b, vals_b, false, false, cap, n_dev, 0, bits, hist, sg,
+    small_passes<KT>(plan, keys_a, vals_a, keys_b, vals_b, false, false, cap, n_dev, 0, hist, sg,
                      seg.nkeys > 0 ? seg.ranges : nullptr, seg.nkeys, nullptr, result_in_b, st);
     return hipGetLastError();
 }
@@ -842,7 +855,7 @@ hipError_t depth_sort(const float *mean, int64_t n, float bz, uint32_t *keys_a, 
         hipLaunchKernelGGL(k_depth_keys_hist<8>, grid, blk, 0, st, mean, n, bz, keys_a, hist);
     else
         hipLaunchKernelGGL(k_depth_keys_hist<16>, grid, blk, 0, st, mean, n, bz, keys_a, hist);
-    small_passes<uint32_t>(plan, keys_a, vals_a, keys_b, vals_b, true, true, n, nullptr, n, 32, hist,
+    small_passes<uint32_t>(plan, keys_a, vals_a, keys_b, vals_b, true, true, n, nullptr, n, hist,
                            SmallSegs{nullptr, 0, 0, nullptr}, nullptr, 0, rank, result_in_b, st);
     return hipGetLastError();
 }
@@ -887,7 +900,6 @@ hipError_t radix_sort_pairs(KT *keys_a, uint32_t *vals_a, KT *keys_b,
     uint32_t *vi = vals_a, *vo = vals_b;
     for (int p = 0; p < passes; ++p) {
         const int shift = 8 * p;
-        const int nbits = std::max(1, std::min(8, bits - shift));
         hipLaunchKernelGGL(k_radix_hist<KT>, dim3((unsigned)nb), dim3(kSortThreads), 0, st, ki, segs,
                            nseg, n_dev, cap, n_host, shift, hist);
         hipLaunchKernelGGL(k_hist_scan_reduce, dim3((unsigned)nparts), dim3(kSortThreads), 0,
@@ -900,7 +912,7 @@ hipError_t radix_sort_pairs(KT *keys_a, uint32_t *vals_a, KT *keys_b,
         const bool last = p == passes - 1;
         hipLaunchKernelGGL(k_radix_scatter<KT>, dim3((unsigned)nb), dim3(kSortThreads), 0, st, ki,
                            vi, last && ranges ? nullptr : ko, vo, hist, segs, nseg, n_dev, cap,
-                           n_host, shift, nbits, last ? ranges : nullptr, seg ? seg->nkeys : 0,
+                           n_host, shift, last ? ranges : nullptr, seg ? seg->nkeys : 0,
                            last ? rank_out : nullptr);
         std::swap(ki, ko);
         std::swap(vi, vo);
