@@ -356,14 +356,17 @@ hipError_t launch_vis_to_rank(const float *vis, int64_t n, int32_t nv, const uin
 }
 
 // ------------------------------------------------------------------------ emit
-// One thread per (rank, view): one (tile id, rank) pair per overlapped tile.  A block's 256
-// ranks own one contiguous run of the output, which starts at the block's scanned pair sum;
-// inside it the threads' places come from a scan of their counts here (the tile rectangles
-// give them, or `counts` where a tile mask cut them).  Runs of up to kEmitStage pairs are
+// One thread per kEmitRanks consecutive ranks of a view: one (tile id, rank) pair per overlapped
+// tile.  A block's ranks own one contiguous run of the output, which starts at the scanned
+// pair sum of its first kRankBlock; inside it the threads' places come from a scan of their
+// counts here (the tile rectangles give them, or `counts` where a tile mask cut them).  Runs of up to kEmitStage pairs are
 // assembled in LDS and written out coalesced, longer ones go straight to memory.  Pairs
 // beyond the bound capacity are dropped (the scan already raised the overflow flag).
-constexpr int kEmitThreads = kRankBlock;
-constexpr int kEmitStage = 1024;
+// Bound by the latency of a block's few steps: two ranks a thread halve the blocks (2M surfels
+// x (40 views + 40 sun maps) 1.28 -> 0.84 ms, 1M x 20 sun maps 195 -> 166 us); four make the
+// large sizes 0.76 ms and 157 us, but leave one view of 1M too few blocks (30 -> 42 us).
+constexpr int kEmitThreads = kRankBlock, kEmitRanks = 2;
+constexpr int kEmitStage = 2048;
 
 template <typename KT>
 __global__ __launch_bounds__(kEmitThreads) void k_emit(
@@ -376,21 +379,25 @@ __global__ __launch_bounds__(kEmitThreads) void k_emit(
     __shared__ uint32_t sv[kEmitStage];
     __shared__ uint32_t lds_w[kEmitThreads / 64];
     const int v = blockIdx.y;
-    const int64_t r = (int64_t)blockIdx.x * kEmitThreads + threadIdx.x;
-    const uint64_t b_lo = base[(int64_t)v * gridDim.x + blockIdx.x];
-    short4 t = make_short4(0, -1, 0, -1);
+    const int64_t r0 = ((int64_t)blockIdx.x * kEmitThreads + threadIdx.x) * kEmitRanks;
+    const uint64_t b_lo = base[(int64_t)v * rank_blocks(n) + kEmitRanks * (int64_t)blockIdx.x];
+    const ViewDesc vd = views[v];
+    short4 ts[kEmitRanks];
     uint32_t cnt = 0;
-    if (r < n) {
-        t = tiles[(int64_t)v * n + r];
-        cnt = counts ? counts[(int64_t)v * n + r]
-                     : (uint32_t)(t.y - t.x + 1) * (uint32_t)(t.w - t.z + 1);
+#pragma unroll
+    for (int k = 0; k < kEmitRanks; ++k) {
+        ts[k] = r0 + k < n ? tiles[(int64_t)v * n + r0 + k] : make_short4(0, -1, 0, -1);
+        if (counts) cnt += r0 + k < n ? counts[(int64_t)v * n + r0 + k] : 0u;
+        else cnt += (uint32_t)(ts[k].y - ts[k].x + 1) * (uint32_t)(ts[k].w - ts[k].z + 1);
     }
     uint32_t total;
     const uint32_t before = block_exclusive_scan(cnt, lds_w, &total);
-    const ViewDesc vd = views[v];
     const bool staged = total <= (uint32_t)kEmitStage;   // uniform over the block
-    if (cnt != 0) {
-        uint64_t l = before;
+    uint64_t l = before;
+#pragma unroll
+    for (int k = 0; k < kEmitRanks; ++k) {
+        const short4 t = ts[k];
+        const uint32_t r = (uint32_t)(r0 + k);
         for (int ty = t.z; ty <= t.w; ++ty)
             for (int tx = t.x; tx <= t.y; ++tx) {
                 const uint32_t lkey = (uint32_t)(ty * vd.tiles_x + tx);
@@ -400,11 +407,11 @@ __global__ __launch_bounds__(kEmitThreads) void k_emit(
                 if (!staged) {
                     if (b_lo + l < cap) {
                         keys[b_lo + l] = key;
-                        vals[b_lo + l] = (uint32_t)r;
+                        vals[b_lo + l] = r;
                     }
                 } else if (l < (uint64_t)kEmitStage) {
                     sk[l] = key;
-                    sv[l] = (uint32_t)r;
+                    sv[l] = r;
                 }
                 ++l;
             }
@@ -424,7 +431,7 @@ hipError_t launch_emit(int64_t n, int32_t nv, const ViewDesc *views, const short
                        bool keys16, uint32_t *vals, const uint32_t *tmask, hipStream_t st)
 {
     if (n <= 0 || cap == 0) return hipSuccess;
-    const dim3 grid((unsigned)rank_blocks(n), (unsigned)nv);
+    const dim3 grid((unsigned)((rank_blocks(n) + kEmitRanks - 1) / kEmitRanks), (unsigned)nv);
     const uint32_t *cn = tmask ? counts : nullptr;
     if (keys16)
         hipLaunchKernelGGL(k_emit<uint16_t>, grid, dim3(kEmitThreads), 0, st, n, views, tiles, cn, base,
