@@ -136,6 +136,10 @@ hipError_t launch_sun_cameras(const float *mean, int64_t n, int32_t nv, const fl
 // Per (view, surfel): project the centre into the sun map (FP64, the texel choice is a
 // floor), read the 3x3 texels around it (outside the map: background z_far), and
 //   vis = min(1, (1/9) sum_t exp(c_e (D_t - d_k + beta))),  d_k = b_z - p_k,z.
+// Bound by the map's cache lines where every point is looked up (three or four of 128 bytes
+// per point: 2M surfels in 40 maps of 4 MB 1.48 ms, ~25 TB/s from L2), by latency where few
+// are: the window's rows are read together (2M x 40: 1.56 -> 1.48 ms; 1M x 20, only points
+// within a band: 194 -> 144 us).  Reading both float4 of every row without a test: 1.74 ms.
 __global__ void k_shadow_query(const float *__restrict__ mean, int64_t n,
                                const SunCam *__restrict__ sun, const float *__restrict__ D,
                                int32_t S, float bz, float esm_c, float esm_bias,
@@ -156,35 +160,44 @@ __global__ void k_shadow_query(const float *__restrict__ mean, int64_t n,
     const float dk = __fsub_rn(bz, (float)p2);
     const float zfar = (float)c.zfar;
     const float *Dv = D + (int64_t)v * S * S;
-    // texels in row-major window order, each row's three read together: with rows16 (S a
-    // multiple of 4 and D 16-byte aligned) every map row is 16-byte aligned, and a window
-    // row inside the map lies in the aligned float4 at its first texel or in that one and
-    // the next
+    // texels in row-major window order; with rows16 (S a multiple of 4 and D 16-byte aligned)
+    // every map row is 16-byte aligned, and a window row inside the map lies in the aligned
+    // float4 at its first texel or in that one and the next
     const double tx0 = fx - 1;
     const bool cols_in = tx0 >= 0 && tx0 + 2 < S;
+    const double ty0 = fy - 1;
     float acc = 0.f;
-    for (int r = 0; r < 3; ++r) {
-        const double ty = fy + r - 1;
-        float d[3] = {zfar, zfar, zfar};
-        if (ty >= 0 && ty < S) {
-            const float *row = Dv + (int64_t)ty * S;
-            if (rows16 && cols_in) {
-                const int64_t x0 = (int64_t)tx0, a = x0 & ~(int64_t)3;
-                const int o = (int)(x0 - a);
-                const float4 A = *reinterpret_cast<const float4 *>(row + a);
-                float4 B = A;
-                if (o >= 2) B = *reinterpret_cast<const float4 *>(row + a + 4);
-                d[0] = o == 0 ? A.x : o == 1 ? A.y : o == 2 ? A.z : A.w;
-                d[1] = o == 0 ? A.y : o == 1 ? A.z : o == 2 ? A.w : B.x;
-                d[2] = o == 0 ? A.z : o == 1 ? A.w : o == 2 ? B.x : B.y;
-            } else {
-                for (int i = 0; i < 3; ++i) {
-                    const double tx = tx0 + i;
-                    if (tx >= 0 && tx < S) d[i] = row[(int64_t)tx];
-                }
+    if (rows16 && cols_in && ty0 >= 0 && ty0 + 2 < S) {
+        // the window is inside the map: all its reads go out before the first is used
+        const int64_t x0 = (int64_t)tx0, a = x0 & ~(int64_t)3;
+        const int o = (int)(x0 - a);
+        const float *row = Dv + (int64_t)ty0 * S + a;
+        float4 A[3];
+        float2 B[3] = {};
+#pragma unroll
+        for (int r = 0; r < 3; ++r) A[r] = *reinterpret_cast<const float4 *>(row + (int64_t)r * S);
+        if (o >= 2) {
+#pragma unroll
+            for (int r = 0; r < 3; ++r) B[r] = *reinterpret_cast<const float2 *>(row + (int64_t)r * S + 4);
+        }
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const float d[3] = {o == 0 ? A[r].x : o == 1 ? A[r].y : o == 2 ? A[r].z : A[r].w,
+                                o == 0 ? A[r].y : o == 1 ? A[r].z : o == 2 ? A[r].w : B[r].x,
+                                o == 0 ? A[r].z : o == 1 ? A[r].w : o == 2 ? B[r].x : B[r].y};
+#pragma unroll
+            for (int i = 0; i < 3; ++i) acc += expf(esm_c * (d[i] - dk + esm_bias));
+        }
+    } else {
+        for (int r = 0; r < 3; ++r) {
+            const double ty = ty0 + r;
+            for (int i = 0; i < 3; ++i) {
+                const double tx = tx0 + i;
+                const float d = ty >= 0 && ty < S && tx >= 0 && tx < S
+                                    ? Dv[(int64_t)ty * S + (int64_t)tx] : zfar;
+                acc += expf(esm_c * (d - dk + esm_bias));
             }
         }
-        for (int i = 0; i < 3; ++i) acc += expf(esm_c * (d[i] - dk + esm_bias));
     }
     acc *= (1.f / 9.f);
     vis[(int64_t)v * n + k] = fminf(1.f, acc);
