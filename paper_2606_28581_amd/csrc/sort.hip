@@ -577,8 +577,8 @@ hipError_t finish_ranges(uint32_t *ranges, int64_t nkeys, hipStream_t st)
 // blocks of 1024 items, then up to 256 of 2048 and 4096 (1M items), beyond which the scans
 // above are as fast.  (Counting the next pass's digits while scattering saves the histogram launch, but
 // keys that share a digit then meet on one address: 80 us for a pass of 190,000 pairs.)
-// Depth order of 20,000 surfels: 21 launches, 104 us -> 8 launches, 44 us; of 1M: 145 ->
-// 125 us.
+// Depth order of 20,000 surfels: 21 launches, 104 us -> 8 launches, 44 us (fewer still by
+// k_depth_merge); of 1M: 145 -> 125 us.
 constexpr int kSmallRows4 = 128, kSmallRows = 256;
 
 SmallSort plan_small_sort(int64_t cap, int32_t nseg, int bits)
@@ -825,6 +825,127 @@ template hipError_t small_sort_tiles<uint16_t>(const SmallSort &, uint16_t *, ui
                                                int64_t, const unsigned long long *, int, uint32_t *, bool *,
                                                hipStream_t, const SortSegments &);
 
+// Depth order of few surfels in two launches: chunks of 1024 sorted in LDS, then every item
+// finds its place by binary search in all chunks, whose keys fit one CU's LDS.  Stable: equal
+// keys of earlier chunks come first.  20,000 surfels: 8 launches of eight-bit passes and 41 us
+// -> 2 launches and 26 us.  The line at kMergeMax is what a CU's LDS holds beside nothing else
+// (a second block of 128 KB does not fit); the searches also grow with n^2 / 1024.
+constexpr int kChunkItems = 4, kChunk = kChunkItems * kSortThreads;
+constexpr int kMergeThreads = 256, kMergeMax = 32768;
+
+__global__ __launch_bounds__(kSortThreads) void k_depth_chunks(const float *__restrict__ mean, int64_t n,
+                                                               float bz, uint32_t *__restrict__ keys,
+                                                               uint32_t *__restrict__ vals)
+{
+    __shared__ uint4 tab[kSortWaves * 256];
+    __shared__ uint32_t wcnt[kSortWaves][256];
+    __shared__ uint32_t dbase[256];
+    __shared__ uint32_t lds_w[kSortWaves];
+    __shared__ uint32_t skey[kChunk];
+    __shared__ uint16_t sidx[kChunk];
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    const int64_t i0 = (int64_t)blockIdx.x * kChunk;
+    const int cnt = (int)min((int64_t)kChunk, n - i0);
+    const int at = w * (kChunkItems * kWave) + lane;
+    uint4 *const wtab = tab + w * 256;
+    uint32_t key[kChunkItems], idx[kChunkItems], rank[kChunkItems];
+#pragma unroll
+    for (int it = 0; it < kChunkItems; ++it) {
+        const int i = at + it * kWave;
+        key[it] = i < cnt ? depth_key(bz, mean[3 * (i0 + i) + 2]) : 0u;
+        idx[it] = (uint32_t)i;
+    }
+    for (int shift = 0; shift < 32; shift += 8) {
+        for (int i = lane; i < 256; i += kWave) wtab[i] = make_uint4(0, 0, 0, 0);
+        rank_rows<uint32_t, kChunkItems>(key, rank, wtab, (int64_t)w * (kChunkItems * kWave), cnt, 0, shift);
+        for (int i = lane; i < 256; i += kWave) wcnt[w][i] = wtab[i].z;
+        __syncthreads();
+        {
+            const int d = threadIdx.x;
+            uint32_t run = 0;
+#pragma unroll
+            for (int k = 0; k < kSortWaves; ++k) {
+                const uint32_t c = wcnt[k][d];
+                wcnt[k][d] = run;
+                run += c;
+            }
+            uint32_t tot;
+            dbase[d] = block_exclusive_scan(run, lds_w, &tot);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kChunkItems; ++it) {
+            const uint32_t d = key_digit<uint32_t>(key[it], 0, shift);
+            const uint32_t lp = dbase[d] + wcnt[w][d] + rank[it];
+            if (at + it * kWave < cnt && lp < (uint32_t)kChunk) {
+                skey[lp] = key[it];
+                sidx[lp] = (uint16_t)idx[it];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < kChunkItems; ++it) {
+            const int i = at + it * kWave;
+            if (i < cnt) {
+                key[it] = skey[i];
+                idx[it] = sidx[i];
+            }
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < kChunkItems; ++it) {
+        const int i = at + it * kWave;
+        if (i < cnt) {
+            keys[i0 + i] = key[it];
+            vals[i0 + i] = (uint32_t)i0 + idx[it];
+        }
+    }
+}
+
+// Keys of a sorted chunk of m (at most kChunk) that come before k.
+template <bool EQUAL>
+__device__ __forceinline__ uint32_t keys_before(const uint32_t *chunk, uint32_t m, uint32_t k)
+{
+    uint32_t pos = 0;
+#pragma unroll
+    for (uint32_t s = kChunk; s > 0; s >>= 1) {
+        const uint32_t x = chunk[min(pos + s, m) - 1];
+        const bool before = EQUAL ? x <= k : x < k;
+        pos += pos + s <= m && before ? s : 0u;
+    }
+    return pos;
+}
+
+__global__ __launch_bounds__(kMergeThreads) void k_depth_merge(const uint32_t *__restrict__ keys,
+                                                               const uint32_t *__restrict__ vals, int n,
+                                                               uint32_t *__restrict__ order,
+                                                               uint32_t *__restrict__ rank)
+{
+    __shared__ __align__(16) uint32_t all[kMergeMax];
+    const int n4 = n / 4;
+#pragma unroll 8
+    for (int i = threadIdx.x; i < n4; i += kMergeThreads)
+        reinterpret_cast<uint4 *>(all)[i] = reinterpret_cast<const uint4 *>(keys)[i];
+    if (threadIdx.x < n - 4 * n4) all[4 * n4 + threadIdx.x] = keys[4 * n4 + threadIdx.x];
+    __syncthreads();
+    const int i = blockIdx.x * kMergeThreads + threadIdx.x;
+    if (i >= n) return;
+    static_assert(kChunk % kMergeThreads == 0);       // a block's items lie in one chunk
+    const int c = (int)(blockIdx.x * kMergeThreads) / kChunk, chunks = (n + kChunk - 1) / kChunk;
+    const uint32_t k = all[i];
+    uint32_t pos = (uint32_t)(i - c * kChunk);
+#pragma unroll 4
+    for (int q = 0; q < c; ++q) pos += keys_before<true>(all + q * kChunk, kChunk, k);
+#pragma unroll 4
+    for (int q = c + 1; q < chunks; ++q)
+        pos += keys_before<false>(all + q * kChunk, (uint32_t)min(kChunk, n - q * kChunk), k);
+    const uint32_t v = vals[i];
+    if (pos < (uint32_t)n && v < (uint32_t)n) {       // always
+        order[pos] = v;
+        if (rank) rank[v] = pos;
+    }
+}
+
 __global__ void k_depth_keys(const float *__restrict__ mean, int64_t n, float bz,
                              uint32_t *__restrict__ keys, uint32_t *__restrict__ vals)
 {
@@ -840,6 +961,13 @@ hipError_t depth_sort(const float *mean, int64_t n, float bz, uint32_t *keys_a, 
 {
     *result_in_b = false;
     if (n <= 0) return hipSuccess;
+    if (n <= kMergeMax) {
+        hipLaunchKernelGGL(k_depth_chunks, dim3((unsigned)((n + kChunk - 1) / kChunk)), dim3(kSortThreads), 0,
+                           st, mean, n, bz, keys_b, vals_b);
+        hipLaunchKernelGGL(k_depth_merge, dim3((unsigned)((n + kMergeThreads - 1) / kMergeThreads)),
+                           dim3(kMergeThreads), 0, st, keys_b, vals_b, (int)n, vals_a, rank);
+        return hipGetLastError();
+    }
     const SmallSort plan = plan_small_sort(n, 0, 32);
     if (plan.rows == 0) {
         hipLaunchKernelGGL(k_depth_keys, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, mean, n, bz,

@@ -506,6 +506,12 @@ def test_depth_order_and_tile_lists_across_sort_sizes(n, views, slack):
     np.testing.assert_array_equal(b["ranges"], expect)
 
 
+@pytest.mark.parametrize("n", [63, 1024, 2047, 2049, 32_767, 32_768, 32_769])
+def test_depth_order_around_the_sizes_of_merged_chunks(n):
+    """Whole chunks of 1024, one item less and more, and the last size that is merged."""
+    test_depth_order_and_tile_lists_across_sort_sizes(n, 1, 0)
+
+
 def test_backward_writes_gradients_directly_and_by_rows():
     """Up to 65,536 surfels the projection backward writes the gradient arrays itself, beyond
     by way of rank-ordered rows: one transparent surfel more must change nothing."""
