@@ -189,7 +189,7 @@ static int64_t max_view_tiles(const std::vector<ViewDesc> &views)
     return m;
 }
 
-static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs)
+static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs, bool masks = true)
 {
     Layout L{};
     size_t o = 0;
@@ -237,7 +237,7 @@ static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs)
     L.inv_sun = take(n * 4);
     L.vis_rank = take(vn * 4);
     // forward -> backward contributor masks at the current tile size
-    L.cmask_bytes = cmask_words(cm, p->tiles_main, p->st.tile_size) * 8;
+    L.cmask_bytes = masks ? cmask_words(cm, p->tiles_main, p->st.tile_size) * 8 : 0;
     L.cmask = take(L.cmask_bytes);
     // heavy-first raster dispatch orders and their per-XCD block counts
     L.torder_main = take((size_t)p->tiles_main_max * 4);
@@ -414,7 +414,7 @@ static ss_status bin_views(ss_plan *p, const ss_views *v, bool sun, const float 
 }
 
 // Contributor masks: there is room for them unless the tile size grew since the workspace was
-// laid out (then the backward uses the box test).
+// laid out, or it was bound with less than the full size (then the backward uses the box test).
 static unsigned long long *cmask_ptr(const ss_plan *p)
 {
     if (p->L.cmask_bytes < cmask_words(p->cap_main, p->tiles_main, p->st.tile_size) * 8) return nullptr;
@@ -630,6 +630,8 @@ ss_status ss_plan_bind_workspace(ss_plan *p, void *workspace, size_t bytes, int6
     if (main_pairs < 0 || sun_pairs < 0 || main_pairs > 0xFFFFFFFFll || sun_pairs > 0xFFFFFFFFll)
         return fail(SS_ERR_INVALID_ARG, "pair capacity must be in [0, 2^32)");
     Layout L = make_layout(p, main_pairs, sun_pairs);
+    // 16x16 and 32x32 tiles can do without contributor masks
+    if (bytes < L.total && p->st.tile_size != 8) L = make_layout(p, main_pairs, sun_pairs, false);
     if (bytes < L.total) return fail(SS_ERR_CAPACITY, "workspace smaller than required");
     p->L = L;
     p->ws = reinterpret_cast<char *>(workspace);

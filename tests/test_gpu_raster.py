@@ -5,6 +5,8 @@ Bars: tile ids, per-tile lists and the depth order bit-exact; images max-abs 1e-
 not flag as threshold-ambiguous; gradients per tensor max |g - g*| / max(|g*|,
 1e-2 rms(g*)) <= 1e-3 with the upstream gradient zeroed on ambiguous pixels.
 """
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -12,6 +14,7 @@ import torch
 import oracle
 import synth
 import paper_2606_28581_amd as ss
+from paper_2606_28581_amd import _lib
 from gpu_common import (ATOMIC_ORDER_TOL, GRAD_KEYS, context, expand3, make_plan, oracle_settings, rel_err,
                         to_np)
 
@@ -223,6 +226,18 @@ def test_backward_of_larger_tiles_with_and_without_masks(ts, bound_at, n, mean_l
     out = plan.forward(surf, views, torch.as_tensor(vis, device="cuda"))
     ref = oracle.forward(sc, oracle_settings(ts=ts), vis=vis)
     check_backward(sc, plan, surf, views, out, ref, vis=vis)
+
+
+def test_workspace_of_smaller_tiles_is_enough_for_larger_ones():
+    """The bytes that 8x8 tiles need bind at 16x16 too (no room for contributor masks there)."""
+    sc = scene_tiny(seed=18, n=2000)
+    plan, surf, views = make_plan(sc, ts=8)
+    caps, nbytes = (plan.cap_main, plan.cap_sun), plan.workspace.numel()
+    plan.set_settings(ss.default_settings(tile_size=16, batch_depth=64))
+    assert plan.workspace_size(*caps) > nbytes
+    _lib.call("ss_plan_bind_workspace", plan.handle, C.c_void_p(plan.workspace.data_ptr()), nbytes, *caps)
+    out = plan.forward(surf, views)
+    check_backward(sc, plan, surf, views, out, oracle.forward(sc, oracle_settings(ts=16)))
 
 
 @pytest.mark.parametrize("ts,n", [(16, 6000), (32, 6000), (32, 700)])
