@@ -199,10 +199,11 @@ static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs, bool masks =
     L.views_main = take(nv * sizeof(ViewDesc));
     L.views_sun = take(nv * sizeof(ViewDesc));
     L.suncam = take(nv * sizeof(SunCam));
-    L.counters = take(16 * sizeof(unsigned long long));
+    // flags right behind the counters: one copy reads both
+    L.counters = take(16 * sizeof(unsigned long long) + 16 * sizeof(uint32_t));
+    L.flags = L.counters + 16 * sizeof(unsigned long long);
     L.stat_main = take((size_t)kStatSlots * kStatStride * sizeof(unsigned long long));
     L.stat_sun = take((size_t)kStatSlots * kStatStride * sizeof(unsigned long long));
-    L.flags = take(16 * sizeof(uint32_t));
     L.mk_a = take(n * 4); L.mk_b = take(n * 4); L.mv_a = take(n * 4); L.mv_b = take(n * 4);
     L.sorted_main = take(n * 16 * 4);
     L.sk_a = take(n * 4); L.sk_b = take(n * 4); L.sv_a = take(n * 4); L.sv_b = take(n * 4);
@@ -679,14 +680,12 @@ ss_status ss_plan_check(ss_plan *p, int32_t *overflowed, int64_t *main_pairs, in
     if (!p || !p->ws) return fail(SS_ERR_STATE, "plan has no workspace");
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     SS_HIP(hipSetDevice(p->ctx->device));
-    unsigned long long c[2];
-    uint32_t f[2];
-    SS_HIP(hipMemcpyAsync(c, p->at<void>(p->L.counters), sizeof c, hipMemcpyDeviceToHost, st));
-    SS_HIP(hipMemcpyAsync(f, p->at<void>(p->L.flags), sizeof f, hipMemcpyDeviceToHost, st));
+    struct { unsigned long long c[16]; uint32_t f[2]; } h;      // as laid out in the workspace
+    SS_HIP(hipMemcpyAsync(&h, p->at<void>(p->L.counters), sizeof h, hipMemcpyDeviceToHost, st));
     SS_HIP(hipStreamSynchronize(st));
-    if (overflowed) *overflowed = (f[0] | f[1]) ? 1 : 0;
-    if (main_pairs) *main_pairs = (int64_t)c[0];
-    if (sun_pairs) *sun_pairs = (int64_t)c[1];
+    if (overflowed) *overflowed = (h.f[0] | h.f[1]) ? 1 : 0;
+    if (main_pairs) *main_pairs = (int64_t)h.c[0];
+    if (sun_pairs) *sun_pairs = (int64_t)h.c[1];
     return SS_OK;
 }
 

@@ -409,6 +409,9 @@ class RasterizeAffine2DGS(torch.autograd.Function):
                         views.sun)
         out = plan.forward(s, v, vis)
         ctx.plan, ctx.views = plan, v
+        # an output that no loss uses has no gradient tensor, and the adjoint takes a null pointer
+        # for it (zeros for the four non-differentiable maps cost four launches a backward)
+        ctx.set_materialize_grads(False)
         ctx.has = (colC is not None, colc is not None, ambient is not None)
         ctx.save_for_backward(mean, t_u, t_v, scale, opacity, albedo, vis, out["albedo"],
                               out["vis"], out["T"], out["last"])

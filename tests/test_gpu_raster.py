@@ -298,6 +298,24 @@ def test_autograd_function_matches_plan_backward():
 
 
 # ------------------------------------------------------- clamp and degenerate branches
+@pytest.mark.parametrize("used", [("image",), ("depth",), ("normal",), ("depth", "normal")])
+def test_autograd_of_some_outputs_is_the_adjoint_with_zeros_for_the_rest(used):
+    sc = scene_tiny(seed=14, views=((30, 30), (17, 22)), n=300)
+    plan, surf, views = make_plan(sc, ts=8)
+    params = [surf.mean, surf.t_u, surf.t_v, surf.scale, surf.opacity, surf.albedo, views.dF,
+              views.colC, views.colc, views.ambient]
+    for p in params:
+        p.requires_grad_(True)
+    o = ss.rasterize(plan, views, surf)
+    t = lambda a: torch.as_tensor(a, device="cuda")
+    up = dict(zip(("image", "depth", "normal"), (t(x) for x in synth.upstream_grads(sc))))
+    got = torch.autograd.grad([o[k] for k in used], params, [up[k] for k in used])
+    ref = plan.backward(surf, views, {k: o[k] for k in ("albedo", "vis", "T", "last")},
+                        *(x if k in used else torch.zeros_like(x) for k, x in up.items()))
+    for k, g in zip(GRAD_KEYS, got):
+        assert rel_err(to_np(g), to_np(ref[k])) < ATOMIC_ORDER_TOL, k
+
+
 @pytest.mark.parametrize("ts,batch,mode", [(8, 64, 0), (8, 48, 1), (16, 64, 0), (16, 64, 1)])
 def test_clamped_and_degenerate_surfels_forward_and_backward(ts, batch, mode):
     """Surfels with o G above alpha_max (alpha clamped to 0.99; the backward recovers T by
