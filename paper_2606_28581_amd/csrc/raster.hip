@@ -1591,8 +1591,14 @@ __device__ __forceinline__ float rows_prefix_add(float x, bool odd, bool upper, 
 // A staged record: centre, Q, (o, z0, k) with o negative where the record has no ellipse,
 // albedo with visibility, normal with the record's rank.
 constexpr int kBwdVec4 = 5;
+// Launches of up to this many 8x8 blocks give every quadrant a wave of its own (SPLIT): a chip
+// holds 4096-5120 of these waves, so fewer blocks leave it to its longest ones.  Backward of
+// 8x8 tiles, one wave a block -> four: 1024 blocks 86 -> 35 us, 8192 152 -> 106, 15,625 151 -> 141;
+// of 16x16 tiles, whose four waves each stage the whole block's records: 1024 99 -> 52, 7744 128 ->
+// 116, 12,100 136 -> 153.
+constexpr int64_t bwd_split(int ts) { return ts == 8 ? 16384 : 8192; }
 
-template <int TS, bool HAS_VIS, bool DIST, bool FILT>
+template <int TS, bool HAS_VIS, bool DIST, bool FILT, bool SPLIT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DIST || TS > 8 ? 4 : 5))) void k_raster_bwd_rp(
     int32_t nv, const ViewDesc *__restrict__ views, int32_t ntiles, const uint32_t *__restrict__ ranges,
     const uint32_t *__restrict__ lists, const float4 *__restrict__ rec, int64_t n,
@@ -1613,10 +1619,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DIST || TS >
     __shared__ float pst[kPst * 64];
     __shared__ uint32_t qlist[68];
     __shared__ int max_last;
-    // blocks go round-robin to the 8 XCDs: the SUB blocks of a tile stay on the tile's XCD
+    // blocks go round-robin to the 8 XCDs: the blocks of a tile stay on the tile's XCD
+    constexpr int PER = SUB * (SPLIT ? 4 : 1);
+    // a split wave stages its quadrant's records; dense batches are made of the whole block's,
+    // so that every quadrant is walked in the same steps as by one wave
+    constexpr bool MINE = SPLIT && !DENSE;
     const int b = (int)blockIdx.x;
-    const int vb = SUB == 1 ? b : 8 * (b / (8 * SUB)) + b % 8;
-    const int sub = SUB == 1 ? 0 : (b / 8) % SUB;
+    const int vb = PER == 1 ? b : 8 * (b / (8 * PER)) + b % 8;
+    const int part = PER == 1 ? 0 : (b / 8) % PER;
+    const int sub = SPLIT ? part >> 2 : part, qsel = SPLIT ? part & 3 : 0;
     if (vb >= ntiles) return;
     const int tile = rc.torder ? (int)rc.torder[vb] : xcd_tile(vb, ntiles);
     const int v = find_view(views, nv, tile);
@@ -1640,7 +1651,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DIST || TS >
         const PixelAdjoint pa = pixel_adjoint<HAS_VIS>(inside, v, g, b3, P, colC, colc, amb, Ain, Vin,
                                                        Tin, lastin, dI, dD, dN, cg);
         const float s = wave_transpose_reduce16(cg, lane);
-        if ((lane & 3) == 0) colour_partials[((int64_t)tile * SUB + sub) * 16 + (lane >> 2)] = s;
+        if ((lane & 3) == 0 && qsel == 0) colour_partials[((int64_t)tile * SUB + sub) * 16 + (lane >> 2)] = s;
         pst[0 * 64 + lane] = pa.gA0; pst[1 * 64 + lane] = pa.gA1; pst[2 * 64 + lane] = pa.gA2;
         pst[3 * 64 + lane] = pa.gV;  pst[4 * 64 + lane] = pa.gD;
         pst[5 * 64 + lane] = pa.gN0; pst[6 * 64 + lane] = pa.gN1; pst[7 * 64 + lane] = pa.gN2;
@@ -1651,7 +1662,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DIST || TS >
             pst[12 * 64 + lane] = dp.At;    pst[13 * 64 + lane] = dp.M1;
             pst[14 * 64 + lane] = dp.M2;
         }
-        if (pa.last > 0) atomicMax(&max_last, pa.last);
+        if (pa.last > 0 && (!MINE || row == qsel)) atomicMax(&max_last, pa.last);
     }
     __syncthreads();
     const uint2 range = tile_range(ranges, tile);
@@ -1669,7 +1680,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DIST || TS >
     // pixel composited, row q of `un` their union over quadrant q.
     auto walk = [&](const uint64_t own, const uint64_t un) {
         __syncthreads();
-        for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int qi = 0; qi < (SPLIT ? 1 : 4); ++qi) {
+            const int q = SPLIT ? qsel : qi;
             const uint64_t U = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(un >> 32), 16 * q) << 32) |
                                (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)un, 16 * q);
             if (U == 0) continue;                     // uniform
@@ -1752,7 +1765,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(DIST || TS >
     int kb = (blk_last + 63) >> 6;
     auto load_word = [&](int k) {                     // masks and list entries of word k
         const int nb = blk_last - 64 * k;
-        own_nn = inside ? own_at[(size_t)k * NT] : 0ull;
+        own_nn = inside && (!MINE || row == qsel) ? own_at[(size_t)k * NT] : 0ull;
         if (nb < 64) own_nn &= (1ull << nb) - 1ull;
         if (lane < nb) nidx = lists[start + 64 * k + lane];
     };
@@ -1842,13 +1855,19 @@ static void launch_bwd_d(size_t lds, hipStream_t st, int32_t ntiles, int32_t nv,
                          float *cp, const unsigned long long *cmask, const DistArgs &da)
 {
     if (cmask) {
-        const dim3 grid((unsigned)raster_blocks(ts_sub(TS), ntiles));
-#define SS_BWD_LAUNCH(FILT_)                                                                         \
-    hipLaunchKernelGGL((k_raster_bwd_rp<TS, HV, DIST, FILT_>), grid, dim3(64), 0, st, nv, views,     \
-                       ntiles, ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc, colC,    \
+        const bool split = raster_blocks(ts_sub(TS), ntiles) <= bwd_split(TS);
+        const dim3 grid((unsigned)raster_blocks(ts_sub(TS) * (split ? 4 : 1), ntiles));
+#define SS_BWD_LAUNCH(FILT_, SPLIT_)                                                                   \
+    hipLaunchKernelGGL((k_raster_bwd_rp<TS, HV, DIST, FILT_, SPLIT_>), grid, dim3(64), 0, st, nv, views, \
+                       ntiles, ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc, colC,      \
                        colc, amb, A, V, T, last, dI, dD, dN, recgrad, cp, cmask, da)
-        if (rc.lowpass_mode == 0) SS_BWD_LAUNCH(true);
-        else SS_BWD_LAUNCH(false);
+        if (rc.lowpass_mode == 0) {
+            if (split) SS_BWD_LAUNCH(true, true);
+            else SS_BWD_LAUNCH(true, false);
+        } else {
+            if (split) SS_BWD_LAUNCH(false, true);
+            else SS_BWD_LAUNCH(false, false);
+        }
 #undef SS_BWD_LAUNCH
         return;
     }

@@ -228,6 +228,28 @@ def test_backward_of_larger_tiles_with_and_without_masks(ts, bound_at, n, mean_l
     check_backward(sc, plan, surf, views, out, ref, vis=vis)
 
 
+@pytest.mark.parametrize("ts", [8, 16])
+def test_backward_of_a_small_and_of_a_large_launch(ts):
+    """The same pixels as a view of their own (a wave per quadrant) and as the corner of a view
+    of 17,161 blocks (a wave per block), with the upstream gradient on those pixels only."""
+    S, L = 64, 1048
+    small = scene_tiny(seed=19, views=((S, S),), n=800)
+    up = synth.upstream_grads(small)
+    grads = []
+    for side in (S, L):
+        sc = dict(small, width=np.array([side], np.int32), height=np.array([side], np.int32))
+        d = []
+        for x in up:
+            full = np.zeros((x.size // (S * S), side, side), np.float32)
+            full[:, :S, :S] = x.reshape(-1, S, S)
+            d.append(torch.as_tensor(full.reshape(-1), device="cuda"))
+        plan, surf, views = make_plan(sc, ts=ts)
+        out = plan.forward(surf, views)
+        grads.append(plan.backward(surf, views, out, *d))
+    for k in GRAD_KEYS:
+        assert rel_err(to_np(grads[1][k]), to_np(grads[0][k])) < 1e-3, k
+
+
 def test_workspace_of_smaller_tiles_is_enough_for_larger_ones():
     """The bytes that 8x8 tiles need bind at 16x16 too (no room for contributor masks there)."""
     sc = scene_tiny(seed=18, n=2000)
