@@ -741,7 +741,15 @@ __device__ __forceinline__ unsigned long long composite(const float4 *lds, uint6
     return cmc;
 }
 
-// One wave per 8x8 pixel block of a tile.  Records are staged in LDS, up to 64 at a time;
+// LDS written by other lanes of the wave is read after this, and the other way round.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One wave per 8x8 pixel block of a tile (SHARE: four of them a block).  Records are staged in LDS, up to 64 at a time;
 // each lane builds the mask of those that cover its pixel and composites them front to
 // back until its transmittance would drop below T_min; a wave whose 64 pixels all stopped
 // is done.
@@ -752,11 +760,16 @@ __device__ __forceinline__ unsigned long long composite(const float4 *lds, uint6
 // staged batch, and that is shorter for 64 records at once than for three times 20.  16x16
 // tiles against one block of four waves that shared the staged list: 20 sun maps of 1M
 // surfels 2175 -> 1578 us, three ~530^2 views of 150k surfels 141 -> 129 us.
+// SHARE: the blocks of a tile drift apart, and each then reads the tile's boxes from beyond L2 on its
+// own (5M surfels in 1024^2 maps: 67 GB a launch against the 18 of a shared read).  Four waves
+// of one block, for 16x16 pixels, read a quarter of the boxes each, test them for all four, and
+// meet at a barrier every 256 records: slower while lists are short, for a block then holds its
+// place until its longest wave ends, faster where they are long (9.9 -> 8.0 ms there).
 // The loop over a lane's own mask diverges on purpose: a uniform loop (idle lanes on a zeroed
 // slot, work counters in scalar registers) issues 8 % fewer VALU instructions and runs 3-8 %
 // longer, since idle lanes then read LDS too.
-template <int TS, bool DEPTH_ONLY, bool HAS_VIS, bool DIST, bool FILT>
-__global__ __launch_bounds__(64) void k_raster_fwd(
+template <int TS, bool DEPTH_ONLY, bool HAS_VIS, bool DIST, bool FILT, bool SHARE>
+__global__ __launch_bounds__(SHARE ? 256 : 64) void k_raster_fwd(
     int32_t nv, const ViewDesc *__restrict__ views, int32_t ntiles, const uint32_t *__restrict__ ranges,
     const uint32_t *__restrict__ lists, const float4 *__restrict__ rec, int64_t n,
     RasterConsts rc, const float *__restrict__ colC, const float *__restrict__ colc,
@@ -772,11 +785,16 @@ __global__ __launch_bounds__(64) void k_raster_fwd(
     // composited (the backward walks only those)
     constexpr bool CM = !DEPTH_ONLY;
     constexpr int RS = DEPTH_ONLY ? kSunRecStride4 : kRecStride4;   // record slot
-    __shared__ float4 lds[kFwdSlots * (DEPTH_ONLY ? 3 : 5)];
-    // blocks go round-robin to the 8 XCDs: the SUB blocks of a tile stay on the tile's XCD
+    constexpr int NW = SHARE ? 4 : 1, REG = SUB / NW;           // waves a block, blocks a tile
+    constexpr int SLOTS = kFwdSlots * (DEPTH_ONLY ? 3 : 5);
+    __shared__ float4 lds_all[NW * SLOTS];
+    const int wv = SHARE ? (int)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+    float4 *const lds = lds_all + wv * SLOTS;
+    // blocks go round-robin to the 8 XCDs: the blocks of a tile stay on the tile's XCD
     const int b = (int)blockIdx.x;
-    const int vb = SUB == 1 ? b : 8 * (b / (8 * SUB)) + b % 8;
-    const int sub = SUB == 1 ? 0 : (b / 8) % SUB;
+    const int vb = REG == 1 ? b : 8 * (b / (8 * REG)) + b % 8;
+    const int reg = REG == 1 ? 0 : (b / 8) % REG;
+    const int sub = SHARE ? (2 * (reg >> 1) + (wv >> 1)) * WPR + 2 * (reg & 1) + (wv & 1) : reg;
     if (vb >= ntiles) return;
     // sun maps are equal in size and even in work: one contiguous run of tiles per XCD
     const int tile = rc.torder ? (int)rc.torder[vb] : xcd_tile<!DEPTH_ONLY>(vb, ntiles);
@@ -784,7 +802,7 @@ __global__ __launch_bounds__(64) void k_raster_fwd(
     const ViewDesc vd = views[v];
     const int lt = tile - vd.tile_off;
     const int tx = lt % vd.tiles_x, ty = lt / vd.tiles_x;
-    const int lane = threadIdx.x;
+    const int lane = SHARE ? threadIdx.x & 63 : threadIdx.x;
     const int wx0 = tx * TS + (sub % WPR) * 8, wy0 = ty * TS + (sub / WPR) * 8;
     const int px = wx0 + (lane & 7), py = wy0 + (lane >> 3);
     const bool inside = px < vd.W && py < vd.H;
@@ -849,35 +867,86 @@ __global__ __launch_bounds__(64) void k_raster_fwd(
         if (CM && cmask && wcur >= 0) word_at[(size_t)wcur * NT] = wacc;
     } else {
         // staged positions of up to 64 consecutive words of the list, one mask each
-        __shared__ unsigned long long segs[CM ? 64 : 1];
-        __shared__ float2 boxes[64];
+        __shared__ unsigned long long segs_all[CM ? NW * 64 : 1];
+        __shared__ float2 boxes_all[NW * 64];
+        unsigned long long *const segs = segs_all + (CM ? wv * 64 : 0);
+        float2 *const boxes = boxes_all + wv * 64;
+        // SHARE: four words of the list at a time, one read by each wave: their entries, which
+        // records meet which wave's block, which waves are done; two buffers, one barrier
+        __shared__ uint32_t entries[2][NW * 64];
+        __shared__ unsigned long long meet[2][NW][4];
+        __shared__ int over[2][4];
         const int nw = (int)((end - start + 63) >> 6);
+        const int rx0 = wx0 - 8 * (wv & 1), ry0 = wy0 - 8 * (wv >> 1);   // the waves' 16x16 pixels
         auto entry = [&](int w) {                 // the lane's list entry in word w (0 past the end)
             const uint32_t k = start + 64u * (uint32_t)w + (uint32_t)lane;
             return k < end ? lists[k] : 0u;
         };
         auto slot = [&](uint32_t idx) { return recv + (size_t)min(idx, (uint32_t)(n - 1)) * RS; };
-        // heads (box and centre) of word wq + 1, list entries of word wq + 2
-        uint32_t idx_h = nw > 0 ? entry(0) : 0u, idx_n = nw > 1 ? entry(1) : 0u;
+        // heads of the wave's next word, list entries of the one after it
+        uint32_t idx_h = wv < nw ? entry(wv) : 0u, idx_n = wv + NW < nw ? entry(wv + NW) : 0u;
         float4 head = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (nw > 0) head = slot(idx_h)[0];
+        auto head_of = [&](uint32_t idx) {
+            if constexpr (SHARE) {
+                const float2 b = *reinterpret_cast<const float2 *>(slot(idx));
+                return make_float4(b.x, b.y, 0.f, 0.f);
+            } else
+                return slot(idx)[0];
+        };
+        if (wv < nw) head = head_of(idx_h);
+        // Every wave of the block calls this for words NW * g .. NW * g + NW - 1, g = 0, 1, ..., also
+        // when its own pixels have stopped, until the list ends or all waves say that they have.
+        [[maybe_unused]] auto group = [&](int g, bool stopped) {
+            const int bf = g & 1, w = NW * g + wv;
+            const int x = __float_as_int(head.x), y = __float_as_int(head.y);
+            const int x0 = (x << 16) >> 16, x1 = x >> 16, y0 = (y << 16) >> 16, y1 = y >> 16;
+            const bool in = w < nw && start + 64u * (uint32_t)w + (uint32_t)lane < end;
+            const bool cl = in && x0 <= rx0 + 7 && x1 >= rx0, cr = in && x0 <= rx0 + 15 && x1 >= rx0 + 8;
+            const bool rl = y0 <= ry0 + 7 && y1 >= ry0, rr = y0 <= ry0 + 15 && y1 >= ry0 + 8;
+            const uint64_t m0 = __ballot(cl && rl), m1 = __ballot(cr && rl);
+            const uint64_t m2 = __ballot(cl && rr), m3 = __ballot(cr && rr);
+            entries[bf][wv * 64 + lane] = idx_h;
+            if (lane == 0) {
+                unsigned long long *const mw = meet[bf][wv];
+                mw[0] = m0; mw[1] = m1; mw[2] = m2; mw[3] = m3;
+                over[bf][wv] = stopped;
+            }
+            idx_h = idx_n;
+            if (w + NW < nw) head = head_of(idx_h);
+            if (w + 2 * NW < nw) idx_n = entry(w + 2 * NW);
+            __syncthreads();
+            return (over[bf][0] & over[bf][1] & over[bf][2] & over[bf][3]) != 0;
+        };
         int wq = -1, staged = 0, nseg = 0, w0 = 0;
         uint64_t U = 0;                           // records of word wq still to stage (uniform)
         for (;;) {
             if (U == 0 && ++wq < nw) {
-                const int x = __float_as_int(head.x), y = __float_as_int(head.y);
-                const bool meets = ((x << 16) >> 16) <= wx0 + 7 && (x >> 16) >= wx0 &&
-                                   ((y << 16) >> 16) <= wy0 + 7 && (y >> 16) >= wy0 &&
-                                   start + 64u * (uint32_t)wq + (uint32_t)lane < end;
-                U = __ballot(meets);
-                if (meets) {
-                    const float4 *src = slot(idx_h);
-                    q0 = head; q1 = src[1]; q2 = src[2]; q3 = src[3];
-                    if (!DEPTH_ONLY) { q4 = src[4]; q5 = src[5]; }
+                if constexpr (SHARE) {
+                    if (wq % NW == 0) group(wq / NW, false);
+                    const int bf = (wq / NW) & 1;
+                    const unsigned long long mm = meet[bf][wq % NW][wv];
+                    U = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(mm >> 32)) << 32) |
+                        (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)mm);
+                    if ((U >> lane) & 1ull) {
+                        const float4 *src = slot(entries[bf][(wq % NW) * 64 + lane]);
+                        q0 = src[0]; q1 = src[1]; q2 = src[2]; q3 = src[3];
+                        if (!DEPTH_ONLY) { q4 = src[4]; q5 = src[5]; }
+                    }
+                } else {
+                    const int x = __float_as_int(head.x), y = __float_as_int(head.y);
+                    const bool meets = ((x << 16) >> 16) <= wx0 + 7 && (x >> 16) >= wx0 &&
+                                       ((y << 16) >> 16) <= wy0 + 7 && (y >> 16) >= wy0 &&
+                                       start + 64u * (uint32_t)wq + (uint32_t)lane < end;
+                    U = __ballot(meets);
+                    if (meets) {
+                        const float4 *src = slot(idx_h);
+                        q0 = head; q1 = src[1]; q2 = src[2]; q3 = src[3];
+                        if (!DEPTH_ONLY) { q4 = src[4]; q5 = src[5]; }
+                    }
+                    idx_h = idx_n;
+                    if (wq + 1 < nw) head = head_of(idx_h);
+                    if (wq + 2 < nw) idx_n = entry(wq + 2);
                 }
-                idx_h = idx_n;
-                if (wq + 1 < nw) head = slot(idx_h)[0];
-                if (wq + 2 < nw) idx_n = entry(wq + 2);
                 if (U == 0) {
                     if (!CM) continue;
                     if (lane == 0) segs[nseg] = 0ull;
@@ -900,7 +969,7 @@ __global__ __launch_bounds__(64) void k_raster_fwd(
                 }
                 if (staged < 64 && (!CM || nseg < 64)) continue;
             }
-            __syncthreads();
+            wave_sync();
             unsigned long long cmc = 0ull;
             if (staged > 0) {
                 const float2 box = boxes[lane < staged ? lane : 0];
@@ -932,10 +1001,13 @@ __global__ __launch_bounds__(64) void k_raster_fwd(
                 w0 += U != 0 ? nseg - 1 : nseg;   // a word cut short goes on in the next batch
                 nseg = 0;
             }
-            __syncthreads();
+            wave_sync();
             staged = 0;
             if (wq >= nw || all_done) break;
         }
+        if constexpr (SHARE)
+            for (int g = wq / NW + 1; NW * g < nw; ++g)
+                if (group(g, true)) break;
     }
 #undef SS_FETCH_FWD
     {
@@ -992,6 +1064,13 @@ static int64_t raster_blocks(int sub, int32_t ntiles)
     return sub == 1 ? ntiles : ((int64_t)ntiles + 7) / 8 * 8 * sub;
 }
 
+// Depth-only maps of larger tiles with at least this many surfels per tile take the blocks whose
+// waves read the list together (SHARE).  20 sun maps, one wave a block -> shared, by surfels
+// per tile: 16x16 tiles 244: kernel 1580 -> 2012 us; whole pass 488: 1600 -> 1738, 684: 2253 -> 2255, 879:
+// 2923 -> 2765, 1172: 3927 -> 3614; 32x32 tiles 293: 1637 -> 1840, 977: 4140 -> 3893, 1172: 1355 -> 1304, 4688:
+// 7527 -> 4141.
+constexpr int64_t kShareSurfels = 768;
+
 template <int TS, bool DO, bool HV>
 static void launch_fwd_t(int32_t ntiles, hipStream_t st, int32_t nv,
                          const ViewDesc *views, const uint32_t *ranges, const uint32_t *lists,
@@ -1002,17 +1081,21 @@ static void launch_fwd_t(int32_t ntiles, hipStream_t st, int32_t nv,
                          unsigned long long *cmask, const DistArgs *dist)
 {
     const DistArgs da = dist ? *dist : DistArgs{0.f, nullptr, nullptr, nullptr, 0};
-    const dim3 grid((unsigned)raster_blocks(ts_sub(TS), ntiles));
-#define SS_FWD_LAUNCH(DIST_, FILT_)                                                                    \
-    hipLaunchKernelGGL((k_raster_fwd<TS, DO, HV, DIST_, FILT_>), grid, dim3(64), 0, st, nv, views,     \
+    const bool share = DO && TS > 8 && n * nv >= kShareSurfels * ntiles;
+    const dim3 grid((unsigned)raster_blocks(ts_sub(TS) / (share ? 4 : 1), ntiles)), block(share ? 256 : 64);
+#define SS_FWD_LAUNCH(DIST_, FILT_, SHARE_)                                                            \
+    hipLaunchKernelGGL((k_raster_fwd<TS, DO, HV, DIST_, FILT_, SHARE_>), grid, block, 0, st, nv, views, \
                        ntiles, ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc, colC, colc, \
                        amb, sun, image, A, V, D, N, T, last, stats, cmask, da)
-    if (!DO && dist) {
-        if (rc.lowpass_mode == 0) SS_FWD_LAUNCH(!DO, true);
-        else SS_FWD_LAUNCH(!DO, false);
+    if (share) {
+        if (rc.lowpass_mode == 0) SS_FWD_LAUNCH(false, true, (DO && TS > 8));
+        else SS_FWD_LAUNCH(false, false, (DO && TS > 8));
+    } else if (!DO && dist) {
+        if (rc.lowpass_mode == 0) SS_FWD_LAUNCH(!DO, true, false);
+        else SS_FWD_LAUNCH(!DO, false, false);
     } else {
-        if (rc.lowpass_mode == 0) SS_FWD_LAUNCH(false, true);
-        else SS_FWD_LAUNCH(false, false);
+        if (rc.lowpass_mode == 0) SS_FWD_LAUNCH(false, true, false);
+        else SS_FWD_LAUNCH(false, false, false);
     }
 #undef SS_FWD_LAUNCH
 }

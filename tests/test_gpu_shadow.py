@@ -92,3 +92,21 @@ def test_plain_pass_agrees_with_heightfield_ground_truth():
               f"{agree[conf].mean():.5f}", flush=True)
         assert agree[conf].all(), (v, np.flatnonzero(conf & ~agree)[:10])
     assert dark > 1500
+
+
+@pytest.mark.parametrize("ts,n", [(16, 12_287), (16, 12_288), (16, 40_000), (32, 3_071), (32, 3_072), (32, 40_000)])
+def test_sun_maps_of_larger_tiles_around_the_line_of_shared_lists(ts, n):
+    """A texel composites the same surfels in the same order at every tile size, so maps and
+    visibility equal those of 8x8 tiles bit for bit: 50^2 maps (ragged tiles) on both sides of 768
+    surfels per tile, and with lists much longer than the texels' pixels need."""
+    sc = synth.make_scene(synth.tiny(n_surfels=n, views=((40, 40), (31, 22)), seed=9))
+    S = 50
+    got = []
+    for t in (8, ts):
+        plan, surf, views = make_plan(sc, ts=t, S=S, with_sun=True)
+        D = torch.full((2, S, S), float("nan"), device="cuda")
+        vis = plan.shadow(surf, views, sun_depth=D)
+        got.append((to_np(D), to_np(vis)))
+    assert np.isfinite(got[0][0]).all()
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    np.testing.assert_array_equal(got[0][1], got[1][1])
