@@ -656,13 +656,21 @@ struct PixelSums {
 // (40 views of 2M surfels: 8.19 -> 7.85 ms, their sun maps 4.46 -> 4.35 ms).
 constexpr int kFwdSlots = 64;
 
-template <bool DEPTH_ONLY>
+template <bool DEPTH_ONLY, bool FILT>
 __device__ __forceinline__ void stage_record(float4 *lds, int slot, float4 r0, float4 r1, float4 r2,
                                              float4 r3, float4 r4, float4 r5)
 {
-    const float none = r1.z > 0.f ? __uint_as_float(0x7FC00000u) : 0.f;
+    bool ell = !(r1.z > 0.f);
+    // Q beyond FP32: Q delta is infinite or, at the centre, NaN, and with no low-pass branch to
+    // take instead the pair has no weight at any pixel.  Staged without an ellipse and with no
+    // opacity its depth stays finite as well.
+    if (!FILT && !(isfinite(r2.x) && isfinite(r2.y) && isfinite(r2.z) && isfinite(r2.w))) {
+        ell = false;
+        r3.x = 0.f;
+    }
+    const float none = __uint_as_float(0x7FC00000u);
     lds[slot] = make_float4(r0.z, r0.w, r1.x, r1.y);
-    lds[kFwdSlots + slot] = r1.z > 0.f ? make_float4(none, none, none, none) : r2;
+    lds[kFwdSlots + slot] = ell ? r2 : make_float4(none, none, none, none);
     lds[2 * kFwdSlots + slot] = r3;
     if (!DEPTH_ONLY) { lds[3 * kFwdSlots + slot] = r4; lds[4 * kFwdSlots + slot] = r5; }
 }
@@ -832,7 +840,7 @@ __global__ __launch_bounds__(SHARE ? 256 : 64) void k_raster_fwd(
         for (uint32_t b0 = start; b0 < end; b0 += B) {
             const int nb = (int)min((uint32_t)B, end - b0);
             __syncthreads();
-            if (lane < nb) stage_record<DEPTH_ONLY>(lds, lane, q0, q1, q2, q3, q4, q5);
+            if (lane < nb) stage_record<DEPTH_ONLY, FILT>(lds, lane, q0, q1, q2, q3, q4, q5);
             const float box_x = q0.x, box_y = q0.y;
             __syncthreads();
             const uint32_t b1 = b0 + B, b2 = b1 + B;
@@ -959,7 +967,7 @@ __global__ __launch_bounds__(SHARE ? 256 : 64) void k_raster_fwd(
                 const uint64_t take = __ballot(sel);
                 U &= ~take;
                 if (sel) {
-                    stage_record<DEPTH_ONLY>(lds, k, q0, q1, q2, q3, q4, q5);
+                    stage_record<DEPTH_ONLY, FILT>(lds, k, q0, q1, q2, q3, q4, q5);
                     boxes[k] = make_float2(q0.x, q0.y);
                 }
                 staged += (int)__popcll(take);

@@ -587,3 +587,30 @@ def test_backward_writes_gradients_directly_and_by_rows():
             assert not b[-1].any()
             b = b[:-1]
         assert rel_err(b, a) <= ATOMIC_ORDER_TOL, k
+
+
+@pytest.mark.parametrize("ts", [8, 16, 32])
+def test_surfel_too_small_for_fp32_without_the_low_pass_floor(ts):
+    """A frame whose inverse leaves FP32 (Q infinite), centred on a pixel's centre, so that Q
+    delta is NaN there.  Without the low-pass floor such a pair has no weight, and no output may
+    see it: the render equals the one in which the surfel is transparent."""
+    f = lambda a: torch.as_tensor(np.ascontiguousarray(a, np.float32), device="cuda")
+    F = np.zeros((1, 2, 4), np.float32)
+    F[0, 0, 0] = F[0, 1, 1] = 0.125                  # exact: both centres are at (4.5, 4.5) px
+    eye = np.tile(np.eye(3)[None], (2, 1, 1))
+    v = ss.ViewTensors(np.array([24], np.int32), np.array([17], np.int32), f(F), 10.0)
+    res = []
+    for o in (0.9, 0.0):
+        surf = ss.SurfelTensors(f([[36, 36, 3], [36, 36, 0]]), f(eye[:, 0]), f(eye[:, 1]),
+                                f([[2e-38, 2e-38], [16, 16]]), f([o, 0.8]), f([[1, 0, 0], [0, 1, 0]]))
+        plan = ss.Plan(context(), 2, v.width, v.height,
+                       ss.default_settings(tile_size=ts, batch_depth=64, lowpass_mode=1))
+        plan.ensure_capacity(surf, v)
+        res.append({**plan.forward(surf, v, depth_scale=0.1), **{k + "_plain": t for k, t in plan.forward(surf, v).items()}})
+        if o:
+            rec = plan.debug_binning(0, records=True)["records"][0, 0]
+            assert np.isinf(rec[8]) and np.isinf(rec[11]) and np.array_equal(rec[2:6], [4.5, 4.5, 0, 0])
+    for k in res[0]:
+        if not k.startswith("last"):                 # positions count the opaque one's list entry
+            same = torch.equal(res[0][k], res[1][k]) and bool(torch.isfinite(res[0][k]).all())
+            assert same, k
