@@ -1443,15 +1443,15 @@ __device__ __forceinline__ void pair_gradients(const PairEval &e, bool contrib, 
 // 4x4 quadrant of the wave's 8x8 pixels and walks, back to front, the staged records
 // whose box meets the quadrant (4 ballots per chunk of 64).  A lane takes part in a pair
 // only where the forward composited it - the forward's box and FP32 alpha tests and the
-// pixel's `last` - so the walk revisits exactly the forward's pairs.  (Only for 16x16 and
-// 32x32 tiles on a workspace laid out for smaller ones, without room for the forward's
-// contributor masks; with them the kernel below runs.)
+// pixel's `last` - so the walk revisits exactly the forward's pairs.  (Only on a workspace
+// without room for the forward's contributor masks at the plan's tile size: one bound with
+// less than the full size, or at another tile size; with them the kernel below runs.)
 // The 16 record-gradient values are reduced within the row and added with one atomic per
 // lane, so one instruction carries the sums of up to four records.
 // The colour adjoint of Eq. image_formation runs first per pixel; its 15 per-view
 // sums are reduced per tile into colour_partials.
 template <int TS, bool HAS_VIS, bool DIST>
-__global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(4))) void k_raster_bwd(
+__global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 8 ? 5 : 4))) void k_raster_bwd(
     int32_t nv, const ViewDesc *__restrict__ views, const uint32_t *__restrict__ ranges,
     const uint32_t *__restrict__ lists, const float4 *__restrict__ rec, int64_t n,
     RasterConsts rc, const float *__restrict__ colC, const float *__restrict__ colc,
@@ -1962,10 +1962,9 @@ static void launch_bwd_d(size_t lds, hipStream_t st, int32_t ntiles, int32_t nv,
 #undef SS_BWD_LAUNCH
         return;
     }
-    if constexpr (TS != 8)     // 8x8 tiles always have their masks
-        hipLaunchKernelGGL((k_raster_bwd<TS, HV, DIST>), dim3((unsigned)ntiles), dim3(TS * TS), lds, st, nv,
-                           views, ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc, colC, colc,
-                           amb, A, V, T, last, dI, dD, dN, recgrad, cp, da);
+    hipLaunchKernelGGL((k_raster_bwd<TS, HV, DIST>), dim3((unsigned)ntiles), dim3(TS * TS), lds, st, nv,
+                       views, ranges, lists, reinterpret_cast<const float4 *>(rec), n, rc, colC, colc,
+                       amb, A, V, T, last, dI, dD, dN, recgrad, cp, da);
 }
 
 template <int TS, bool HV>
@@ -1999,7 +1998,6 @@ hipError_t launch_raster_bwd(int ts, bool has_vis, int32_t total_tiles, int32_t 
     if (total_tiles <= 0) return hipSuccess;
     const size_t lds = (size_t)min(rc.batch, ts * ts) * (kRecVec4 * sizeof(float4) + sizeof(uint32_t)) +
                        (size_t)(ts * ts / 64) * 16 * sizeof(float) + sizeof(int);
-    if (ts == 8 && !cmask) return hipErrorInvalidValue;
 #define SS_BWD(TS_)                                                                          \
     if (ts == TS_) {                                                                         \
         if (has_vis)                                                                         \

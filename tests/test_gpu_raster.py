@@ -262,6 +262,48 @@ def test_workspace_of_smaller_tiles_is_enough_for_larger_ones():
     check_backward(sc, plan, surf, views, out, oracle.forward(sc, oracle_settings(ts=16)))
 
 
+def bind_smallest(plan):
+    """Binds the plan's workspace again with the fewest bytes that are accepted."""
+    caps = plan.cap_main, plan.cap_sun
+    lo, hi = 0, plan.workspace_size(*caps)
+    bind = lambda n: _lib.call("ss_plan_bind_workspace", plan.handle, C.c_void_p(plan.workspace.data_ptr()), n, *caps)
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        try:
+            bind(mid)
+            hi = mid
+        except ss.SatSplatError:
+            lo = mid
+    bind(hi)
+    return hi
+
+
+@pytest.mark.parametrize("bound_at", [16, 32])
+def test_8x8_tiles_on_a_workspace_bound_without_masks(bound_at):
+    """The fewest bytes that 16x16 or 32x32 tiles accept have no room for contributor masks at
+    8x8 either: forward, backward, a step and the autotuner run all the same after the switch."""
+    sc = scene_tiny(seed=21)
+    plan, surf, views = make_plan(sc, ts=bound_at)
+    plan.bind(16 * plan.cap_main, 0)                  # room for the 8x8 pairs
+    assert bind_smallest(plan) < plan.workspace_size(plan.cap_main, 0)
+    plan.set_settings(ss.default_settings(tile_size=8, batch_depth=64))
+    m, _ = plan.count_pairs(surf, views)
+    assert m <= plan.cap_main
+    out = plan.forward(surf, views)
+    check_backward(sc, plan, surf, views, out, oracle.forward(sc, oracle_settings(ts=8)))
+    up = [torch.as_tensor(x, device="cuda") for x in synth.upstream_grads(sc)]
+    ref = {k: to_np(t) for k, t in plan.backward(surf, views, out, *up).items()}
+    bufs = ss.StepBuffers(surf.mean.shape[0], views.width, views.height, with_sun=False, upstream=up)
+    ss.step(plan, surf, views, bufs)
+    for k in GRAD_KEYS:
+        assert rel_err(to_np(bufs.grads[k]), ref[k]) < ATOMIC_ORDER_TOL, k
+    table = (C.c_double * 36)()
+    best, ms, sv, vv, io = _lib.RasterSettings(), C.c_double(), surf.c(), views.c(), bufs.c()
+    _lib.call("ss_autotune", plan.handle, C.byref(sv), C.byref(vv), C.byref(io), 1, C.byref(best), C.byref(ms),
+              C.cast(table, C.c_void_p), C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert ms.value > 0 and sum(x > 0 for x in table[2::3]) == 10
+
+
 @pytest.mark.parametrize("ts,n", [(16, 6000), (32, 6000), (32, 700)])
 def test_blocks_of_a_tile_that_see_little_of_its_list(ts, n):
     """All surfels in a few pixels: most 8x8 blocks of a tile stage nothing from a list of more
