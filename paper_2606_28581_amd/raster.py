@@ -112,17 +112,20 @@ class Plan:
         self.n = int(n)
         self.width = np.asarray(width, np.int32)
         self.height = np.asarray(height, np.int32)
-        nv = len(self.width)
-        w = (C.c_int32 * nv)(*[int(x) for x in self.width])
-        h = (C.c_int32 * nv)(*[int(x) for x in self.height])
-        ph = C.c_void_p()
-        call("ss_plan_create", ctx.handle, self.n, nv, w, h, C.byref(self.settings), C.byref(ph))
-        self.handle = ph
+        self.handle = self._create(self.settings)
         self.cap_main = -1
         self.cap_sun = -1
         self.workspace = None
         self.regrows = 0
         self.bind(0, 0)
+
+    def _create(self, settings: RasterSettings):
+        nv = len(self.width)
+        w = (C.c_int32 * nv)(*[int(x) for x in self.width])
+        h = (C.c_int32 * nv)(*[int(x) for x in self.height])
+        ph = C.c_void_p()
+        call("ss_plan_create", self.ctx.handle, self.n, nv, w, h, C.byref(settings), C.byref(ph))
+        return ph
 
     def __del__(self):
         if getattr(self, "handle", None) and _lib._lib is not None:
@@ -134,17 +137,41 @@ class Plan:
         self.settings = settings
 
     def workspace_size(self, main_pairs: int, sun_pairs: int) -> int:
+        return self._size(self.handle, main_pairs, sun_pairs)
+
+    @staticmethod
+    def _size(handle, main_pairs: int, sun_pairs: int) -> int:
         b = C.c_size_t()
-        call("ss_plan_workspace_size", self.handle, int(main_pairs), int(sun_pairs), C.byref(b))
+        call("ss_plan_workspace_size", handle, int(main_pairs), int(sun_pairs), C.byref(b))
         return b.value
+
+    def _size_at(self, tile_size: int, main_pairs: int, sun_pairs: int) -> int:
+        """workspace_size at another tile size (of a plan of its own: it allocates nothing)."""
+        st = RasterSettings.from_buffer_copy(self.settings)
+        st.tile_size = tile_size
+        h = self._create(st)
+        try:
+            return self._size(h, main_pairs, sun_pairs)
+        finally:
+            _lib.load().ss_plan_destroy(h)
 
     def bind(self, main_pairs: int, sun_pairs: int):
         if main_pairs == self.cap_main and sun_pairs == self.cap_sun:
             return
-        nbytes = self.workspace_size(main_pairs, sun_pairs)
+        self._bind(main_pairs, sun_pairs, self.workspace_size(main_pairs, sun_pairs))
+
+    def _bind(self, main_pairs: int, sun_pairs: int, nbytes: int):
         self.workspace = None
-        self.workspace = torch.empty(max(nbytes, 256), dtype=torch.uint8,
-                                     device=f"cuda:{self.ctx.device}")
+        f = lambda k: torch.empty(max(k, 256), dtype=torch.uint8, device=f"cuda:{self.ctx.device}")
+        try:
+            self.workspace = f(nbytes)
+        except torch.OutOfMemoryError:
+            # 16x16 and 32x32 tiles also run without room for contributor masks, most of the
+            # size per pair: what 8x8 tiles take is enough
+            least = self._size_at(8, main_pairs, sun_pairs)
+            if least >= nbytes:
+                raise
+            self.workspace = f(least)
         call("ss_plan_bind_workspace", self.handle, C.c_void_p(self.workspace.data_ptr()),
              self.workspace.numel(), int(main_pairs), int(sun_pairs))
         self.cap_main, self.cap_sun = int(main_pairs), int(sun_pairs)

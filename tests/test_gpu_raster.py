@@ -304,6 +304,29 @@ def test_8x8_tiles_on_a_workspace_bound_without_masks(bound_at):
     assert ms.value > 0 and sum(x > 0 for x in table[2::3]) == 10
 
 
+@pytest.mark.parametrize("ts", [16, 32])
+def test_workspace_without_masks_where_the_full_one_does_not_fit(ts, monkeypatch):
+    """A card without room for the full size of 16x16 or 32x32 tiles still takes the plan."""
+    sc = scene_tiny(seed=23, n=3000)
+    plan, surf, views = make_plan(sc, ts=ts)
+    cap, full = plan.cap_main, plan.workspace.numel()
+    empty = torch.empty
+
+    def small_card(*size, **kw):
+        if kw.get("dtype") == torch.uint8 and size[0] >= full:
+            raise torch.OutOfMemoryError("no room")
+        return empty(*size, **kw)
+
+    monkeypatch.setattr(torch, "empty", small_card)
+    plan.bind(0, 0)
+    plan.bind(cap, 0)
+    assert plan.workspace.numel() < full
+    out = plan.forward(surf, views)
+    check_backward(sc, plan, surf, views, out, oracle.forward(sc, oracle_settings(ts=ts)))
+    with pytest.raises(torch.OutOfMemoryError):
+        plan.bind(64 * cap, 0)
+
+
 @pytest.mark.parametrize("ts,n", [(16, 6000), (32, 6000), (32, 700)])
 def test_blocks_of_a_tile_that_see_little_of_its_list(ts, n):
     """All surfels in a few pixels: most 8x8 blocks of a tile stage nothing from a list of more
