@@ -121,19 +121,25 @@ ss_status ss_plan_create(ss_context *ctx, int64_t n_surfels, int32_t n_views,
                          const ss_raster_settings *settings, ss_plan **out);
 ss_status ss_plan_destroy(ss_plan *plan);
 
-/* Change tile size / batch depth / thresholds of an existing plan (same workspace;
- * the workspace is always sized for the smallest tile size). */
+/* Change tile size / batch depth / thresholds of an existing plan (same workspace and
+ * capacities; every tile size runs on it).  Only the contributor masks that let the
+ * backward skip its box test depend on the tile size: they are used where the bound bytes
+ * hold the size that ss_plan_workspace_size gives for the new settings.  Where they do not,
+ * the gradients are the same and the backward is slower; bind that size again. */
 ss_status ss_plan_set_settings(ss_plan *plan, const ss_raster_settings *settings);
 
 /* Workspace bytes for capacities of `main_pairs` (tile, surfel) pairs over all main
- * views and `sun_pairs` over all sun views.  Capacities may be 0 (then only
- * ss_count_pairs may run). */
+ * views and `sun_pairs` over all sun views, at the plan's tile size.  Capacities may be 0
+ * (then only ss_count_pairs may run). */
 ss_status ss_plan_workspace_size(ss_plan *plan, int64_t main_pairs, int64_t sun_pairs,
                                  size_t *bytes);
 
 /* Bind caller-owned device memory (256-byte aligned, >= the queried size) as the
  * plan's workspace.  The plan keeps the binning of the last forward in it for the
- * backward, so the workspace must stay alive and untouched between the two. */
+ * backward, so the workspace must stay alive and untouched between the two.  16x16 and
+ * 32x32 tiles also accept less, down to the size without contributor masks (the size of
+ * 8x8 tiles is enough); 8x8 tiles do not.  Bytes beyond the queried size are kept for the
+ * masks of larger tiles. */
 ss_status ss_plan_bind_workspace(ss_plan *plan, void *workspace, size_t bytes,
                                  int64_t main_pairs, int64_t sun_pairs);
 
@@ -385,7 +391,9 @@ ss_status ss_graph_destroy(ss_graph *graph);
  * the fastest; *best receives those settings, best_ms its step time.  Candidates whose
  * pairs exceed the bound capacities are skipped (bind capacities counted with
  * tile_size 8, the largest pair count, to try all); so are batch depths above the tile's
- * thread count (tile_size^2: one staged record per thread).  table (host, may be NULL)
+ * thread count (tile_size^2: one staged record per thread).  Tile sizes whose contributor
+ * masks do not fit the bound bytes are timed with the box-test backward (see
+ * ss_plan_set_settings).  table (host, may be NULL)
  * receives 12 x 3 doubles: tile, batch, ms (ms < 0: skipped). */
 ss_status ss_autotune(ss_plan *plan, const ss_surfels *s, const ss_views *v,
                       const ss_step_io *io, int32_t reps, ss_raster_settings *best,

@@ -189,7 +189,7 @@ static int64_t max_view_tiles(const std::vector<ViewDesc> &views)
     return m;
 }
 
-static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs, bool masks = true)
+static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs)
 {
     Layout L{};
     size_t o = 0;
@@ -237,9 +237,6 @@ static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs, bool masks =
     L.inv_main = take(n * 4);
     L.inv_sun = take(n * 4);
     L.vis_rank = take(vn * 4);
-    // forward -> backward contributor masks at the current tile size
-    L.cmask_bytes = masks ? cmask_words(cm, p->tiles_main, p->st.tile_size) * 8 : 0;
-    L.cmask = take(L.cmask_bytes);
     // heavy-first raster dispatch orders and their per-XCD block counts
     L.torder_main = take((size_t)p->tiles_main_max * 4);
     L.torder_sun = take((size_t)p->tiles_sun_max * 4);
@@ -251,6 +248,10 @@ static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs, bool masks =
                                          l1_blocks(max_view_pixels(p))) * nv * 8);
     // chain sums of the backward's per-view reduction
     L.vr_parts = take(view_reduce_parts(p->nv) * 4);
+    // forward -> backward contributor masks at the current tile size.  They come last: a binding
+    // gives them whatever is left, so that a later tile size finds them wherever they fit
+    L.cmask_bytes = cmask_words(cm, p->tiles_main, p->st.tile_size) * 8;
+    L.cmask = take(L.cmask_bytes);
     L.total = o;
     return L;
 }
@@ -414,8 +415,9 @@ static ss_status bin_views(ss_plan *p, const ss_views *v, bool sun, const float 
     return SS_OK;
 }
 
-// Contributor masks: there is room for them unless the tile size grew since the workspace was
-// laid out, or it was bound with less than the full size (then the backward uses the box test).
+// Contributor masks at the current tile size, or NULL where the bound bytes leave no room for them:
+// the workspace was bound with less than the full size, or at a smaller tile size (then the backward
+// uses the box test).
 static unsigned long long *cmask_ptr(const ss_plan *p)
 {
     if (p->L.cmask_bytes < cmask_words(p->cap_main, p->tiles_main, p->st.tile_size) * 8) return nullptr;
@@ -632,8 +634,9 @@ ss_status ss_plan_bind_workspace(ss_plan *p, void *workspace, size_t bytes, int6
         return fail(SS_ERR_INVALID_ARG, "pair capacity must be in [0, 2^32)");
     Layout L = make_layout(p, main_pairs, sun_pairs);
     // 16x16 and 32x32 tiles can do without contributor masks
-    if (bytes < L.total && p->st.tile_size != 8) L = make_layout(p, main_pairs, sun_pairs, false);
-    if (bytes < L.total) return fail(SS_ERR_CAPACITY, "workspace smaller than required");
+    if (bytes < (p->st.tile_size == 8 ? L.total : L.cmask))
+        return fail(SS_ERR_CAPACITY, "workspace smaller than required");
+    L.cmask_bytes = bytes - L.cmask;
     p->L = L;
     p->ws = reinterpret_cast<char *>(workspace);
     p->ws_bytes = bytes;

@@ -115,6 +115,7 @@ class Plan:
         self.handle = self._create(self.settings)
         self.cap_main = -1
         self.cap_sun = -1
+        self._bound_tile = 0
         self.workspace = None
         self.regrows = 0
         self.bind(0, 0)
@@ -156,9 +157,15 @@ class Plan:
             _lib.load().ss_plan_destroy(h)
 
     def bind(self, main_pairs: int, sun_pairs: int):
-        if main_pairs == self.cap_main and sun_pairs == self.cap_sun:
+        """Workspace for these capacities, and for the contributor masks of the present tile
+        size: a larger tile size than the one that was bound for needs more."""
+        same = main_pairs == self.cap_main and sun_pairs == self.cap_sun
+        if same and self.settings.tile_size <= self._bound_tile:
             return
-        self._bind(main_pairs, sun_pairs, self.workspace_size(main_pairs, sun_pairs))
+        nbytes = self.workspace_size(main_pairs, sun_pairs)
+        if same and nbytes <= self.workspace.numel():
+            return
+        self._bind(main_pairs, sun_pairs, nbytes)
 
     def _bind(self, main_pairs: int, sun_pairs: int, nbytes: int):
         self.workspace = None
@@ -175,6 +182,7 @@ class Plan:
         call("ss_plan_bind_workspace", self.handle, C.c_void_p(self.workspace.data_ptr()),
              self.workspace.numel(), int(main_pairs), int(sun_pairs))
         self.cap_main, self.cap_sun = int(main_pairs), int(sun_pairs)
+        self._bound_tile = self.settings.tile_size
 
     def count_pairs(self, s: SurfelTensors, v: ViewTensors):
         m = C.c_int64()
@@ -188,8 +196,7 @@ class Plan:
         m, sp = self.count_pairs(s, v)
         need_m = max(self.cap_main, int(np.ceil(m * slack)) + 1024) if m > self.cap_main else self.cap_main
         need_s = max(self.cap_sun, int(np.ceil(sp * slack)) + 1024) if sp > self.cap_sun else self.cap_sun
-        if need_m != self.cap_main or need_s != self.cap_sun:
-            self.bind(need_m, need_s)
+        self.bind(need_m, need_s)
         return m, sp
 
     def check(self):
@@ -406,14 +413,19 @@ def step(plan: "Plan", s: SurfelTensors, v: ViewTensors, bufs: StepBuffers):
 
 
 def autotune(plan: "Plan", s: SurfelTensors, v: ViewTensors, bufs: StepBuffers, reps: int = 3):
-    """Bind capacities for the largest pair count (tile 8), time all 12 candidates, leave
-    the plan on the fastest.  Returns (settings, ms, table)."""
+    """Bind capacities for the largest pair count (tile 8), time all 12 candidates, each with
+    room for its contributor masks, leave the plan on the fastest and on a workspace of its
+    size.  Returns (settings, ms, table)."""
     base = plan.settings
     probe = default_settings(**{k: getattr(base, k) for k, _ in RasterSettings._fields_
                                 if k != "struct_size"})
     probe.tile_size = 8
     plan.set_settings(probe)
     plan.ensure_capacity(s, v)
+    caps = plan.cap_main, plan.cap_sun
+    room = max(plan._size_at(t, *caps) for t in (8, 16, 32))
+    if room > plan.workspace.numel():
+        plan._bind(*caps, room)
     best = RasterSettings()
     ms = C.c_double()
     table = (C.c_double * 36)()
@@ -421,6 +433,8 @@ def autotune(plan: "Plan", s: SurfelTensors, v: ViewTensors, bufs: StepBuffers, 
     call("ss_autotune", plan.handle, C.byref(sc), C.byref(vc), C.byref(io), int(reps),
          C.byref(best), C.byref(ms), C.cast(table, C.c_void_p), _stream())
     plan.settings = best
+    if plan.workspace.numel() != plan.workspace_size(*caps):
+        plan._bind(*caps, plan.workspace_size(*caps))
     return best, ms.value, np.frombuffer(table, dtype=np.float64).reshape(12, 3).copy()
 
 

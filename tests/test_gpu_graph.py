@@ -10,6 +10,7 @@ import torch
 import oracle
 import synth
 import paper_2606_28581_amd as ss
+from paper_2606_28581_amd import _lib, raster
 from gpu_common import ATOMIC_ORDER_TOL, GRAD_KEYS, make_plan, oracle_settings, rel_err, to_np
 
 pytestmark = pytest.mark.gpu
@@ -98,3 +99,28 @@ def test_autotune_leaves_plan_on_a_candidate_that_keeps_parity():
                           zip(np.cumsum([0] + [w * h for w, h in zip(sc["width"], sc["height"])])[:-1],
                               sc["width"], sc["height"])])
     assert np.abs(to_np(bufs.out["image"])[ok3] - ref["image"][ok3]).max() < 1e-4
+
+
+def test_autotune_times_every_tile_size_with_room_for_its_masks(monkeypatch):
+    sc, plan, surf, views, bufs = setup(seed=24)
+    seen, raw = [], raster.call
+
+    def call(name, *args):
+        if name == "ss_autotune":
+            seen.append((plan.workspace.numel(), plan.cap_main, plan.cap_sun))
+        return raw(name, *args)
+
+    monkeypatch.setattr(raster, "call", call)
+    best, _, _ = ss.autotune(plan, surf, views, bufs, reps=1)
+    (bound, *caps), = seen
+    sizes = {}
+    for ts in (8, 16, 32):
+        st = _lib.RasterSettings.from_buffer_copy(best)
+        st.tile_size = ts
+        plan.set_settings(st)
+        sizes[ts] = plan.workspace_size(*caps)
+    plan.set_settings(best)
+    assert bound >= max(sizes.values())
+    assert plan.workspace.numel() == sizes[best.tile_size]
+    ss.step(plan, surf, views, bufs)
+    assert not plan.check()[0]

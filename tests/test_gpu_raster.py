@@ -327,6 +327,25 @@ def test_workspace_without_masks_where_the_full_one_does_not_fit(ts, monkeypatch
         plan.bind(64 * cap, 0)
 
 
+@pytest.mark.parametrize("ts", [16, 32])
+def test_capacity_after_a_change_of_tile_size_has_room_for_masks(ts):
+    sc = scene_tiny(seed=22, n=3000)
+    plan, surf, views = make_plan(sc, ts=8)
+    plan.set_settings(ss.default_settings(tile_size=ts, batch_depth=64))
+    plan.ensure_capacity(surf, views)
+    full = plan.workspace_size(plan.cap_main, plan.cap_sun)
+    assert plan.workspace.numel() >= full
+    out = plan.forward(surf, views)
+    check_backward(sc, plan, surf, views, out, oracle.forward(sc, oracle_settings(ts=ts)))
+    # and back: smaller tiles need less, nothing is bound again
+    ptr = plan.workspace.data_ptr()
+    plan.set_settings(ss.default_settings(tile_size=8, batch_depth=64))
+    plan.ensure_capacity(surf, views)
+    assert plan.workspace.data_ptr() == ptr
+    out = plan.forward(surf, views)
+    check_backward(sc, plan, surf, views, out, oracle.forward(sc, oracle_settings(ts=8)))
+
+
 @pytest.mark.parametrize("ts,n", [(16, 6000), (32, 6000), (32, 700)])
 def test_blocks_of_a_tile_that_see_little_of_its_list(ts, n):
     """All surfels in a few pixels: most 8x8 blocks of a tile stage nothing from a list of more
