@@ -250,6 +250,29 @@ def test_backward_of_a_small_and_of_a_large_launch(ts):
         assert rel_err(to_np(grads[1][k]), to_np(grads[0][k])) < 1e-3, k
 
 
+@pytest.mark.parametrize("ts,dist,mode", [(32, False, 0), (32, False, 1), (16, False, 1), (8, False, 1),
+                                          (8, True, 0), (16, True, 0), (32, True, 0)])
+def test_backward_of_a_small_and_of_a_large_launch_of_every_variant(ts, dist, mode):
+    """As above for 32x32 tiles, the distortion term and no low-pass floor."""
+    S, L = 64, 1048
+    small = scene_tiny(seed=19, views=((S, S),), n=800)
+    up = (*synth.upstream_grads(small), np.random.default_rng(8).normal(size=S * S).astype(np.float32))
+    grads = []
+    for side in (S, L):
+        sc = dict(small, width=np.array([side], np.int32), height=np.array([side], np.int32))
+        d = []
+        for x in up:
+            full = np.zeros((x.size // (S * S), side, side), np.float32)
+            full[:, :S, :S] = x.reshape(-1, S, S)
+            d.append(torch.as_tensor(full.reshape(-1), device="cuda"))
+        plan, surf, views = make_plan(sc, ts=ts, mode=mode)
+        kw = dict(depth_scale=0.1) if dist else {}
+        out = plan.forward(surf, views, **kw)
+        grads.append(plan.backward(surf, views, out, *d[:3], **kw, **(dict(d_dist=d[3]) if dist else {})))
+    for k in GRAD_KEYS:      # each within 1e-3 of the oracle by the bar of these tests
+        assert rel_err(to_np(grads[1][k]), to_np(grads[0][k])) < 2e-3, k
+
+
 def test_workspace_of_smaller_tiles_is_enough_for_larger_ones():
     """The bytes that 8x8 tiles need bind at 16x16 too (no room for contributor masks there)."""
     sc = scene_tiny(seed=18, n=2000)
