@@ -57,6 +57,22 @@ def test_dsm_init_search_edges_match_oracle(nx, ny, n, height):
     np.testing.assert_allclose(to_np(s.t_v), ref["t_v"], atol=2e-6)
 
 
+def test_dsm_init_of_more_blocks_than_the_search_holds_in_lds():
+    """5407 x 3103 cells are 8193 blocks of 2048, one more than the sampler's LDS table has
+    entries: an entry then stands for two blocks, the last one for a single block of 705 cells.
+    A rough last row draws some hundred samples into it."""
+    rng = np.random.default_rng(5)
+    z = rng.uniform(0.0, 0.2, (3104, 5408)).astype(np.float32)
+    z[-1] = rng.uniform(0.0, 20.0, 5408)
+    n = 500_000
+    s, cells = gi.dsm_init(torch.as_tensor(z, device="cuda"), -3.0, 2.0, 0.5, n, seed=78, with_cells=True)
+    ref = odi.dsm_init(z, -3.0, 2.0, 0.5, n, seed=78)
+    assert (ref["cell"] >= 8192 * 2048).sum() > 100
+    np.testing.assert_array_equal(to_np(cells), ref["cell"])
+    # FP64 geometry rounded once to FP32: half an ulp of the heights and coordinates
+    np.testing.assert_allclose(to_np(s.mean), ref["mean"], rtol=1.2e-7, atol=1e-6)
+
+
 def test_dsm_init_5m_surfels_on_the_2km_city():
     spec = synth.config(5)
     x0, g, z = dsm_of(spec)
