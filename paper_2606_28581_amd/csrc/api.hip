@@ -53,7 +53,7 @@ struct Layout {
     size_t views_main, views_sun, suncam, counters, flags;
     size_t mk_a, mk_b, mv_a, mv_b, sorted_main;
     size_t sk_a, sk_b, sv_a, sv_b, sorted_sun;
-    size_t rec_main, tiles_main, counts_main, offs_main, scanparts;
+    size_t rec_main, tiles_main, offs_main, scanparts;
     size_t pk_a, pv_a, pk_b, pv_b, ranges_main, recgrad, colour_parts, dF_parts;
     size_t rec_sun, tiles_sun, counts_sun, offs_sun, qk_a, qv_a, qk_b, qv_b, ranges_sun;
     size_t sun_depth, bounds, radix_temp, tmask_sun, cmask, cmask_bytes, stat_main, stat_sun;
@@ -210,7 +210,6 @@ static Layout make_layout(const ss_plan *p, int64_t cm, int64_t cs)
     L.sorted_sun = take(n * 16 * 4);
     L.rec_main = take(vn * kRecStride4 * 16);
     L.tiles_main = take(vn * sizeof(short4));
-    L.counts_main = take(vn * 4);
     const size_t nrb = (size_t)rank_blocks(p->n) * nv;
     L.offs_main = take((nrb + 1) * 4);
     L.scanparts = take(scan_temp_elems((int64_t)nrb) * 4);
@@ -350,7 +349,7 @@ static ss_status bin_views(ss_plan *p, const ss_views *v, bool sun, const float 
     const ViewDesc *views = p->at<ViewDesc>(sun ? L.views_sun : L.views_main);
     float *rec = p->at<float>(sun ? L.rec_sun : L.rec_main);
     short4 *tiles = p->at<short4>(sun ? L.tiles_sun : L.tiles_main);
-    uint32_t *counts = p->at<uint32_t>(sun ? L.counts_sun : L.counts_main);
+    uint32_t *counts = tmask ? p->at<uint32_t>(L.counts_sun) : nullptr;   // masks are the sun maps'
     uint32_t *offs = p->at<uint32_t>(sun ? L.offs_sun : L.offs_main);
     unsigned long long *counters = p->at<unsigned long long>(L.counters);
     uint32_t *flags = p->at<uint32_t>(L.flags);

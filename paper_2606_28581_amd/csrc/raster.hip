@@ -594,16 +594,6 @@ __device__ __forceinline__ PairEval eval_pair(const float4 r0, const float4 r1, 
     return e;
 }
 
-__device__ __forceinline__ bool box_hits(float bx, float by, int wx0, int wy0)
-{
-    const uint32_t x = __builtin_amdgcn_readfirstlane(__float_as_uint(bx));
-    const uint32_t y = __builtin_amdgcn_readfirstlane(__float_as_uint(by));
-    const int xlo = (int)(int16_t)(x & 0xFFFFu), xhi = (int)(int16_t)(x >> 16);
-    const int ylo = (int)(int16_t)(y & 0xFFFFu), yhi = (int)(int16_t)(y >> 16);
-    return xlo <= wx0 + 7 && xhi >= wx0 && ylo <= wy0 + 7 && yhi >= wy0;
-}
-
-
 // ------------------------------------------------------------- per-pixel coverage
 // chunk_mask: lane t holds record c0 + t of a chunk of up to 64 (valid = t < count);
 // returns, for the calling lane's pixel (wx0 + lane % 8, wy0 + lane / 8), the 64-bit
