@@ -59,8 +59,10 @@ typedef struct ihipStream_t *ss_stream;   /* hipStream_t; NULL = default stream 
 typedef struct ss_raster_settings {
     uint32_t struct_size;   /* sizeof(ss_raster_settings)                              */
     int32_t  tile_size;     /* 8, 16 (paper default, Sec. 3.2) or 32                    */
-    int32_t  batch_depth;   /* surfel records staged in LDS per batch (1..256; capped at
-                               tile_size^2, one record per thread)                      */
+    int32_t  batch_depth;   /* surfel records staged in LDS per batch, 1..256: by the 8x8
+                               forward (at most 64) and by the backward without
+                               contributor masks (at most tile_size^2); other kernels
+                               stage up to 64 whatever it is                            */
     float    alpha_min;     /* skip a surfel at a pixel when alpha < alpha_min (1/255)  */
     float    alpha_max;     /* alpha = min(alpha_max, o * G) (0.99)                     */
     float    T_min;         /* stop before transmittance would drop below T_min (1e-4) */
@@ -393,8 +395,9 @@ ss_status ss_graph_destroy(ss_graph *graph);
  * tile_size 8, the largest pair count, to try all); so are batch depths above the tile's
  * thread count (tile_size^2: one staged record per thread).  Tile sizes whose contributor
  * masks do not fit the bound bytes are timed with the box-test backward (see
- * ss_plan_set_settings).  table (host, may be NULL)
- * receives 12 x 3 doubles: tile, batch, ms (ms < 0: skipped). */
+ * ss_plan_set_settings); with masks the depths of 16x16 and 32x32 tiles run the same
+ * kernels.  table (host, may be NULL) receives 12 x 3 doubles: tile, batch, ms
+ * (ms < 0: skipped). */
 ss_status ss_autotune(ss_plan *plan, const ss_surfels *s, const ss_views *v,
                       const ss_step_io *io, int32_t reps, ss_raster_settings *best,
                       double *best_ms, double *table, ss_stream stream);
@@ -440,7 +443,7 @@ ss_status ss_mlp_backward(ss_mlp *mlp, const float *w, const float *pts, const f
 /* Allocation-free variant of ss_mlp_backward, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight training or serving loops, harnesses that
  * forbid hipMalloc).  Same arguments, outputs and rounding as ss_mlp_backward (the same
- * kernels run), but the MLP needs no bound workspace: the buffers live in a fixed device
+ * two kernels run), but the MLP needs no bound workspace: the buffers live in a fixed device
  * array inside the library of 8.2 MiB per device (held from library load until the
  * process ends), laid out for M <= SS_NOALLOC_MAX_POINTS points; a larger M returns
  * SS_ERR_CAPACITY and launches nothing.  The call allocates nothing, device or host

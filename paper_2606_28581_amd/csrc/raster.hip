@@ -1063,10 +1063,13 @@ static int64_t raster_blocks(int sub, int32_t ntiles)
 }
 
 // Depth-only maps of larger tiles with at least this many surfels per tile take the blocks whose
-// waves read the list together (SHARE).  20 sun maps, one wave a block -> shared, by surfels
-// per tile: 16x16 tiles 244: kernel 1580 -> 2012 us; whole pass 488: 1600 -> 1738, 684: 2253 -> 2255, 879:
-// 2923 -> 2765, 1172: 3927 -> 3614; 32x32 tiles 293: 1637 -> 1840, 977: 4140 -> 3893, 1172: 1355 -> 1304, 4688:
-// 7527 -> 4141.
+// waves read the list together (SHARE).  Whole passes of 20 sun maps, one wave a block -> shared,
+// by surfels per tile, in us:
+//   512^2 maps, 16x16 tiles   293: 1083 -> 1202   488: 1600 -> 1738   684: 2253 -> 2255
+//                             879: 2923 -> 2765  1172: 3927 -> 3614
+//   512^2 maps, 32x32 tiles   234:  480 ->  532  1172: 1355 -> 1304  4688: 7527 -> 4141
+//   1024^2 maps, 32x32 tiles  293: 1637 -> 1840   977: 4140 -> 3893
+// The kernel alone at 1024^2 and 16x16: 244: 1580 -> 2012 us, 1221: 9.9 -> 8.0 ms.
 constexpr int64_t kShareSurfels = 768;
 
 template <int TS, bool DO, bool HV>
@@ -1519,8 +1522,8 @@ __global__ __launch_bounds__(TS *TS) __attribute__((amdgpu_waves_per_eu(TS == 8 
         const float4 *src_ = recv + (size_t)qidx * kRecStride4;                           \
         q0 = src_[0]; q1 = src_[1]; q2 = src_[2]; q3 = src_[3]; q4 = src_[4]; q5 = src_[5]; \
     }
-    // batches on the forward's grid ([k * batch, (k + 1) * batch) from the list start),
-    // back to front; the first one is cut at the tile's largest `last`
+    // batches [k * batch, (k + 1) * batch) of the list, back to front; the first one is cut at
+    // the tile's largest `last`
     const int nbat = (blk_last + batch - 1) / batch;
     if (nbat > 0) {
         const int bb0 = (nbat - 1) * batch;
@@ -1673,10 +1676,15 @@ __device__ __forceinline__ float rows_prefix_add(float x, bool odd, bool upper, 
 // albedo with visibility, normal with the record's rank.
 constexpr int kBwdVec4 = 5;
 // Launches of up to this many 8x8 blocks give every quadrant a wave of its own (SPLIT): a chip
-// holds 4096-5120 of these waves, so fewer blocks leave it to its longest ones.  Backward of
-// 8x8 tiles, one wave a block -> four: 1024 blocks 86 -> 35 us, 8192 152 -> 106, 15,625 151 -> 141;
-// of 16x16 tiles, whose four waves each stage the whole block's records: 1024 99 -> 52, 7744 128 ->
-// 116, 12,100 136 -> 153.
+// holds 4096-5120 of these waves, so fewer blocks leave it to its longest ones.  With larger tiles
+// the four waves each stage the whole block's records.  Backward stage of one view, one wave a
+// block -> four, in us (in brackets with the distortion, whose four-wave form costs 5-12 % more):
+//    8x8:  1024 blocks 113 ->  45 (119 ->  47)    8100: 168 -> 124 (169 -> 133)
+//         15,625: 243 -> 214 (247 -> 235)       19,044: 268 -> 260 (268 -> 287)
+//   16x16: 1024 blocks 132 ->  67 (133 ->  68)    8128: 194 -> 166 (184 -> 178)
+//         10,816: 220 -> 215 (223 -> 233)       13,024: 226 -> 234 (224 -> 255)
+//   32x32: 1024 blocks 135 ->  71 (140 ->  73)    4096: 165 -> 151 (170 -> 162)
+//           6400: 167 -> 162 (171 -> 179)         8576: 197 -> 204 (200 -> 222)
 constexpr int64_t bwd_split(int ts) { return ts == 8 ? 16384 : 8192; }
 
 template <int TS, bool HAS_VIS, bool DIST, bool FILT, bool SPLIT>
